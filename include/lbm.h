@@ -144,7 +144,10 @@ lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_
  * context's stream and, on a second stream created by the library (default priority,
  * ordered with the caller's stream by events), the launches next to the walled rows.  A
  * single step is two launches: the interior columns, then the columns next to the walls
- * x = 0, x = nx - 1 together with the walled rows. */
+ * x = 0, x = nx - 1 together with the walled rows.  Grids up to about 1.4 (FP64), 2.5 (FP32)
+ * and 2 (FP16) million nodes run, until lbm_set_fusion is called, as launches of several
+ * steps (up to 8, any number on a grid of at most 512 nodes) whose blocks keep a tile of the
+ * grid in LDS; the results are again bitwise those of single steps. */
 lbm_status lbm_step(lbm_ctx *ctx, int64_t nsteps);
 
 /* Non-finite detection inside lbm_step: with every > 0, whenever the context's time
@@ -156,7 +159,9 @@ lbm_status lbm_step(lbm_ctx *ctx, int64_t nsteps);
 lbm_status lbm_set_check_interval(lbm_ctx *ctx, int64_t every);
 
 /* Time steps per pass, 1 or 2.  The default is 2 for FP64 and FP32 storage when nx >= 4
- * and ny >= 8, else 1 (FP16 storage is faster with one step per pass).
+ * and ny >= 8, else 1 (FP16 storage is faster with one step per pass); smaller grids take
+ * more steps per launch by default (lbm_step), and exactly the given passes after this call.
+ * lbm_step_timed always runs the passes.
  * LBM_ERR_UNSUPPORTED for 2 on smaller grids. */
 lbm_status lbm_set_fusion(lbm_ctx *ctx, int32_t steps_per_pass);
 int32_t lbm_fusion(const lbm_ctx *ctx);

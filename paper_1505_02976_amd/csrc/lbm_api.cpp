@@ -217,6 +217,7 @@ struct lbm_ctx {
     int in_batch;
     int cur;             // buffer holding the current populations (0: a, 1: b)
     int fuse;            // time steps per pass over the populations (1 or 2)
+    lbm::TilePlan tile;  // several steps per launch (ns > 0: lbm_step takes it until lbm_set_fusion is called)
     int64_t check_every; // lbm_step checks for non-finite populations at multiples of this time (0: never)
     lbm::KParams kpm;    // parameters of the eight-row scratch grid of the two-step pass
     int n_main2, n_full2;       // wavefronts of the two-step pass's main and full launches
@@ -304,6 +305,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
     // two-step passes by default where they are faster: FP32 and FP64 storage, whose tiles
     // match the two-step wavefronts (see lbm_step2.hip)
     c->fuse = (params->storage != LBM_F16 && lbm::step2_supported(kp)) ? 2 : 1;
+    c->tile = lbm::tile_plan(params->storage, kp);
     c->n_main2 = c->n_full2 = 0;
     c->main_nodes2 = 0;
     if (lbm::step2_supported(kp)) {
@@ -419,7 +421,20 @@ hipError_t run_steps(lbm_ctx *c, int64_t nsteps, const StepEvents *tev, int ever
     hipError_t e = hipSuccess;
     const int sto = c->prm.storage;
     int64_t s = 0, gi = 0;
-    if (c->fuse == 2 && nsteps >= 2) {
+    if (c->tile.ns > 0 && !tev) {
+        // as few launches as the plan allows, of equal numbers of steps to within one
+        int64_t launches = (nsteps + c->tile.ns - 1) / c->tile.ns;
+        for (; launches > 0 && e == hipSuccess; --launches) {
+            const int n = (int)((nsteps - s + launches - 1) / launches);
+            e = lbm::launch_tile(sto, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
+            if (e == hipSuccess) {
+                c->t += n;
+                s += n;
+                c->cur ^= 1;
+            }
+        }
+    }
+    if (c->fuse == 2 && nsteps - s >= 2 && e == hipSuccess) {
         const int64_t npass = nsteps / 2;
         e = run_passes(c, npass, tev, every, 0);
         s = 2 * npass;
@@ -559,6 +574,7 @@ lbm_status lbm_set_fusion(lbm_ctx *c, int32_t steps_per_pass)
     if (steps_per_pass == 2 && !lbm::step2_supported(c->kp))
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need nx >= 4 and ny >= 8");
     c->fuse = steps_per_pass;
+    c->tile.ns = 0;
     return LBM_OK;
 }
 

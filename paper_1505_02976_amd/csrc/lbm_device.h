@@ -687,39 +687,60 @@ __device__ __forceinline__ R gather_Td(const S *__restrict__ src, const KParams 
 // G and F (Eq. ForceEq) at u_b and T_b.  The node collides with that state (wall_collide),
 // which gives the post-collision form of the extrapolation,
 // f^eq(x_b) + (1 - 1/tau) f^neq(x_f) plus the source terms.
-template <typename R, bool PRE = true>
-__device__ __forceinline__ void wall_from_ref(const KParams &P, const Cst<R> &k, int x, int y,
-                                              const EpsC<R> &ef, const EpsC<R> &eb,
-                                              const R *ff, const R *gf, R Tdff, R *f, R *g,
-                                              Macro<R> &mb)
-{
-    const WallInfo w = wall_info(P, x, y);
-    Macro<R> mf;
-    const R T0 = R(P.T0);
-    node_macro_full<R, PRE>(ff, gf, T0, k, ef, mf);
-    const R Tf = T0 + mf.Td;
-    const R epf = ef.eps * mf.p;
+// Constants of a wall node (x, y) in R: wall velocity and speed (zero at corners), T - T0 of
+// its isothermal wall (iso), or the prescribed components of grad T (px, py).
+template <typename R> struct WallC {
+    R ux, uy, um, Td, gx, gy;
+    R dx, dy;
+    bool iso, px, py;
+};
 
-    R ubx = R(0), uby = R(0);
-    double ubm = 0.0;              // |u_b|, a constant of the wall
+template <typename R> __device__ __forceinline__ WallC<R> wall_consts(const KParams &P, const WallInfo &w)
+{
+    WallC<R> c;
+    c.ux = R(0);
+    c.uy = R(0);
+    double um = 0.0;               // |u_b|, a constant of the wall
     const int vw = (w.xw >= 0 && w.yw < 0) ? w.xw : (w.yw >= 0 && w.xw < 0) ? w.yw : -1;
     if (vw >= 0) {
-        ubx = R(P.wall_ux[vw]);
-        uby = R(P.wall_uy[vw]);
-        ubm = sqrt(P.wall_ux[vw] * P.wall_ux[vw] + P.wall_uy[vw] * P.wall_uy[vw]);
+        c.ux = R(P.wall_ux[vw]);
+        c.uy = R(P.wall_uy[vw]);
+        um = sqrt(P.wall_ux[vw] * P.wall_ux[vw] + P.wall_uy[vw] * P.wall_uy[vw]);
     }
+    c.um = R(um);
+    const int dir = thermal_dirichlet_wall(P, w);
+    c.iso = dir >= 0;
+    c.px = !c.iso && w.xw >= 0;
+    c.py = !c.iso && w.yw >= 0;
+    c.Td = c.iso ? R(P.wall_T[dir] - P.T0) : R(0);
+    c.gx = c.px ? R(w.dx * P.wall_dTdn[w.xw]) : R(0);
+    c.gy = c.py ? R(w.dy * P.wall_dTdn[w.yw]) : R(0);
+    c.dx = R(w.dx);
+    c.dy = R(w.dy);
+    return c;
+}
+
+// wall_from_state takes the state mf of x_f as well (node_macro_full of ff, gf at ef) and
+// the wall node's constants: a kernel whose wall nodes pull at x_f computes mf with the code
+// of its other nodes, and one that takes several steps forms the constants once.
+template <typename R>
+__device__ __forceinline__ void wall_from_state(R T0, const Cst<R> &k, const WallC<R> &w,
+                                                const EpsC<R> &ef, const EpsC<R> &eb, const Macro<R> &mf,
+                                                const R *ff, const R *gf, R Tdff, R *f, R *g,
+                                                Macro<R> &mb)
+{
+    const R Tf = T0 + mf.Td;
+    const R epf = ef.eps * mf.p;
+    const R ubx = w.ux, uby = w.uy;
     const R epb = eb.eps * mf.p;   // eps at the wall node, pressure of x_f
 
-    const int dir = thermal_dirichlet_wall(P, w);
-    R Tdb, gbx, gby;
-    if (dir >= 0) {
-        Tdb = R(P.wall_T[dir] - P.T0);
-        gbx = mf.gx;
-        gby = mf.gy;
+    R Tdb, gbx = mf.gx, gby = mf.gy;
+    if (w.iso) {
+        Tdb = w.Td;
     } else {
-        gbx = (w.xw >= 0) ? R(w.dx * P.wall_dTdn[w.xw]) : mf.gx;
-        gby = (w.yw >= 0) ? R(w.dy * P.wall_dTdn[w.yw]) : mf.gy;
-        Tdb = (R(4) * mf.Td - Tdff - R(2) * (R(w.dx) * gbx + R(w.dy) * gby)) * R(1.0 / 3.0);
+        if (w.px) gbx = w.gx;
+        if (w.py) gby = w.gy;
+        Tdb = (R(4) * mf.Td - Tdff - R(2) * (w.dx * gbx + w.dy * gby)) * R(1.0 / 3.0);
     }
     const R Tb = T0 + Tdb;
 
@@ -749,7 +770,7 @@ __device__ __forceinline__ void wall_from_ref(const KParams &P, const Cst<R> &k,
     mb.Td = Tdb;
     mb.ux = ubx;
     mb.uy = uby;
-    const R dl = eb.dlin + eb.dquad * R(ubm);
+    const R dl = eb.dlin + eb.dquad * w.um;
     mb.Fx = eb.eps * k.ax - dl * ubx;
     mb.Fy = eb.eps * (k.ay + k.gb * Tdb) - dl * uby;
     mb.p = mf.p;
@@ -758,6 +779,17 @@ __device__ __forceinline__ void wall_from_ref(const KParams &P, const Cst<R> &k,
     mb.Syy = mf.Syy;
     mb.gx = gbx;
     mb.gy = gby;
+}
+
+template <typename R, bool PRE = true>
+__device__ __forceinline__ void wall_from_ref(const KParams &P, const Cst<R> &k, int x, int y,
+                                              const EpsC<R> &ef, const EpsC<R> &eb,
+                                              const R *ff, const R *gf, R Tdff, R *f, R *g,
+                                              Macro<R> &mb)
+{
+    Macro<R> mf;
+    node_macro_full<R, PRE>(ff, gf, R(P.T0), k, ef, mf);
+    wall_from_state<R>(R(P.T0), k, wall_consts<R>(P, wall_info(P, x, y)), ef, eb, mf, ff, gf, Tdff, f, g, mb);
 }
 
 // Collision of wall node (x, y) with the state mb the boundary scheme assigned to it.
@@ -779,6 +811,17 @@ __device__ __forceinline__ void wall_populations(const S *__restrict__ src, cons
     R Tdff = R(0);
     if (thermal_dirichlet_wall(P, w) < 0) Tdff = gather_Td<S, R>(src, P, k, x + 2 * w.dx, y + 2 * w.dy);
     wall_from_ref<R, PRE>(P, k, x, y, eps_at<R>(P, x + w.dx, y + w.dy), eps_at<R>(P, x, y), ff, gf, Tdff, f, g, mb);
+}
+
+// Logical block of dispatched block b out of nb: blocks are dealt round-robin to the eight
+// XCDs, each with its own L2; this hands every XCD one contiguous range of logical blocks,
+// so that the neighbouring wavefronts whose halo columns and rows overlap share an L2.
+__device__ __forceinline__ int xcd_block(int b, int nb)
+{
+    constexpr int X = 8;
+    const int per = nb / X, rem = nb % X;
+    const int x = b % X, i = b / X;
+    return x * per + min(x, rem) + i;
 }
 
 // Wall-node slot s -> (x, y); returns false for slots that are not wall nodes of this

@@ -109,6 +109,22 @@ hipError_t launch_batch_step2(int storage, const BatchProblem *probs, const int2
                               const int2 *rows, int nrows, int parity, int main_waves, hipStream_t st_main,
                               hipStream_t st_side);
 
+// Several steps per launch, one LDS-resident tile per block (lbm_tile.hip).
+struct TileGrid {
+    int nbx, nby;         // tiles per row and per column
+    int tw, th, rx, ry;   // tile size; the first rx (ry) tiles are one node wider (higher)
+    unsigned magic;       // floor(2^32 / nbx) + 1, to divide by nbx
+};
+struct TilePlan {
+    int ns;               // steps per launch at most (0: this grid does not take the path)
+    TileGrid g;
+};
+TilePlan tile_plan(int storage, const KParams &P);
+// 1 <= ns <= t.ns steps from src into dst; hist != 0 stores every step, step s at element
+// offset (s - 1) hist of dst.
+hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TilePlan &t, int ns,
+                       long long hist, hipStream_t st);
+
 // Adjoint sweep.
 hipError_t launch_adjoint_step(int storage, const void *state, const KParams &P, const AdjBufs &A,
                                hipStream_t st);

@@ -361,17 +361,6 @@ __device__ __forceinline__ void march2(const S *__restrict__ src, S *__restrict_
     }
 }
 
-// Logical block of dispatched block b out of nb: blocks are dealt round-robin to the eight
-// XCDs, each with its own L2; this hands every XCD one contiguous range of logical blocks,
-// so that the neighbouring wavefronts whose halo columns and rows overlap share an L2.
-__device__ __forceinline__ int xcd_block(int b, int nb)
-{
-    constexpr int X = 8;
-    const int per = nb / X, rem = nb % X;
-    const int x = b % X, i = b / X;
-    return x * per + min(x, rem) + i;
-}
-
 // One wavefront's walk with the instance chosen at run time: the main launch runs the lean
 // and the xwall wavefronts (both about 135 VGPRs), the full launch the full ones.
 // w: wavefront index cyi * ncx + cxi.  PRE: the collision's constant products read from

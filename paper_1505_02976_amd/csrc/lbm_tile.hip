@@ -1,0 +1,331 @@
+// Several time steps per launch: a block keeps a tile of nodes in LDS.
+//
+// Small grids are bound by latency, not by memory or arithmetic: a step of 128 x 128 nodes
+// is 256 wavefronts on 1024 SIMDs, so what a step costs is the launches (about 4 us each
+// with their kernel's start and end), the events between the two streams of a two-step pass
+// and the serial walk of its wavefronts.  Here one launch advances the whole grid by ns
+// steps.  A block owns a rectangular tile and starts from its nodes and ns - 1 more on every
+// side; step s computes the nodes within ns - s of the tile (fewer each step; a side that is
+// a wall of the grid does not shrink), one per thread, the first step pulling from the source
+// buffer, the later ones from LDS, where every step leaves its post-collision populations as
+// the one-step path would store them.  Tiles recompute their overlap; no block waits for
+// another.  Every node update is the one-step node code with the same inputs, so ns steps
+// here are bitwise ns single steps.
+//
+// A wall node pulls at its reference node x_f and shares the state computation with the
+// other nodes, so that a wall wavefront adds only the boundary scheme to its chain.  The
+// scheme reaches three nodes inward (x_f, x_ff and their pulls), which the tile holds: tiles
+// are at least four nodes wide wherever there is more than one.
+//
+// Blocks are dealt to the XCDs in contiguous ranges (xcd_block), so that neighbouring tiles,
+// whose halos share cache lines, share an L2: without it a 250 x 250 FP32 launch of one step
+// took 10.1 us instead of 6.7.
+//
+// Measured (one step, 100-step calls, two-step passes before): 128 x 128 FP64 27 -> 2.6 us,
+// 250 x 250 FP32 22 -> 3.0 us, 512 x 512 FP32 25 -> 7.5 us, 1300 x 1300 FP32 43 -> 34 us; a
+// grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
+#include "lbm_kernels.h"
+
+namespace lbm {
+
+constexpr int TILE_NT = 512;      // nodes of the largest region, threads of the largest block
+
+// Stored value in LDS (what the one-step path would store).
+__device__ __forceinline__ void lds_put(double *p, double v, float) { *p = v; }
+__device__ __forceinline__ void lds_put(float *p, float v, float) { *p = v; }
+__device__ __forceinline__ void lds_put(__half *p, float v, float scale) { *p = __float2half(v * scale); }
+
+// The launch constants as a kernel of several steps uses them: read again by scalar loads in
+// every step.  Kept across the loop they, and the products the compiler forms of them ahead
+// of it, take vector registers.
+using KConst = const __attribute__((address_space(4))) KParams *;
+
+__device__ __forceinline__ KConst fresh(KConst p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+template <typename T, typename U>
+__device__ __forceinline__ void copy_consts(T *d, const __attribute__((address_space(4))) U *q)
+{
+    static_assert(sizeof(T) % sizeof(U) == 0, "a struct of U only");
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / sizeof(U)); ++i) reinterpret_cast<U *>(d)[i] = q[i];
+}
+__device__ __forceinline__ void load_consts(KConst p, Cst<float> &k)
+{
+    copy_consts(&k, (const __attribute__((address_space(4))) float *)&p->cf);
+}
+__device__ __forceinline__ void load_consts(KConst p, Cst<double> &k)
+{
+    copy_consts(&k, (const __attribute__((address_space(4))) double *)&p->cd);
+}
+__device__ __forceinline__ void load_eps(KConst p, EpsC<float> &e)
+{
+    e.epsd = p->eps; e.c0 = p->c0; e.c1 = p->c1;
+    e.eps = p->ef.eps; e.ieps = p->ef.ieps; e.dlin = p->ef.dlin; e.dquad = p->ef.dquad; e.bM = p->ef.bM;
+}
+__device__ __forceinline__ void load_eps(KConst p, EpsC<double> &e)
+{
+    e.epsd = p->eps; e.c0 = p->c0; e.c1 = p->c1;
+    e.eps = p->ed.eps; e.ieps = p->ed.ieps; e.dlin = p->ed.dlin; e.dquad = p->ed.dquad; e.bM = p->ed.bM;
+}
+
+// Region of a tile: the nodes of the launch's first step.
+struct TileRegion {
+    int X0, X1, Y0, Y1;              // the tile (written by this block)
+    int xlo, xhi, ylo, yhi;
+    bool oxl, oxh, oyl, oyh;         // sides that shrink by one node per step
+    bool walls;                      // holds a wall node
+};
+
+__device__ __forceinline__ TileRegion tile_region(const KParams &P, const TileGrid &g, int b, int ns)
+{
+    TileRegion t;
+    const int ty = g.nbx == 1 ? b : (int)(((unsigned long long)(unsigned)b * g.magic) >> 32);   // b / nbx
+    const int tx = b - ty * g.nbx;
+    t.X0 = tx * g.tw + min(tx, g.rx); t.X1 = t.X0 + g.tw + (tx < g.rx ? 1 : 0);
+    t.Y0 = ty * g.th + min(ty, g.ry); t.Y1 = t.Y0 + g.th + (ty < g.ry ? 1 : 0);
+    t.xlo = t.X0 - (ns - 1); t.xhi = t.X1 + (ns - 1); t.ylo = t.Y0 - (ns - 1); t.yhi = t.Y1 + (ns - 1);
+    t.oxl = t.oxh = t.oyl = t.oyh = true;
+    if (g.nbx == 1 || (!P.px && t.xlo <= 0)) { t.xlo = 0; t.oxl = false; }
+    if (g.nbx == 1 || (!P.px && t.xhi >= P.nx)) { t.xhi = P.nx; t.oxh = false; }
+    if (g.nby == 1 || (!P.py && t.ylo <= 0)) { t.ylo = 0; t.oyl = false; }
+    if (g.nby == 1 || (!P.py && t.yhi >= P.ny)) { t.yhi = P.ny; t.oyh = false; }
+    t.walls = (!P.px && (!t.oxl || !t.oxh)) || (!P.py && (!t.oyl || !t.oyh));
+    return t;
+}
+
+// ns steps of one tile.  lds: 18 planes of TILE_NT values, [q][node of the region].  WALLS: the
+// region holds wall nodes.  WRAP: it spans the grid along a periodic direction (wx, wy),
+// whose pulls wrap inside it.  hist != 0: every step s is stored, at dst + (s - 1) hist.
+template <typename S, bool FIELD, bool WALLS, bool WRAP>
+__device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restrict__ dst, const KParams &P,
+                                           KConst Pc, const TileRegion &t, bool wx, bool wy, int ns, long long hist,
+                                           S *__restrict__ lds)
+{
+    using R = typename Prec<S>::R;
+    const int rw = t.xhi - t.xlo, rh = t.yhi - t.ylo;
+    // threadIdx.x / rw (exact: the quotient is at least 1 / (2 rw) away from the next integer)
+    const int ly = (int)(((float)threadIdx.x + 0.5f) * __builtin_amdgcn_rcpf((float)rw)), lx = (int)threadIdx.x - ly * rw;
+    int x = t.xlo + lx, y = t.ylo + ly;
+    const bool own = ly < rh && x >= t.X0 && x < t.X1 && y >= t.Y0 && y < t.Y1;
+    if (P.px) x = ((x % P.nx) + P.nx) % P.nx;
+    if (P.py) y = ((y % P.ny) + P.ny) % P.ny;
+    // the last step the node takes: all for the block's own nodes, one less per node of
+    // distance from the tile towards a side that shrinks (0: no node of the region)
+    int last = ns;
+    if (!own) {
+        last = ns - 1;
+        if (t.oxl) last = min(last, lx + 1);
+        if (t.oxh) last = min(last, rw - lx);
+        if (t.oyl) last = min(last, ly + 1);
+        if (t.oyh) last = min(last, rh - ly);
+        if (ly >= rh) last = 0;
+    }
+    WallInfo w = {-1, -1, 0, 0};
+    if (WALLS) w = wall_info(P, x, y);
+    const bool wall = WALLS && (w.xw >= 0 || w.yw >= 0);
+    const int xr = x + w.dx, yr = y + w.dy;               // where the node pulls: itself, or x_f
+    const int nff = w.dx + w.dy * rw;                     // from the node to x_f, and to x_ff from there
+    S *const L = lds + (ly * rw + lx);
+    const S *const r0 = L + nff;
+    // steps to the columns x -+ 1 and rows y -+ 1 of the node it pulls at
+    const int lxr = lx + w.dx, lyr = ly + w.dy;
+    const int cm = WRAP && wx && lxr == 0 ? rw - 1 : -1, cp = WRAP && wx && lxr == rw - 1 ? 1 - rw : 1;
+    const int rm = WRAP && wy && lyr == 0 ? (rh - 1) * rw : -rw, rp = WRAP && wy && lyr == rh - 1 ? (1 - rh) * rw : rw;
+    EpsC<R> er, eo;                                       // at the pulled node, at the node itself
+    WallC<R> wc = {};
+    R f[9], g[9], Tdff = R(0);
+    if (last > 0) {
+        if (FIELD) er = eo = eps_coeffs<R>(P, P.eps_field[(long long)yr * P.nx + xr]);
+        if (wall) {
+            wc = wall_consts<R>(P, w);
+            if (FIELD) eo = eps_coeffs<R>(P, P.eps_field[(long long)y * P.nx + x]);
+        }
+    }
+    const bool neumann = wall && !wc.iso;
+    if (last > 0) {
+        gather<S, R>(src, P, xr, yr, f, g);
+        if (neumann) Tdff = gather_Td<S, R>(src, P, cst<R>(P), x + 2 * w.dx, y + 2 * w.dy);
+    }
+    const int store_from = hist ? 1 : ns;
+#pragma clang loop unroll(disable)
+    for (int s = 1;; ++s) {
+        const KConst pc = fresh(Pc);
+        Cst<R> k;
+        load_consts(pc, k);
+        const R T0 = R(pc->T0);
+        const float hinv = pc->hinv, hscale = pc->hscale;
+        if (!FIELD) { load_eps(pc, er); eo = er; }
+        if (s <= last) {
+            Macro<R> m;
+            node_macro_full<R>(f, g, T0, k, er, m);
+            if (wall) {
+                Macro<R> mb;
+                wall_from_state<R>(T0, k, wc, er, eo, m, f, g, Tdff, f, g, mb);
+                m = mb;
+            }
+            node_collide<R>(f, g, m, T0, k, WALLS ? eo : er);
+            if (own && s >= store_from) store_node<S, R>(dst + (s - 1) * hist, P, x, y, f, g);
+        }
+        if (s == ns) break;
+        if (s <= last) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                lds_put(L + i * TILE_NT, f[i], hscale);
+                lds_put(L + (9 + i) * TILE_NT, g[i], hscale);
+            }
+        }
+        __syncthreads();
+        if (s < last) {
+            const S *const qm = r0 + rm, *const qp = r0 + rp;
+            const S *const b[9] = {r0, r0 + cm, qm, r0 + cp, qp, qm + cm, qm + cp, qp + cp, qp + cm};
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                f[i] = R(Store<S>::ld(b[i] + i * TILE_NT, hinv));
+                g[i] = R(Store<S>::ld(b[i] + (9 + i) * TILE_NT, hinv));
+            }
+            if (neumann) {
+                R sg = R(0);
+#pragma unroll
+                for (int i = 0; i < 9; ++i) sg += R(Store<S>::ld(b[i] + nff + (9 + i) * TILE_NT, hinv));
+                Tdff = (sg + k.halfQ) * k.isig;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+template <typename S, bool FIELD>
+__device__ __forceinline__ void tile_block(const S *__restrict__ src, S *__restrict__ dst, const KParams &P, KConst Pc,
+                                           const TileGrid &g, int b, int ns, long long hist, S *__restrict__ lds)
+{
+    const TileRegion t = tile_region(P, g, b, ns);
+    const bool wx = P.px && g.nbx == 1, wy = P.py && g.nby == 1;
+    if (wx || wy) tile_steps<S, FIELD, true, true>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+    else if (t.walls) tile_steps<S, FIELD, true, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+    else tile_steps<S, FIELD, false, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+}
+
+// P is the third parameter: it starts 16 bytes into the kernel's parameter segment.
+template <typename S, bool FIELD>
+__global__ void __launch_bounds__(TILE_NT)
+k_tile(const S *__restrict__ src, S *__restrict__ dst, KParams P, TileGrid g, int ns, long long hist)
+{
+    __shared__ S lds[18 * TILE_NT];
+    const KConst Pc = (KConst)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + 16);
+    tile_block<S, FIELD>(src, dst, P, Pc, g, xcd_block(blockIdx.x, gridDim.x), ns, hist, lds);
+}
+
+// Tiles of at most tw x th nodes (of equal size to within one node).
+static TileGrid tile_grid(const KParams &P, int tw, int th)
+{
+    TileGrid g;
+    g.nbx = (P.nx + tw - 1) / tw;
+    g.nby = (P.ny + th - 1) / th;
+    g.tw = P.nx / g.nbx; g.rx = P.nx % g.nbx;
+    g.th = P.ny / g.nby; g.ry = P.ny % g.nby;
+    g.magic = g.nbx > 1 ? (unsigned)(0x100000000ull / g.nbx + 1) : 0;
+    return g;
+}
+
+// Largest region of a launch of ns steps: its width and height.
+static void tile_extent(const TileGrid &g, int ns, int &w, int &h)
+{
+    w = g.tw + (g.rx ? 1 : 0) + (g.nbx > 1 ? 2 * (ns - 1) : 0);
+    h = g.th + (g.ry ? 1 : 0) + (g.nby > 1 ? 2 * (ns - 1) : 0);
+}
+
+static int tile_threads(const TileGrid &g, int ns)
+{
+    int w, h;
+    tile_extent(g, ns, w, h);
+    return (w * h + 63) / 64 * 64;
+}
+
+template <typename S>
+static hipError_t tile_t(const void *src, void *dst, const KParams &P, const TilePlan &t, int ns, long long hist,
+                         hipStream_t st)
+{
+    const dim3 grid(t.g.nbx * t.g.nby), block(tile_threads(t.g, ns));
+    if (P.field)
+        hipLaunchKernelGGL((k_tile<S, true>), grid, block, 0, st, (const S *)src, (S *)dst, P, t.g, ns, hist);
+    else
+        hipLaunchKernelGGL((k_tile<S, false>), grid, block, 0, st, (const S *)src, (S *)dst, P, t.g, ns, hist);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TilePlan &t, int ns,
+                       long long hist, hipStream_t st)
+{
+    if (ns < 1 || ns > t.ns) return hipErrorInvalidValue;
+    switch (storage) {
+    case 0: return tile_t<double>(src, dst, P, t, ns, hist, st);
+    case 1: return tile_t<float>(src, dst, P, t, ns, hist, st);
+    case 2: return tile_t<__half>(src, dst, P, t, ns, hist, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// Tiles and steps per launch for one grid.
+//
+// A grid of at most TILE_NT nodes is one block, which needs no overlap and takes any number
+// of steps per launch.  Otherwise the tiles and steps of least estimated time per step are
+// taken.  Per launch the estimate adds, in units of a round's fixed cost (launch, first
+// loads, last stores: 4-6 us): one for each round of blocks on the 256 CUs; 0.05 for every step of a
+// round (its chain of dependent instructions and two barriers); 0.12 for every node update
+// that a SIMD issues for a wavefront.  Over 875 measured combinations on nine grids from
+// 48 x 90 to 1300 x 1201 nodes the choice costs 3 % (FP64, FP16) and 5 % (FP32) more on average
+// than the best one.
+//
+// Grids above TILE_NODES nodes take the two-step pass (FP16: single steps), which is bound by
+// HBM and recomputes less: FP32 1536^2 46 us per step here against 53, 2048^2 102 against 79;
+// FP64 1024^2 45 against 53, 1300 x 1201 65 against 63; FP16 1300 x 1201 30 against 35, 2048^2 73
+// against 68.  With a porosity field, whose coefficients a tile forms once per launch, FP64
+// gains up to 1537 x 1025 (66 against 74).
+constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
+constexpr long long TILE_NODES[3] = {1400000, 2500000, 2000000}, TILE_NODES_FIELD = 2000000;
+
+TilePlan tile_plan(int storage, const KParams &P)
+{
+    TilePlan best = {};
+    const long long n = (long long)P.nx * P.ny;
+    if (n <= TILE_NT) {
+        best.ns = TILE_ALL_STEPS;
+        best.g = tile_grid(P, P.nx, P.ny);
+        return best;
+    }
+    if (n > (storage == 0 && P.field ? TILE_NODES_FIELD : TILE_NODES[storage])) return best;
+    static const int shapes[][2] = {{8, 8}, {12, 8}, {16, 8}, {32, 8}, {12, 12}, {16, 12}, {16, 16},
+                                    {20, 20}, {28, 12}, {26, 10}, {30, 14}};
+    const int resident = storage == 0 ? 8 : 16;   // wavefronts of this kernel that a CU's registers hold
+    double cost = 0.0;
+    for (const auto &sh : shapes) {
+        const TileGrid g = tile_grid(P, sh[0], sh[1]);
+        if ((g.nbx > 1 && g.tw < 4) || (g.nby > 1 && g.th < 4)) continue;
+        const long long nb = (long long)g.nbx * g.nby;
+        if (nb > 0x7fffffff / g.nbx) continue;
+        for (int ns = 1; ns <= TILE_MAX_STEPS; ++ns) {
+            int w, h;
+            tile_extent(g, ns, w, h);
+            if (w * h > TILE_NT) break;
+            const int waves = (w * h + 63) / 64;
+            const long long cus = 256, percu = std::max(1, resident / waves);
+            const double rounds = (double)((nb + cus * percu - 1) / (cus * percu));
+            int updates = 0;      // wavefronts of a block that update nodes, over the steps
+            for (int s = 0; s < ns; ++s) updates += (w * (g.nby > 1 ? h - 2 * s : h) + 63) / 64;
+            const double simd = (double)((nb + cus - 1) / cus) * updates / 4.0;
+            const double c = (rounds + 0.05 * rounds * ns + 0.12 * simd) / ns;
+            if (best.ns == 0 || c < cost) {
+                cost = c;
+                best.ns = ns;
+                best.g = g;
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace lbm
