@@ -251,8 +251,10 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
  * stream of the batch beside its main launch, ordered by events; the call is ordered like
  * launches on the batch's stream), then one single step if nsteps is odd.  With one step
  * per pass: whole HIP graphs of 64 steps (built on the first call that needs one), then
- * single steps.  Results are bitwise those of lbm_step on each problem alone.
- * Asynchronous. */
+ * single steps.  Batches of up to about 2 (FP64) and 4 (FP32) million nodes, and FP16 batches of
+ * grids of up to about 2 million each on average, run, until lbm_batch_set_fusion or
+ * lbm_batch_set_width is called, as launches of several steps on tiles, as lbm_step's small grids
+ * do.  Results are bitwise those of lbm_step on each problem alone.  Asynchronous. */
 lbm_status lbm_batch_step(lbm_batch *batch, int64_t nsteps);
 
 /* Time steps per batched pass, 1 or 2 (as lbm_set_fusion, for all problems at once).  The
@@ -282,7 +284,8 @@ lbm_status lbm_batch_autotune(lbm_batch *batch, int32_t steps, int32_t *width, d
 
 /* Sets, without timing, the width the autotuner would choose for the current steps per
  * pass (256 for the two-step main launch, 64 for the one-step update after
- * lbm_batch_init); LBM_ERR_INVALID for any other value than 64, 128, 256.  Synchronizes. */
+ * lbm_batch_init); later calls of lbm_batch_step run those passes.  LBM_ERR_INVALID for any
+ * other value than 64, 128, 256.  Synchronizes. */
 lbm_status lbm_batch_set_width(lbm_batch *batch, int32_t width);
 
 /* Releases the batch and its contexts (host memory only). */

@@ -217,7 +217,8 @@ struct lbm_ctx {
     int in_batch;
     int cur;             // buffer holding the current populations (0: a, 1: b)
     int fuse;            // time steps per pass over the populations (1 or 2)
-    lbm::TilePlan tile;  // several steps per launch (ns > 0: lbm_step takes it until lbm_set_fusion is called)
+    int tile_steps;      // steps per launch on tiles (0: passes); lbm_step's way until lbm_set_fusion is called
+    lbm::TileGrid tile;
     int64_t check_every; // lbm_step checks for non-finite populations at multiples of this time (0: never)
     lbm::KParams kpm;    // parameters of the eight-row scratch grid of the two-step pass
     int n_main2, n_full2;       // wavefronts of the two-step pass's main and full launches
@@ -233,6 +234,19 @@ struct lbm_ctx {
 
 static void *cur_buf(lbm_ctx *c) { return c->ws + (c->cur ? c->lay.off_b : c->lay.off_a); }
 static void *next_buf(lbm_ctx *c) { return c->ws + (c->cur ? c->lay.off_a : c->lay.off_b); }
+
+// nsteps in as few launches of at most `most` steps as it takes, of equal numbers of steps to
+// within one.  f(n) enqueues n steps.
+template <typename F> hipError_t by_launches(int64_t nsteps, int most, F &&f)
+{
+    hipError_t e = hipSuccess;
+    for (int64_t left = nsteps, l = (nsteps + most - 1) / most; l > 0 && e == hipSuccess; --l) {
+        const int n = (int)((left + l - 1) / l);
+        e = f(n);
+        left -= n;
+    }
+    return e;
+}
 
 extern "C" {
 
@@ -305,7 +319,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
     // two-step passes by default where they are faster: FP32 and FP64 storage, whose tiles
     // match the two-step wavefronts (see lbm_step2.hip)
     c->fuse = (params->storage != LBM_F16 && lbm::step2_supported(kp)) ? 2 : 1;
-    c->tile = lbm::tile_plan(params->storage, kp);
+    c->tile_steps = lbm::tile_plan(params->storage, &kp, 1, &c->tile);
     c->n_main2 = c->n_full2 = 0;
     c->main_nodes2 = 0;
     if (lbm::step2_supported(kp)) {
@@ -421,18 +435,16 @@ hipError_t run_steps(lbm_ctx *c, int64_t nsteps, const StepEvents *tev, int ever
     hipError_t e = hipSuccess;
     const int sto = c->prm.storage;
     int64_t s = 0, gi = 0;
-    if (c->tile.ns > 0 && !tev) {
-        // as few launches as the plan allows, of equal numbers of steps to within one
-        int64_t launches = (nsteps + c->tile.ns - 1) / c->tile.ns;
-        for (; launches > 0 && e == hipSuccess; --launches) {
-            const int n = (int)((nsteps - s + launches - 1) / launches);
-            e = lbm::launch_tile(sto, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
-            if (e == hipSuccess) {
+    if (c->tile_steps > 0 && !tev) {
+        e = by_launches(nsteps, c->tile_steps, [&](int n) {
+            const hipError_t r = lbm::launch_tile(sto, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
+            if (r == hipSuccess) {
                 c->t += n;
-                s += n;
                 c->cur ^= 1;
             }
-        }
+            return r;
+        });
+        s = nsteps;
     }
     if (c->fuse == 2 && nsteps - s >= 2 && e == hipSuccess) {
         const int64_t npass = nsteps / 2;
@@ -574,7 +586,7 @@ lbm_status lbm_set_fusion(lbm_ctx *c, int32_t steps_per_pass)
     if (steps_per_pass == 2 && !lbm::step2_supported(c->kp))
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need nx >= 4 and ny >= 8");
     c->fuse = steps_per_pass;
-    c->tile.ns = 0;
+    c->tile_steps = 0;
     return LBM_OK;
 }
 
@@ -905,6 +917,10 @@ struct lbm_batch {
     int2 *items2[lbm::STEP2_LAUNCHES];   // item tables of the batched two-step pass per launch
     int2 *rows2;
     int nitems2[lbm::STEP2_LAUNCHES], nrows2;
+    int2 *tile_items;           // (problem, tile) of the launches of several steps
+    int ntiles;
+    int tile_steps;             // their steps per launch (0: passes), until lbm_batch_set_fusion is called
+    bool any_field;             // some problem has a porosity field
     hipGraph_t graph;           // one-step mode: GRAPH_STEPS steps replayed as one graph
     hipGraphExec_t exec;
     int graph_steps;
@@ -927,9 +943,11 @@ constexpr double XWALL_COST = 1.34;
 
 struct BatchLayout {
     std::vector<size_t> off;    // workspace offset of each problem
-    size_t off_probs, off_bulk, off_edge, off_wall, off_all, off_flags, off_items2[lbm::STEP2_LAUNCHES], off_rows2, total;
-    std::vector<int2> bulk, edge, wall, all, items2[lbm::STEP2_LAUNCHES], rows2;
+    size_t off_probs, off_bulk, off_edge, off_wall, off_all, off_flags, off_items2[lbm::STEP2_LAUNCHES], off_rows2, off_tiles, total;
+    std::vector<int2> bulk, edge, wall, all, items2[lbm::STEP2_LAUNCHES], rows2, tiles;
     bool two;
+    int tile_steps;
+    std::vector<lbm::TileGrid> tile;
     std::vector<lbm::KParams> kp;
     std::vector<int> tiles_x;
 };
@@ -1026,6 +1044,12 @@ lbm_status batch_layout(const lbm_params *params, int32_t n, BatchLayout &B)
         o += align_up(B.items2[l].size() * sizeof(int2), 256);
     }
     B.off_rows2 = o; o += align_up(B.rows2.size() * sizeof(int2), 256);
+    B.tile.resize(n);
+    B.tile_steps = lbm::tile_plan(params[0].storage, B.kp.data(), n, B.tile.data());
+    B.tiles.clear();
+    for (int k = 0; k < n && B.tile_steps; ++k)
+        for (int b = 0; b < B.tile[k].nbx * B.tile[k].nby; ++b) B.tiles.push_back(make_int2(k, b));
+    B.off_tiles = o; o += align_up(B.tiles.size() * sizeof(int2), 256);
     B.total = o;
     if (B.all.size() > 0x7fffffff || B.items2[lbm::STEP2_MAIN].size() > 0x7fffffff)
         return fail(LBM_ERR_INVALID, "batch too large");
@@ -1168,6 +1192,10 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
     b->ev_join = b->ev_main = b->ev_side = nullptr;
     b->bx = lbm::batch_width(0);
     b->w2 = lbm::STEP2_WAVES_PER_BLOCK;
+    b->any_field = false;
+    b->tile_steps = B.tile_steps;
+    b->tile_items = reinterpret_cast<int2 *>(ws + B.off_tiles);
+    b->ntiles = (int)B.tiles.size();
     b->edge_cap = B.edge.size();
     std::vector<lbm::BatchProblem> &hp = b->hp;
     hp.resize(n);
@@ -1187,6 +1215,8 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
         hp[k].Pm = c->kpm;
         hp[k].scr = c->ws + c->lay.off_scr;
         hp[k].tiles_x = B.tiles_x[k];
+        hp[k].tile = B.tile[k];
+        b->any_field = b->any_field || c->kp.field;
     }
     b->probs = reinterpret_cast<lbm::BatchProblem *>(ws + B.off_probs);
     b->bulk_items = reinterpret_cast<int2 *>(ws + B.off_bulk);
@@ -1219,6 +1249,8 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
                                hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess && b->nrows2)
         e = hipMemcpyAsync(b->rows2, B.rows2.data(), B.rows2.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess && b->ntiles)
+        e = hipMemcpyAsync(b->tile_items, B.tiles.data(), B.tiles.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream);
     // the layout's host vectors are released on return: wait for the copies
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
@@ -1239,6 +1271,20 @@ hipError_t batch_single(lbm_batch *b)
                                           b->nedge, b->wall_items, b->nwall, b->cur, b->stream);
     if (e == hipSuccess) {
         ++b->t;
+        b->cur ^= 1;
+    }
+    return e;
+}
+
+// ns steps of every problem in one launch over their tiles.
+hipError_t batch_tiles(lbm_batch *b, int ns)
+{
+    int threads = 0;
+    for (const auto &h : b->hp) threads = std::max(threads, lbm::tile_threads(h.tile, ns));
+    const hipError_t e = lbm::launch_batch_tile(b->storage, b->probs, b->tile_items, b->ntiles, b->any_field, threads,
+                                                b->cur, ns, b->stream);
+    if (e == hipSuccess) {
+        b->t += ns;
         b->cur ^= 1;
     }
     return e;
@@ -1293,7 +1339,11 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
     if (nsteps < 0) return fail(LBM_ERR_INVALID, "nsteps < 0");
     int64_t left = nsteps;
     hipError_t e = hipSuccess;
-    if (b->fuse == 2) {
+    if (b->tile_steps > 0) {
+        e = by_launches(nsteps, b->tile_steps, [&](int n) { return batch_tiles(b, n); });
+        if (e != hipSuccess) return hip_fail(e, "batch tiles");
+        left = 0;
+    } else if (b->fuse == 2) {
         e = batch_passes(b, left / 2, true, b->w2);
         if (e != hipSuccess) return hip_fail(e, "batch passes");
         left %= 2;
@@ -1332,6 +1382,7 @@ lbm_status lbm_batch_set_fusion(lbm_batch *b, int32_t steps_per_pass)
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need FP32/FP64 storage and every grid at least 4 x 8 nodes");
     if (b->fuse != steps_per_pass) batch_drop_graph(b);
     b->fuse = steps_per_pass;
+    b->tile_steps = 0;
     return LBM_OK;
 }
 
@@ -1414,8 +1465,10 @@ lbm_status lbm_batch_set_width(lbm_batch *b, int32_t width)
 {
     if (!b) return fail(LBM_ERR_INVALID, "batch is NULL");
     for (int i = 0; i < LBM_BATCH_NUM_WIDTHS; ++i)
-        if (lbm::batch_width(i) == width)
+        if (lbm::batch_width(i) == width) {
+            b->tile_steps = 0;
             return b->fuse == 2 ? batch_set_waves2(b, width / 64) : batch_set_width(b, width);
+        }
     return fail(LBM_ERR_INVALID, "width %d is not one of 64, 128, 256", width);
 }
 

@@ -8,6 +8,13 @@
 
 namespace lbm {
 
+// Tiles of a grid for the launches of several steps (lbm_tile.hip).
+struct TileGrid {
+    int nbx, nby;         // tiles per row and per column
+    int tw, th, rx, ry;   // tile size; the first rx (ry) tiles are one node wider (higher)
+    unsigned magic;       // floor(2^32 / nbx) + 1, to divide by nbx
+};
+
 // One problem of a batch: its kernel parameters and its two population buffers.
 struct BatchProblem {
     KParams P;
@@ -15,6 +22,7 @@ struct BatchProblem {
     void *buf[2];
     void *scr;
     int tiles_x;
+    TileGrid tile;
 };
 
 // Instances of the two-step pass: lean (no wall in reach), full, xwall (walls x = 0 and
@@ -109,21 +117,18 @@ hipError_t launch_batch_step2(int storage, const BatchProblem *probs, const int2
                               const int2 *rows, int nrows, int parity, int main_waves, hipStream_t st_main,
                               hipStream_t st_side);
 
-// Several steps per launch, one LDS-resident tile per block (lbm_tile.hip).
-struct TileGrid {
-    int nbx, nby;         // tiles per row and per column
-    int tw, th, rx, ry;   // tile size; the first rx (ry) tiles are one node wider (higher)
-    unsigned magic;       // floor(2^32 / nbx) + 1, to divide by nbx
-};
-struct TilePlan {
-    int ns;               // steps per launch at most (0: this grid does not take the path)
-    TileGrid g;
-};
-TilePlan tile_plan(int storage, const KParams &P);
-// 1 <= ns <= t.ns steps from src into dst; hist != 0 stores every step, step s at element
-// offset (s - 1) hist of dst.
-hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TilePlan &t, int ns,
+// Several steps per launch, one LDS-resident tile per block (lbm_tile.hip).  tile_plan picks
+// the tiles of the n grids of a launch and returns the steps a launch may take (0: these
+// grids do not take the path).
+int tile_plan(int storage, const KParams *P, int n, TileGrid *grids);
+int tile_threads(const TileGrid &g, int ns);   // threads of a block of a launch of ns steps
+// ns steps from src into dst; hist != 0 stores every step, step s at element offset
+// (s - 1) hist of dst.
+hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TileGrid &g, int ns,
                        long long hist, hipStream_t st);
+// Batched: items (problem, tile); threads: the largest of the problems' tile_threads.
+hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
+                             int threads, int parity, int ns, hipStream_t st);
 
 // Adjoint sweep.
 hipError_t launch_adjoint_step(int storage, const void *state, const KParams &P, const AdjBufs &A,

@@ -24,6 +24,8 @@
 // Measured (one step, 100-step calls, two-step passes before): 128 x 128 FP64 27 -> 2.6 us,
 // 250 x 250 FP32 22 -> 3.0 us, 512 x 512 FP32 25 -> 7.5 us, 1300 x 1300 FP32 43 -> 34 us; a
 // grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
+#include <cmath>
+
 #include "lbm_kernels.h"
 
 namespace lbm {
@@ -139,10 +141,10 @@ __device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restr
     WallC<R> wc = {};
     R f[9], g[9], Tdff = R(0);
     if (last > 0) {
-        if (FIELD) er = eo = eps_coeffs<R>(P, P.eps_field[(long long)yr * P.nx + xr]);
+        if (FIELD) er = eo = eps_at<R>(P, xr, yr);
         if (wall) {
             wc = wall_consts<R>(P, w);
-            if (FIELD) eo = eps_coeffs<R>(P, P.eps_field[(long long)y * P.nx + x]);
+            if (FIELD) eo = eps_at<R>(P, x, y);
         }
     }
     const bool neumann = wall && !wc.iso;
@@ -219,6 +221,19 @@ k_tile(const S *__restrict__ src, S *__restrict__ dst, KParams P, TileGrid g, in
     tile_block<S, FIELD>(src, dst, P, Pc, g, xcd_block(blockIdx.x, gridDim.x), ns, hist, lds);
 }
 
+// Batched: item (problem, tile).  FIELD: some problem has a porosity field.  The item, and
+// with it the problem's parameters, are wavefront-uniform.
+template <typename S, bool FIELD>
+__global__ void __launch_bounds__(TILE_NT)
+k_batch_tile(const BatchProblem *__restrict__ probs, const int2 *__restrict__ items, int parity, int ns)
+{
+    __shared__ S lds[18 * TILE_NT];
+    const int2 it = items[xcd_block(blockIdx.x, gridDim.x)];
+    const BatchProblem &B = probs[__builtin_amdgcn_readfirstlane(it.x)];
+    tile_block<S, FIELD>(static_cast<const S *>(B.buf[parity]), static_cast<S *>(B.buf[parity ^ 1]), B.P,
+                         (KConst)&B.P, B.tile, __builtin_amdgcn_readfirstlane(it.y), ns, 0, lds);
+}
+
 // Tiles of at most tw x th nodes (of equal size to within one node).
 static TileGrid tile_grid(const KParams &P, int tw, int th)
 {
@@ -238,94 +253,145 @@ static void tile_extent(const TileGrid &g, int ns, int &w, int &h)
     h = g.th + (g.ry ? 1 : 0) + (g.nby > 1 ? 2 * (ns - 1) : 0);
 }
 
-static int tile_threads(const TileGrid &g, int ns)
-{
-    int w, h;
-    tile_extent(g, ns, w, h);
-    return (w * h + 63) / 64 * 64;
-}
-
 template <typename S>
-static hipError_t tile_t(const void *src, void *dst, const KParams &P, const TilePlan &t, int ns, long long hist,
+static hipError_t tile_t(const void *src, void *dst, const KParams &P, const TileGrid &g, int ns, long long hist,
                          hipStream_t st)
 {
-    const dim3 grid(t.g.nbx * t.g.nby), block(tile_threads(t.g, ns));
+    const dim3 grid(g.nbx * g.nby), block(tile_threads(g, ns));
     if (P.field)
-        hipLaunchKernelGGL((k_tile<S, true>), grid, block, 0, st, (const S *)src, (S *)dst, P, t.g, ns, hist);
+        hipLaunchKernelGGL((k_tile<S, true>), grid, block, 0, st, (const S *)src, (S *)dst, P, g, ns, hist);
     else
-        hipLaunchKernelGGL((k_tile<S, false>), grid, block, 0, st, (const S *)src, (S *)dst, P, t.g, ns, hist);
+        hipLaunchKernelGGL((k_tile<S, false>), grid, block, 0, st, (const S *)src, (S *)dst, P, g, ns, hist);
     return hipGetLastError();
 }
 
-hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TilePlan &t, int ns,
+hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TileGrid &g, int ns,
                        long long hist, hipStream_t st)
 {
-    if (ns < 1 || ns > t.ns) return hipErrorInvalidValue;
+    if (ns < 1 || tile_threads(g, ns) > TILE_NT) return hipErrorInvalidValue;
     switch (storage) {
-    case 0: return tile_t<double>(src, dst, P, t, ns, hist, st);
-    case 1: return tile_t<float>(src, dst, P, t, ns, hist, st);
-    case 2: return tile_t<__half>(src, dst, P, t, ns, hist, st);
+    case 0: return tile_t<double>(src, dst, P, g, ns, hist, st);
+    case 1: return tile_t<float>(src, dst, P, g, ns, hist, st);
+    case 2: return tile_t<__half>(src, dst, P, g, ns, hist, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-// Tiles and steps per launch for one grid.
+template <typename S>
+static hipError_t batch_tile_t(const BatchProblem *probs, const int2 *items, int nitems, bool field, int threads,
+                               int parity, int ns, hipStream_t st)
+{
+    if (field)
+        hipLaunchKernelGGL((k_batch_tile<S, true>), dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
+    else
+        hipLaunchKernelGGL((k_batch_tile<S, false>), dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
+                             int threads, int parity, int ns, hipStream_t st)
+{
+    switch (storage) {
+    case 0: return batch_tile_t<double>(probs, items, nitems, field, threads, parity, ns, st);
+    case 1: return batch_tile_t<float>(probs, items, nitems, field, threads, parity, ns, st);
+    case 2: return batch_tile_t<__half>(probs, items, nitems, field, threads, parity, ns, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// Tiles and steps per launch for the grids of one launch (n = 1: one problem; else a batch,
+// whose problems share the steps per launch and the largest tile).
 //
-// A grid of at most TILE_NT nodes is one block, which needs no overlap and takes any number
-// of steps per launch.  Otherwise the tiles and steps of least estimated time per step are
-// taken.  Per launch the estimate adds, in units of a round's fixed cost (launch, first
-// loads, last stores: 4-6 us): one for each round of blocks on the 256 CUs; 0.05 for every step of a
-// round (its chain of dependent instructions and two barriers); 0.12 for every node update
-// that a SIMD issues for a wavefront.  Over 875 measured combinations on nine grids from
-// 48 x 90 to 1300 x 1201 nodes the choice costs 3 % (FP64, FP16) and 5 % (FP32) more on average
-// than the best one.
+// Grids of at most TILE_NT nodes are one block each, which needs no overlap and takes any
+// number of steps per launch.  Otherwise the tiles and steps of least estimated time per
+// step are taken.  Per launch the estimate adds, in units of a round's fixed cost (launch,
+// first loads, last stores: 4-6 us): one for each round of blocks on the 256 CUs; 0.05 for
+// every step of a round (its chain of dependent instructions and two barriers); 0.12 for
+// every node update that a SIMD issues for a wavefront.  Over 875 measured combinations on
+// nine grids from 48 x 90 to 1300 x 1201 nodes the choice costs 3 % (FP64, FP16) and 5 % (FP32)
+// more on average than the best one.
 //
-// Grids above TILE_NODES nodes take the two-step pass (FP16: single steps), which is bound by
+// More than TILE_NODES nodes take the two-step pass (FP16: single steps), which is bound by
 // HBM and recomputes less: FP32 1536^2 46 us per step here against 53, 2048^2 102 against 79;
 // FP64 1024^2 45 against 53, 1300 x 1201 65 against 63; FP16 1300 x 1201 30 against 35, 2048^2 73
 // against 68.  With a porosity field, whose coefficients a tile forms once per launch, FP64
-// gains up to 1537 x 1025 (66 against 74).
+// gains up to 1537 x 1025 (66 against 74).  A batch's grids are narrower, which costs the
+// other ways more: cavities of 64-300 nodes a side, us per step here and there: FP64 1.19 M nodes
+// 59 and 63, 2.13 M 125 and 129, 2.38 M 118 and 108; FP32 2.38 M 59 and 89, 4.0 M 102 and 103-120,
+// 5.1 M 193 and 135; FP16 1.19 M 29 and 47, 5.1 M 117 and 145, sides of 64-512 with 25.6 M nodes 513
+// and 562.
 constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
 constexpr long long TILE_NODES[3] = {1400000, 2500000, 2000000}, TILE_NODES_FIELD = 2000000;
+constexpr long long TILE_NODES_BATCH[2] = {2000000, 4000000};   // FP16: the mean grid at most TILE_NODES
 
-TilePlan tile_plan(int storage, const KParams &P)
+static long long tile_nodes_limit(int storage, int n, bool field)
 {
-    TilePlan best = {};
-    const long long n = (long long)P.nx * P.ny;
-    if (n <= TILE_NT) {
-        best.ns = TILE_ALL_STEPS;
-        best.g = tile_grid(P, P.nx, P.ny);
-        return best;
+    if (n > 1) return storage == 2 ? n * TILE_NODES[2] : TILE_NODES_BATCH[storage];
+    return storage == 0 && field ? TILE_NODES_FIELD : TILE_NODES[storage];
+}
+
+int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
+{
+    long long nodes = 0;
+    bool field = true, one_block = true;
+    for (int k = 0; k < n; ++k) {
+        const long long nk = (long long)P[k].nx * P[k].ny;
+        nodes += nk;
+        field = field && P[k].field;
+        one_block = one_block && nk <= TILE_NT;
     }
-    if (n > (storage == 0 && P.field ? TILE_NODES_FIELD : TILE_NODES[storage])) return best;
+    if (nodes > tile_nodes_limit(storage, n, field)) return 0;
+    if (one_block) {
+        for (int k = 0; k < n; ++k) grids[k] = tile_grid(P[k], P[k].nx, P[k].ny);
+        return TILE_ALL_STEPS;
+    }
     static const int shapes[][2] = {{8, 8}, {12, 8}, {16, 8}, {32, 8}, {12, 12}, {16, 12}, {16, 16},
                                     {20, 20}, {28, 12}, {26, 10}, {30, 14}};
     const int resident = storage == 0 ? 8 : 16;   // wavefronts of this kernel that a CU's registers hold
+    const double cus = 256.0;
+    const int *shape = nullptr;
+    int best = 0;
     double cost = 0.0;
     for (const auto &sh : shapes) {
-        const TileGrid g = tile_grid(P, sh[0], sh[1]);
-        if ((g.nbx > 1 && g.tw < 4) || (g.nby > 1 && g.th < 4)) continue;
-        const long long nb = (long long)g.nbx * g.nby;
-        if (nb > 0x7fffffff / g.nbx) continue;
         for (int ns = 1; ns <= TILE_MAX_STEPS; ++ns) {
-            int w, h;
-            tile_extent(g, ns, w, h);
-            if (w * h > TILE_NT) break;
-            const int waves = (w * h + 63) / 64;
-            const long long cus = 256, percu = std::max(1, resident / waves);
-            const double rounds = (double)((nb + cus * percu - 1) / (cus * percu));
-            int updates = 0;      // wavefronts of a block that update nodes, over the steps
-            for (int s = 0; s < ns; ++s) updates += (w * (g.nby > 1 ? h - 2 * s : h) + 63) / 64;
-            const double simd = (double)((nb + cus - 1) / cus) * updates / 4.0;
+            double blocks = 0.0, updates = 0.0;   // over all grids: blocks; node updates of a wavefront
+            int waves = 0;                        // of the largest block
+            for (int k = 0; k < n && waves >= 0; ++k) {
+                const TileGrid g = tile_grid(P[k], sh[0], sh[1]);
+                int w, h;
+                tile_extent(g, ns, w, h);
+                if ((g.nbx > 1 && g.tw < 4) || (g.nby > 1 && g.th < 4) || w * h > TILE_NT) {
+                    waves = -1;
+                    break;
+                }
+                const double nb = (double)g.nbx * g.nby;
+                int u = 0;
+                for (int s = 0; s < ns; ++s) u += (w * (g.nby > 1 ? h - 2 * s : h) + 63) / 64;
+                blocks += nb;
+                updates += nb * u;
+                waves = std::max(waves, (w * h + 63) / 64);
+            }
+            if (waves < 0) break;
+            const double percu = std::max(1, resident / waves);
+            const double rounds = std::ceil(blocks / (cus * percu));
+            const double simd = std::ceil(blocks / cus) * (updates / blocks) / 4.0;
             const double c = (rounds + 0.05 * rounds * ns + 0.12 * simd) / ns;
-            if (best.ns == 0 || c < cost) {
+            if (best == 0 || c < cost) {
                 cost = c;
-                best.ns = ns;
-                best.g = g;
+                best = ns;
+                shape = sh;
             }
         }
     }
+    for (int k = 0; k < n && best; ++k) grids[k] = tile_grid(P[k], shape[0], shape[1]);
     return best;
+}
+
+int tile_threads(const TileGrid &g, int ns)
+{
+    int w, h;
+    tile_extent(g, ns, w, h);
+    return (w * h + 63) / 64 * 64;
 }
 
 }  // namespace lbm

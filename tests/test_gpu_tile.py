@@ -72,3 +72,25 @@ def test_three_isothermal_nodes_across(gpu):
     a.step(29)
     b.step(29)
     assert bool((a.get_state() == b.get_state()).all())
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+def test_batched_tiles_are_bitwise_single_steps(gpu, storage):
+    """A batch of uneven grids (with and without a porosity field, walled and periodic, one
+    narrower than a tile), and one whose grids are all a single block."""
+    mixed = [W.random_case(541, 61, 47, storage=storage, eps_field=True, moving_walls=True),
+             W.random_case(542, 6, 200, periodic_x=1, storage=storage),
+             W.random_case(543, 130, 33, periodic_x=1, periodic_y=1, storage=storage, with_Q=True),
+             W.random_case(544, 20, 19, storage=storage, moving_walls=True)]
+    blocks = [W.random_case(545, 16, 32, storage=storage), W.random_case(546, 9, 8, periodic_y=1, storage=storage)]
+    for cfgs in (mixed, blocks):
+        print(f"case: {storage} batch of {len(cfgs)}", flush=True)
+        batch = gpu.Batch(cfgs)
+        singles = [gpu.Sim(c) for c in cfgs]
+        for s in singles:
+            s.fusion = 1
+        for n in (1, 5, 23):
+            batch.step(n)
+            for k, s in enumerate(singles):
+                s.step(n)
+                assert bool((batch[k].get_state() == s.get_state()).all()), (k, n)
