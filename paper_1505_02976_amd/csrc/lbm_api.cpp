@@ -425,6 +425,56 @@ hipError_t run_passes(lbm_ctx *c, int64_t npass, const StepEvents *tev, int ever
     return e;
 }
 
+// nsteps steps as launches of several steps on tiles.
+hipError_t tile_steps(lbm_ctx *c, int64_t nsteps)
+{
+    return by_launches(nsteps, c->tile_steps, [&](int n) {
+        const hipError_t e = lbm::launch_tile(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
+        if (e == hipSuccess) {
+            c->t += n;
+            c->cur ^= 1;
+        }
+        return e;
+    });
+}
+
+// n steps of the adjoint's forward sweep: as run_steps with one step per pass (tiles where the
+// grid takes them).
+hipError_t single_steps(lbm_ctx *c, int64_t n)
+{
+    if (c->tile_steps > 0) return tile_steps(c, n);
+    hipError_t e = hipSuccess;
+    for (; n > 0 && e == hipSuccess; --n) {
+        e = lbm::launch_step(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->stream);
+        if (e == hipSuccess) {
+            c->t += 1;
+            c->cur ^= 1;
+        }
+    }
+    return e;
+}
+
+// The n states after src, one step apart, into dst, dst + stride, ... (bytes).
+hipError_t states_after(const lbm_ctx *c, const char *src, char *dst, size_t stride, int64_t n)
+{
+    const int sto = c->prm.storage;
+    if (c->tile_steps > 0)
+        return by_launches(n, c->tile_steps, [&](int k) {
+            const hipError_t r = lbm::launch_tile(sto, src, dst, c->kp, c->tile, k,
+                                                  (long long)(stride / elem_size(sto)), c->stream);
+            src = dst + (size_t)(k - 1) * stride;
+            dst += (size_t)k * stride;
+            return r;
+        });
+    hipError_t e = hipSuccess;
+    for (; n > 0 && e == hipSuccess; --n) {
+        e = lbm::launch_step(sto, src, dst, c->kp, c->stream);
+        src = dst;
+        dst += stride;
+    }
+    return e;
+}
+
 // nsteps steps on the context's stream.  One step: the interior launch, then the launch of
 // the columns next to the walls x = 0, x = nx - 1 and of the walled rows.  With fuse = 2,
 // pairs of steps run as two-step passes (run_passes), a last odd step as one step.  With
@@ -436,14 +486,7 @@ hipError_t run_steps(lbm_ctx *c, int64_t nsteps, const StepEvents *tev, int ever
     const int sto = c->prm.storage;
     int64_t s = 0, gi = 0;
     if (c->tile_steps > 0 && !tev) {
-        e = by_launches(nsteps, c->tile_steps, [&](int n) {
-            const hipError_t r = lbm::launch_tile(sto, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
-            if (r == hipSuccess) {
-                c->t += n;
-                c->cur ^= 1;
-            }
-            return r;
-        });
+        e = tile_steps(c, nsteps);
         s = nsteps;
     }
     if (c->fuse == 2 && nsteps - s >= 2 && e == hipSuccess) {
@@ -832,12 +875,10 @@ lbm_status lbm_adjoint_forward(lbm_ctx *c, int32_t wall, int64_t nsteps, void *w
     if (workspace_bytes < L.total) return fail(LBM_ERR_INVALID, "workspace too small: %zu < %zu bytes", workspace_bytes, L.total);
     char *ws = static_cast<char *>(workspace);
     hipError_t e = hipSuccess;
-    for (int64_t s = 0; s < nsteps && e == hipSuccess; ++s) {
-        if (s % L.K == 0)
-            e = hipMemcpyAsync(ws + L.off_ck + (size_t)(s / L.K) * c->lay.pop_bytes, cur_buf(c),
-                               c->lay.pop_bytes, hipMemcpyDeviceToDevice, c->stream);
-        if (e == hipSuccess) e = lbm::launch_step(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->stream);
-        if (e == hipSuccess) { c->t += 1; c->cur ^= 1; }
+    for (int64_t s = 0; s < nsteps && e == hipSuccess; s += L.K) {
+        e = hipMemcpyAsync(ws + L.off_ck + (size_t)(s / L.K) * c->lay.pop_bytes, cur_buf(c), c->lay.pop_bytes,
+                           hipMemcpyDeviceToDevice, c->stream);
+        if (e == hipSuccess) e = single_steps(c, std::min<int64_t>(L.K, nsteps - s));
     }
     if (e != hipSuccess) return hip_fail(e, "adjoint forward");
     double J;
@@ -881,13 +922,12 @@ lbm_status lbm_adjoint_backward(lbm_adjoint *a, double dJ, double *grad)
     for (int64_t sg = a->nck - 1; sg >= 0 && e == hipSuccess; --sg) {
         const int64_t t0 = sg * a->K;
         const int64_t t1 = std::min<int64_t>(a->nsteps, t0 + a->K);
-        e = hipMemcpyAsync(seg(0), ws + a->off_ck + (size_t)sg * a->pop, a->pop, hipMemcpyDeviceToDevice, c->stream);
-        for (int64_t i = 1; i < t1 - t0 && e == hipSuccess; ++i)
-            e = lbm::launch_step(c->prm.storage, seg(i - 1), seg(i), c->kp, c->stream);
+        const char *ck = ws + a->off_ck + (size_t)sg * a->pop;   // state t0 + i is at ck (i = 0) or seg(i)
+        e = states_after(c, ck, seg(1), a->pop, t1 - t0 - 1);
         for (int64_t i = t1 - t0 - 1; i >= 0 && e == hipSuccess; --i) {
             A.lam_next = lam[cur];
             A.lam = lam[cur ^ 1];
-            e = lbm::launch_adjoint_step(c->prm.storage, seg(i), c->kp, A, c->stream);
+            e = lbm::launch_adjoint_step(c->prm.storage, i == 0 ? ck : seg(i), c->kp, A, c->stream);
             cur ^= 1;
         }
     }
