@@ -776,7 +776,7 @@ struct lbm_adjoint {
     int64_t nsteps, K, nck;
     char *ws;
     size_t pop;
-    size_t off_ck, off_seg, off_lam0, off_lam1, off_wf, off_wt, off_we, off_wtj;
+    size_t off_ck, off_seg, off_mu0, off_mu1, off_wtj;
     double J;
 };
 
@@ -784,7 +784,7 @@ namespace {
 
 struct AdjLayout {
     int64_t K, nck;
-    size_t off_ck, off_seg, off_lam0, off_lam1, off_wf, off_wt, off_we, off_wtj, total;
+    size_t off_ck, off_seg, off_mu0, off_mu1, off_wtj, total;
 };
 
 AdjLayout adj_layout(const lbm_ctx *c, int64_t nsteps)
@@ -799,11 +799,8 @@ AdjLayout adj_layout(const lbm_ctx *c, int64_t nsteps)
     size_t o = 0;
     L.off_ck = o; o += (size_t)L.nck * pop;
     L.off_seg = o; o += (size_t)K * pop;
-    L.off_lam0 = o; o += align_up(18 * N * 8, 256);
-    L.off_lam1 = o; o += align_up(18 * N * 8, 256);
-    L.off_wf = o; o += align_up(18 * N * 8, 256);
-    L.off_wt = o; o += align_up(N * 8, 256);
-    L.off_we = o; o += align_up(N * 8, 256);
+    L.off_mu0 = o; o += align_up(18 * N * 8, 256);
+    L.off_mu1 = o; o += align_up(18 * N * 8, 256);
     L.off_wtj = o; o += align_up(N * 8, 256);
     L.total = o;
     return L;
@@ -888,8 +885,7 @@ lbm_status lbm_adjoint_forward(lbm_ctx *c, int32_t wall, int64_t nsteps, void *w
     if (!a) return fail(LBM_ERR_DEVICE, "out of host memory");
     a->ctx = c; a->wall = wall; a->nsteps = nsteps; a->K = L.K; a->nck = L.nck; a->ws = ws;
     a->pop = c->lay.pop_bytes;
-    a->off_ck = L.off_ck; a->off_seg = L.off_seg; a->off_lam0 = L.off_lam0; a->off_lam1 = L.off_lam1;
-    a->off_wf = L.off_wf; a->off_wt = L.off_wt; a->off_we = L.off_we;
+    a->off_ck = L.off_ck; a->off_seg = L.off_seg; a->off_mu0 = L.off_mu0; a->off_mu1 = L.off_mu1;
     a->off_wtj = L.off_wtj;
     a->J = J;
     *nu_host = J;
@@ -905,31 +901,36 @@ lbm_status lbm_adjoint_backward(lbm_adjoint *a, double dJ, double *grad)
     std::vector<double> wtj;
     nusselt_weights(c, a->wall, dJ, wtj);
     char *ws = a->ws;
-    double *lam[2] = {reinterpret_cast<double *>(ws + a->off_lam0), reinterpret_cast<double *>(ws + a->off_lam1)};
+    double *mu[2] = {reinterpret_cast<double *>(ws + a->off_mu0), reinterpret_cast<double *>(ws + a->off_mu1)};
     lbm::AdjBufs A;
-    A.wf = reinterpret_cast<double *>(ws + a->off_wf);
-    A.wt = reinterpret_cast<double *>(ws + a->off_wt);
-    A.we = reinterpret_cast<double *>(ws + a->off_we);
     A.grad = grad;
-    A.wtj = reinterpret_cast<double *>(ws + a->off_wtj);
-    hipError_t e = hipMemcpyAsync(const_cast<double *>(A.wtj), wtj.data(), N * 8, hipMemcpyHostToDevice, c->stream);
+    double *const wtj_dev = reinterpret_cast<double *>(ws + a->off_wtj);
+    lbm::TileGrid grid;
+    int threads = 0;
+    const int steps = lbm::adjoint_plan(c->kp, grid, threads);
+    if (steps < 1) return fail(LBM_ERR_UNSUPPORTED, "no tiles for this grid");
+    hipError_t e = hipMemcpyAsync(wtj_dev, wtj.data(), N * 8, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(grad, 0, N * 8, c->stream);
+    if (e == hipSuccess) e = lbm::launch_adjoint_seed(c->kp, wtj_dev, mu[0], c->stream);
     int cur = 0;
-    A.lam_next = nullptr;
-    A.lam = lam[cur];
-    if (e == hipSuccess) e = lbm::launch_adjoint_seed(c->kp, A, c->stream);
+    const long long stride = (long long)(a->pop / elem_size(c->prm.storage));
     auto seg = [&](int64_t i) { return ws + a->off_seg + (size_t)i * a->pop; };
     for (int64_t sg = a->nck - 1; sg >= 0 && e == hipSuccess; --sg) {
         const int64_t t0 = sg * a->K;
         const int64_t t1 = std::min<int64_t>(a->nsteps, t0 + a->K);
         const char *ck = ws + a->off_ck + (size_t)sg * a->pop;   // state t0 + i is at ck (i = 0) or seg(i)
         e = states_after(c, ck, seg(1), a->pop, t1 - t0 - 1);
-        for (int64_t i = t1 - t0 - 1; i >= 0 && e == hipSuccess; --i) {
-            A.lam_next = lam[cur];
-            A.lam = lam[cur ^ 1];
-            e = lbm::launch_adjoint_step(c->prm.storage, i == 0 ? ck : seg(i), c->kp, A, c->stream);
-            cur ^= 1;
-        }
+        int i = (int)(t1 - t0 - 1);
+        if (e == hipSuccess)
+            e = by_launches(t1 - t0, steps, [&](int n) {
+                A.mu_in = mu[cur];
+                A.mu_out = mu[cur ^ 1];
+                const hipError_t r = lbm::launch_adjoint_steps(c->prm.storage, ck, seg(0), stride, c->kp, A, grid,
+                                                               threads, i, n, c->stream);
+                i -= n;
+                cur ^= 1;
+                return r;
+            });
     }
     // the seed array on the host must outlive the copy
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

@@ -41,35 +41,6 @@ __device__ constexpr int CXd[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 __device__ constexpr int CYd[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 __host__ __device__ constexpr double Wd(int i) { return i == 0 ? 4.0 / 9.0 : (i < 5 ? 1.0 / 9.0 : 1.0 / 36.0); }
 
-// Forward-mode dual number (value, derivative) in FP64, used by the adjoint to evaluate
-// directional derivatives of the node update with the same templated code.
-struct Dual {
-    double v, d;
-    __host__ __device__ constexpr Dual() : v(0.0), d(0.0) {}
-    __host__ __device__ explicit constexpr Dual(double a) : v(a), d(0.0) {}
-    __host__ __device__ constexpr Dual(double a, double b) : v(a), d(b) {}
-};
-__device__ __forceinline__ Dual operator+(Dual a, Dual b) { return Dual(a.v + b.v, a.d + b.d); }
-__device__ __forceinline__ Dual operator-(Dual a, Dual b) { return Dual(a.v - b.v, a.d - b.d); }
-__device__ __forceinline__ Dual operator-(Dual a) { return Dual(-a.v, -a.d); }
-__device__ __forceinline__ Dual operator*(Dual a, Dual b) { return Dual(a.v * b.v, a.d * b.v + a.v * b.d); }
-__device__ __forceinline__ Dual operator/(Dual a, Dual b)
-{
-    const double q = a.v / b.v;
-    return Dual(q, (a.d - q * b.d) / b.v);
-}
-__device__ __forceinline__ Dual &operator+=(Dual &a, Dual b) { a = a + b; return a; }
-__device__ __forceinline__ Dual sqrt(Dual a)
-{
-    const double r = ::sqrt(a.v);
-    return Dual(r, r > 0.0 ? 0.5 * a.d / r : 0.0);
-}
-using ::sqrt;   // keep the FP32/FP64 overloads visible next to the dual one
-
-// Type of the FP64 quantities of the drag solve for arithmetic type R.
-template <typename R> struct DragT { using T = double; };
-template <> struct DragT<Dual> { using T = Dual; };
-
 // 1 / tau and 1 - 1 / tau in the arithmetic type R with it + o == 1 exactly: the collision
 // forms o f + it (...), whose zeroth moment then carries the state's own moment with the
 // factor o + it = 1 (a rounded pair would scale the temperature deviation by 1 + 6e-8 per
@@ -204,7 +175,6 @@ template <> __device__ __forceinline__ const EpsR<float> &epsu<float>(const KPar
 // Reciprocal: IEEE division in FP64 arithmetic, the hardware reciprocal (1 ulp) in FP32.
 __device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ Dual rcp(Dual x) { return Dual(1.0) / x; }
 
 // Element index of population q (0..17) of node (x, y) inside a population buffer of
 // storage type S.
@@ -274,9 +244,8 @@ template <typename R> __device__ __forceinline__ const Cst<R> &make_cst(const KP
 
 // Porosity-dependent coefficients (Sec. 3.1 for c0 and c1; Eq. ForceEq for the drag).
 template <typename R> struct EpsC {
-    using D = typename DragT<R>::T;
     R eps, ieps, dlin, dquad, bM;
-    D c0, c1, epsd;
+    double c0, c1, epsd;
 };
 
 template <typename R> __device__ __forceinline__ EpsC<R> eps_uniform(const KParams &P)
@@ -294,24 +263,21 @@ template <typename R> __device__ __forceinline__ EpsC<R> eps_uniform(const KPara
     return e;
 }
 
-// Coefficients at porosity eps (any of double, Dual): F_eps from the Ergun relation or
-// as given, c0 and c1 of the velocity solve, the drag coefficients of Eq. ForceEq and
-// b = (1/eps - 1/sigma)/2 of Eq. MatrM.
-template <typename R>
-__device__ __forceinline__ EpsC<R> eps_coeffs(const KParams &P, typename DragT<R>::T eps)
+// Coefficients at porosity eps: F_eps from the Ergun relation or as given, c0 and c1 of the
+// velocity solve, the drag coefficients of Eq. ForceEq and b = (1/eps - 1/sigma)/2 of Eq. MatrM.
+template <typename R> __device__ __forceinline__ EpsC<R> eps_coeffs(const KParams &P, double eps)
 {
-    using D = typename DragT<R>::T;
-    const D ie = D(1.0) / eps;
-    const D Fe = P.ergun ? D(1.75) / sqrt(D(150.0) * eps * eps * eps) : D(P.Feps);
+    const double ie = 1.0 / eps;
+    const double Fe = P.ergun ? 1.75 / sqrt(150.0 * eps * eps * eps) : P.Feps;
     EpsC<R> e;
     e.epsd = eps;
     e.eps = R(eps);
     e.ieps = R(ie);
-    e.c0 = D(0.5) * (D(1.0) + D(0.5) * eps * D(P.nu_over_K));
-    e.c1 = D(0.5) * eps * Fe * D(P.inv_sqrtK);
-    e.dlin = R(eps * D(P.nu_over_K));
-    e.dquad = R(eps * Fe * D(P.inv_sqrtK));
-    e.bM = R(D(0.5) * (ie - D(P.cd.isig)));   // isig = 1 / sigma, rounded once on the host
+    e.c0 = 0.5 * (1.0 + 0.5 * eps * P.nu_over_K);
+    e.c1 = 0.5 * eps * Fe * P.inv_sqrtK;
+    e.dlin = R(eps * P.nu_over_K);
+    e.dquad = R(eps * Fe * P.inv_sqrtK);
+    e.bM = R(0.5 * (ie - P.cd.isig));   // isig = 1 / sigma, rounded once on the host
     return e;
 }
 
@@ -332,18 +298,15 @@ template <typename R> struct Macro {
 };
 
 // FP64 part of the velocity computation (Sec. 3.1): u = v / (c0 + sqrt(c0^2 + c1 |v|)).
-// Returns 1 / (c0 + sqrt(c0^2 + c1 |v|)) and |v|.  |v| is not differentiable at v = 0; the
-// dual version takes the derivative of |v| there as 0, the limit in which u(v) is C^1
-// with du/dv = I / (2 c0).
-template <typename R, typename D>
-__device__ __forceinline__ D drag_factor(D vx, D vy, D c0, D c1, D &vm)
+// Returns 1 / (c0 + sqrt(c0^2 + c1 |v|)) and |v|.
+template <typename R>
+__device__ __forceinline__ double drag_factor(double vx, double vy, double c0, double c1, double &vm)
 {
     vm = sqrt(vx * vx + vy * vy);
-    return D(1.0) / (c0 + sqrt(c0 * c0 + c1 * vm));
+    return 1.0 / (c0 + sqrt(c0 * c0 + c1 * vm));
 }
 template <>
-__device__ __forceinline__ double drag_factor<float, double>(double vx, double vy, double c0, double c1,
-                                                             double &vm)
+__device__ __forceinline__ double drag_factor<float>(double vx, double vy, double c0, double c1, double &vm)
 {
     vm = sqrt_nr(vx * vx + vy * vy);
     return rcp_nr(c0 + sqrt_pos_nr(c0 * c0 + c1 * vm));   // c0 > 0, c1 >= 0
@@ -367,11 +330,10 @@ __device__ __forceinline__ void node_macro(const R *f, const R *g, const Cst<R> 
 
     const R jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
     const R jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
-    using D = typename DragT<R>::T;
-    const D vx = D(jx) + D(0.5) * e.epsd * D(Gx);
-    const D vy = D(jy) + D(0.5) * e.epsd * D(Gy);
-    D vm;
-    const D iden = drag_factor<R, D>(vx, vy, e.c0, e.c1, vm);
+    const double vx = double(jx) + 0.5 * e.epsd * double(Gx);
+    const double vy = double(jy) + 0.5 * e.epsd * double(Gy);
+    double vm;
+    const double iden = drag_factor<R>(vx, vy, e.c0, e.c1, vm);
     m.ux = R(vx * iden);
     m.uy = R(vy * iden);
     const R um = R(vm * iden);

@@ -30,15 +30,11 @@ struct BatchProblem {
 enum : int { STEP2_LEAN = 0, STEP2_FULL = 1, STEP2_XWALL = 2 };
 enum : int { STEP2_MAIN = 0, STEP2_LAUNCHES = 2 };
 
-// Device buffers of the adjoint sweep (FP64, [18][ny][nx] for the 18-component arrays).
+// Device buffers of the adjoint sweep (FP64).
 struct AdjBufs {
-    const double *lam_next;   // adjoint of s_{t+1}
-    double *lam;              // adjoint of s_t (output)
-    double *wf;               // wall nodes: adjoint of the reference node's populations
-    double *wt;               // wall nodes: adjoint of T at x_ff
-    double *we;               // wall nodes: adjoint of eps at the reference node
+    const double *mu_in;      // mu of the step before the launch's first (lbm_adjoint.hip), [18][ny][nx]
+    double *mu_out;           // mu of its last step
     double *grad;             // dJ/deps, accumulated
-    const double *wtj;        // dJ/dT at interior nodes (seed)
 };
 
 struct BatchKernels {
@@ -130,10 +126,14 @@ hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P
 hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
                              int threads, int parity, int ns, hipStream_t st);
 
-// Adjoint sweep.
-hipError_t launch_adjoint_step(int storage, const void *state, const KParams &P, const AdjBufs &A,
-                               hipStream_t st);
-hipError_t launch_adjoint_seed(const KParams &P, const AdjBufs &A, hipStream_t st);
+// Adjoint sweep.  adjoint_plan picks the tiles and returns the steps a launch may take;
+// threads: of its blocks.  launch_adjoint_steps reverses the steps from forward state i1 down to
+// i1 + 1 - ns; state i > 0 lies at element offset i stride of seg, state 0 at ck.
+// launch_adjoint_seed writes the first mu from wtj, dJ/dT at the interior nodes.
+int adjoint_plan(const KParams &P, TileGrid &grid, int &threads);
+hipError_t launch_adjoint_steps(int storage, const void *ck, const void *seg, long long stride, const KParams &P,
+                                const AdjBufs &A, const TileGrid &g, int threads, int i1, int ns, hipStream_t st);
+hipError_t launch_adjoint_seed(const KParams &P, const double *wtj, double *mu, hipStream_t st);
 
 // Batched stepping: items are (problem, tile) / (problem, wall block) pairs.
 // bx: block width of the batched update, one of batch_width(0..2).

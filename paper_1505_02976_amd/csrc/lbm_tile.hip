@@ -26,7 +26,7 @@
 // grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
 #include <cmath>
 
-#include "lbm_kernels.h"
+#include "lbm_tile.h"
 
 namespace lbm {
 
@@ -36,43 +36,6 @@ constexpr int TILE_NT = 512;      // nodes of the largest region, threads of the
 __device__ __forceinline__ void lds_put(double *p, double v, float) { *p = v; }
 __device__ __forceinline__ void lds_put(float *p, float v, float) { *p = v; }
 __device__ __forceinline__ void lds_put(__half *p, float v, float scale) { *p = __float2half(v * scale); }
-
-// The launch constants as a kernel of several steps uses them: read again by scalar loads in
-// every step.  Kept across the loop they, and the products the compiler forms of them ahead
-// of it, take vector registers.
-using KConst = const __attribute__((address_space(4))) KParams *;
-
-__device__ __forceinline__ KConst fresh(KConst p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
-template <typename T, typename U>
-__device__ __forceinline__ void copy_consts(T *d, const __attribute__((address_space(4))) U *q)
-{
-    static_assert(sizeof(T) % sizeof(U) == 0, "a struct of U only");
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / sizeof(U)); ++i) reinterpret_cast<U *>(d)[i] = q[i];
-}
-__device__ __forceinline__ void load_consts(KConst p, Cst<float> &k)
-{
-    copy_consts(&k, (const __attribute__((address_space(4))) float *)&p->cf);
-}
-__device__ __forceinline__ void load_consts(KConst p, Cst<double> &k)
-{
-    copy_consts(&k, (const __attribute__((address_space(4))) double *)&p->cd);
-}
-__device__ __forceinline__ void load_eps(KConst p, EpsC<float> &e)
-{
-    e.epsd = p->eps; e.c0 = p->c0; e.c1 = p->c1;
-    e.eps = p->ef.eps; e.ieps = p->ef.ieps; e.dlin = p->ef.dlin; e.dquad = p->ef.dquad; e.bM = p->ef.bM;
-}
-__device__ __forceinline__ void load_eps(KConst p, EpsC<double> &e)
-{
-    e.epsd = p->eps; e.c0 = p->c0; e.c1 = p->c1;
-    e.eps = p->ed.eps; e.ieps = p->ed.ieps; e.dlin = p->ed.dlin; e.dquad = p->ed.dquad; e.bM = p->ed.bM;
-}
 
 // Region of a tile: the nodes of the launch's first step.
 struct TileRegion {
@@ -85,8 +48,7 @@ struct TileRegion {
 __device__ __forceinline__ TileRegion tile_region(const KParams &P, const TileGrid &g, int b, int ns)
 {
     TileRegion t;
-    const int ty = g.nbx == 1 ? b : (int)(((unsigned long long)(unsigned)b * g.magic) >> 32);   // b / nbx
-    const int tx = b - ty * g.nbx;
+    const int ty = tile_row(g, b), tx = b - ty * g.nbx;
     t.X0 = tx * g.tw + min(tx, g.rx); t.X1 = t.X0 + g.tw + (tx < g.rx ? 1 : 0);
     t.Y0 = ty * g.th + min(ty, g.ry); t.Y1 = t.Y0 + g.th + (ty < g.ry ? 1 : 0);
     t.xlo = t.X0 - (ns - 1); t.xhi = t.X1 + (ns - 1); t.ylo = t.Y0 - (ns - 1); t.yhi = t.Y1 + (ns - 1);
@@ -232,18 +194,6 @@ k_batch_tile(const BatchProblem *__restrict__ probs, const int2 *__restrict__ it
     const BatchProblem &B = probs[__builtin_amdgcn_readfirstlane(it.x)];
     tile_block<S, FIELD>(static_cast<const S *>(B.buf[parity]), static_cast<S *>(B.buf[parity ^ 1]), B.P,
                          (KConst)&B.P, B.tile, __builtin_amdgcn_readfirstlane(it.y), ns, 0, lds);
-}
-
-// Tiles of at most tw x th nodes (of equal size to within one node).
-static TileGrid tile_grid(const KParams &P, int tw, int th)
-{
-    TileGrid g;
-    g.nbx = (P.nx + tw - 1) / tw;
-    g.nby = (P.ny + th - 1) / th;
-    g.tw = P.nx / g.nbx; g.rx = P.nx % g.nbx;
-    g.th = P.ny / g.nby; g.ry = P.ny % g.nby;
-    g.magic = g.nbx > 1 ? (unsigned)(0x100000000ull / g.nbx + 1) : 0;
-    return g;
 }
 
 // Largest region of a launch of ns steps: its width and height.
