@@ -87,8 +87,7 @@ size_t lbm3_workspace_bytes(const lbm3_params *params);
 lbm_status lbm3_init(const lbm3_params *params, void *workspace, size_t workspace_bytes,
                      void *hip_stream, lbm3_ctx **out);
 
-/* Enqueues nsteps time steps (collide, stream, boundary scheme; per step one launch over
- * the interior nodes and, with walls, one over the wall nodes).  Asynchronous;
+/* Enqueues nsteps time steps (collide, stream, boundary scheme; one launch per step).  Asynchronous;
  * nsteps < 0 is LBM_ERR_INVALID. */
 lbm_status lbm3_step(lbm3_ctx *ctx, int64_t nsteps);
 
@@ -108,7 +107,7 @@ lbm_status lbm3_populations(lbm3_ctx *ctx, double *f, double *g);
  * mean along each periodic in-plane direction, the trapezoid rule along each walled one; a
  * heat flux along +n counts positive at both walls of a pair).  FP64 arithmetic in a fixed summation order.  Needs that wall to exist
  * (LBM_ERR_INVALID otherwise) and T_hot != T_cold.  *nu_host receives the value.
- * Synchronizes. */
+ * Uses the population buffer that the next step overwrites as scratch.  Synchronizes. */
 lbm_status lbm3_nusselt(lbm3_ctx *ctx, int32_t wall, double *nu_host);
 
 /* The library's D3Q19 velocities (c: 19 x 3 ints, host) in population order; returns 19. */

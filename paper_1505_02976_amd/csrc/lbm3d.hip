@@ -9,6 +9,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -18,6 +19,7 @@
 
 #include "../../include/lbm3d.h"
 #include "lbm_error.h"
+#include "lbm_xcd.h"
 
 namespace lbm3 {
 
@@ -147,21 +149,27 @@ template <> struct Arith<float> { using R = float; };
 template <> struct Arith<__half> { using R = float; };
 
 // Load and store of one stored deviation.  FP16 holds 256 times the deviation: the
-// deviations are small, and the scale keeps them clear of FP16's subnormal range.  Stores
-// are non-temporal: the next step reads them from HBM, not from this launch's caches.
+// deviations are small, and the scale keeps them clear of FP16's subnormal range.  NT: a
+// non-temporal store, for launches whose wavefronts write whole cache lines (lines_whole).
 template <typename S> struct St3 {
     template <typename R> static __device__ __forceinline__ R ld(const S *p) { return R(*p); }
-    template <typename R> static __device__ __forceinline__ void st(S *p, R v) { __builtin_nontemporal_store(S(v), p); }
+    template <bool NT, typename R> static __device__ __forceinline__ void st(S *p, R v)
+    {
+        if (NT) __builtin_nontemporal_store(S(v), p);
+        else *p = S(v);
+    }
 };
 template <> struct St3<__half> {
     template <typename R> static __device__ __forceinline__ R ld(const __half *p)
     {
         return R(__half2float(*p) * (1.0f / 256.0f));
     }
-    template <typename R> static __device__ __forceinline__ void st(__half *p, R v)
+    template <bool NT, typename R> static __device__ __forceinline__ void st(__half *p, R v)
     {
-        __builtin_nontemporal_store(__half_as_ushort(__float2half(float(v) * 256.0f)),
-                                    reinterpret_cast<unsigned short *>(p));
+        const unsigned short h = __half_as_ushort(__float2half(float(v) * 256.0f));
+        unsigned short *o = reinterpret_cast<unsigned short *>(p);
+        if (NT) __builtin_nontemporal_store(h, o);
+        else *o = h;
     }
 };
 
@@ -322,30 +330,37 @@ template <typename R> __device__ __forceinline__ R w3(int q) { return q < 7 ? w3
 // Equilibria (Eqs. EQFIN, EQTSHIN, TeEDFEQ) of direction q for pressure term ep = eps p;
 // the flow equilibrium as a deviation (f_0^eq - rho0 for q = 0).  Used by the boundary
 // scheme and the initialisation; the collision below evaluates the same terms pairwise.
+// The contractions of one direction: its weight, 3 omega_q, c.u and c.S.c (0 at rest).
+template <typename R>
+__device__ __forceinline__ R feq_of(bool rest, R w, R w3q, R cu, R cSc, const K3 &K, const Por<R> &e, R ep, const R *u,
+                                    const R *S)
+{
+    const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const R trS = S[0] + S[3] + S[5];
+    const R base = rest ? R(-2) * ep : R(3) * w * ep;      // -(1 - omega_0) eps p / cs^2; omega_q eps p / cs^2
+    return base + (rest ? R(0) : w3q * cu) + w * R(4.5) * (cu * cu - uu * R(1.0 / 3.0)) * e.ieps
+         + w * cst3<R>(K).A15 * (cSc - trS * R(1.0 / 3.0));
+}
 template <typename R>
 __device__ __forceinline__ R feq(int q, const K3 &K, const Por<R> &e, R ep, const R *u, const R *S)
 {
-    const R w = R(W(q));
-    const R cu = cdot<R>(q, u);
-    const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const R cSc = cScq<R>(q, S);
-    const R trS = S[0] + S[3] + S[5];
-    const R base = q == 0 ? R(-2) * ep : R(3) * w * ep;      // -(1 - omega_0) eps p / cs^2; omega_q eps p / cs^2
-    return base + (q == 0 ? R(0) : w3<R>(q) * cu) + w * R(4.5) * (cu * cu - uu * R(1.0 / 3.0)) * e.ieps
-         + w * cst3<R>(K).A15 * (cSc - trS * R(1.0 / 3.0));
+    return feq_of<R>(q == 0, R(W(q)), w3<R>(q), cdot<R>(q, u), cScq<R>(q, S), K, e, ep, u, S);
 }
 
 // The temperature equilibrium as a deviation, g^eq_q - omega_q sigma T0, for T = T0 + Td.
 template <typename R>
+__device__ __forceinline__ R geq_of(bool rest, R w, R w3q, R cu, R cg, const K3 &K, const Por<R> &e, R Td, R T, R ep,
+                                    const R *u)
+{
+    const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const R pres = rest ? R(-2) * T * ep : R(3) * w * T * ep;   // varpi_q T eps p / (cs^2 rho0)
+    return w * (cst3<R>(K).sig * Td + T * R(4.5) * (cu * cu - uu * R(1.0 / 3.0)) * e.ieps) + pres
+         + (rest ? R(0) : w3q * (T * cu + cst3<R>(K).sigB3 * cg));
+}
+template <typename R>
 __device__ __forceinline__ R geq(int q, const K3 &K, const Por<R> &e, R Td, R T, R ep, const R *u, const R *gT)
 {
-    const R w = R(W(q));
-    const R cu = cdot<R>(q, u);
-    const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const R cg = cdot<R>(q, gT);
-    const R pres = q == 0 ? R(-2) * T * ep : R(3) * w * T * ep;   // varpi_q T eps p / (cs^2 rho0)
-    return w * (cst3<R>(K).sig * Td + T * R(4.5) * (cu * cu - uu * R(1.0 / 3.0)) * e.ieps) + pres
-         + (q == 0 ? R(0) : w3<R>(q) * (T * cu + cst3<R>(K).sigB3 * cg));
+    return geq_of<R>(q == 0, R(W(q)), w3<R>(q), cdot<R>(q, u), cdot<R>(q, gT), K, e, Td, T, ep, u);
 }
 
 // BGK collision with forcing and sources (Eqs. LBEeq, FtermF, TEqColli, Eq:Tforce),
@@ -365,8 +380,13 @@ __device__ __forceinline__ R geq(int q, const K3 &K, const Por<R> &e, R Td, R T,
 // energy are conserved by the arithmetic, not only up to the rounding of the lattice
 // weights (in FP32 that rounding biases the heat balance by about 1e-8 sigma T / tau_T per
 // step).
+template <typename R> struct Coll {
+    R b0, k45, c9, m3b5, b1, T45, sc, bsg, V[3], Ef, Eg;
+};
+
+// The per-node coefficients.
 template <typename R>
-__device__ __forceinline__ void collide(R *f, R *g, const Mac<R> &m, const K3 &K, const Por<R> &e)
+__device__ __forceinline__ Coll<R> coll_of(const Mac<R> &m, const K3 &K, const Por<R> &e)
 {
     const C3<R> &c = cst3<R>(K);
     const R ep = e.eps * m.p, ieps = e.ieps;
@@ -374,94 +394,148 @@ __device__ __forceinline__ void collide(R *f, R *g, const Mac<R> &m, const K3 &K
     const R uF = m.u[0] * m.F[0] + m.u[1] * m.F[1] + m.u[2] * m.F[2];
     const R ugT = m.u[0] * m.gT[0] + m.u[1] * m.gT[1] + m.u[2] * m.gT[2];
     const R trS = m.S[0] + m.S[3] + m.S[5];
-    const R V[3] = {m.T * m.F[0] + ep * m.gT[0], m.T * m.F[1] + ep * m.gT[1], m.T * m.F[2] + ep * m.gT[2]};
-    // per-node coefficients
-    const R b0 = R(3) * ep - R(1.5) * uu * ieps - R(0.5) * c.A * trS;
-    const R k45 = R(4.5) * ieps, c9 = R(9) * c.fF * ieps, m3b5 = R(-3) * (c.fF * uF * ieps);
-    const R b1 = c.sig * m.Td - R(1.5) * m.T * uu * ieps + R(3) * m.T * ep;
-    const R T45 = k45 * m.T;
-    const R sc = c.itT * m.T + c.fT * ((ieps - c.isig) * ugT + c.Q * c.isig);
-    const R bsg = c.itT * c.sigB3;
-    R Ef = R(0), Eg = R(0);
-#pragma unroll
-    for (int q = 1; q < NQ; q += 2) {
-        const R w = R(W(q)), w3q = w3<R>(q);
-        const R cu = cdot<R>(q, m.u), cF = cdot<R>(q, m.F), cV = cdot<R>(q, V), cg = cdot<R>(q, m.gT);
-        const R cSc = cScq<R>(q, m.S), cu2 = cu * cu;
-        const R Ae = w * (c.itf * (c.A15 * cSc + (k45 * cu2 + b0)) + (c9 * (cu * cF) + m3b5));
-        const R Ao = w3q * (c.itf * cu + c.fF * cF);
-        const R Ge = w * (c.itT * (T45 * cu2 + b1) + c.fT * c.Q);
-        const R Go = w3q * (sc * cu + (bsg * cg + c.fT * cV));
-        f[q] = c.of * f[q] + (Ae + Ao);
-        f[q + 1] = c.of * f[q + 1] + (Ae - Ao);
-        g[q] = c.og * g[q] + (Ge + Go);
-        g[q + 1] = c.og * g[q + 1] + (Ge - Go);
-        Ef += Ae;
-        Eg += Ge;
-    }
-    f[0] = c.of * f[0] - R(2) * Ef;
-    g[0] = c.og * g[0] + (c.sig * m.Td * c.itT + c.fT * c.Q - R(2) * Eg);
+    Coll<R> t;
+    t.V[0] = m.T * m.F[0] + ep * m.gT[0];
+    t.V[1] = m.T * m.F[1] + ep * m.gT[1];
+    t.V[2] = m.T * m.F[2] + ep * m.gT[2];
+    t.b0 = R(3) * ep - R(1.5) * uu * ieps - R(0.5) * c.A * trS;
+    t.k45 = R(4.5) * ieps;
+    t.c9 = R(9) * c.fF * ieps;
+    t.m3b5 = R(-3) * (c.fF * uF * ieps);
+    t.b1 = c.sig * m.Td - R(1.5) * m.T * uu * ieps + R(3) * m.T * ep;
+    t.T45 = t.k45 * m.T;
+    t.sc = c.itT * m.T + c.fT * ((ieps - c.isig) * ugT + c.Q * c.isig);
+    t.bsg = c.itT * c.sigB3;
+    t.Ef = t.Eg = R(0);
+    return t;
 }
 
-// Pre-collision populations and state of node (x, y, z).  Interior: pulled populations
-// and their moments.  Wall node: the non-equilibrium extrapolation from the next node
-// inward x_f (and T of x_ff on prescribed-gradient walls), whose state is the one the
-// scheme assigns (T_b, u_b, p and S of x_f, the boundary grad T).  On an edge or a vertex
-// where two or three walls meet, x_f is the inward diagonal neighbour, the wall is at rest,
-// an isothermal wall's temperature wins over a prescribed gradient (among isothermal walls
-// x first, then y, then z), and each prescribed gradient sets its own normal component of
-// grad T, as at the corners in two dimensions.
-template <typename S, typename R, bool WALLS = true>
-__device__ __forceinline__ void node_state(const S *__restrict__ src, const K3 &K, int x, int y, int z,
-                                           R *f, R *g, Mac<R> &m, Por<R> &e)
+// One pair of opposite directions, from the first one's contractions c.u, c.F, c.V, c.grad T
+// and c.S.c; Ae and Ge are the even parts.
+template <typename R>
+__device__ __forceinline__ void collide_of(R w, R w3q, R cu, R cF, R cV, R cg, R cSc, const K3 &K, const Coll<R> &t,
+                                           R *f, R *g, R &Ae, R &Ge)
 {
-    const size_t plane = (size_t)K.nx * K.ny, k = (size_t)z * plane + (size_t)y * K.nx + x;
-    e = por_of<R>(K, k);
-    int xw = -1, yw = -1, zw = -1;
-    if (WALLS) wall_of(K, x, y, z, xw, yw, zw);
-    if (xw < 0 && yw < 0 && zw < 0) {
-        pull<S, R>(src, K, x, y, z, f, g);
-        macro3<R>(f, g, K, e, m);
-        return;
-    }
-    const int dx = xw == 2 ? 1 : (xw == 3 ? -1 : 0), dz = zw == 0 ? 1 : (zw == 1 ? -1 : 0);
-    const int dy = yw == 4 ? 1 : (yw == 5 ? -1 : 0);
-    R ff[NQ], gf[NQ];
-    pull<S, R>(src, K, x + dx, y + dy, z + dz, ff, gf);
-    const Por<R> ef = por_of<R>(K, (size_t)((long long)k + dz * (long long)plane + dy * (long long)K.nx + dx));
-    Mac<R> mf;
-    macro3<R>(ff, gf, K, ef, mf);
-    R Tdb, gb[3] = {mf.gT[0], mf.gT[1], mf.gT[2]};
-    const int iso = (xw >= 0 && K.wkind[xw] == 0) ? xw
-                  : ((yw >= 0 && K.wkind[yw] == 0) ? yw : ((zw >= 0 && K.wkind[zw] == 0) ? zw : -1));
-    if (iso >= 0) {
-        Tdb = R(K.wT[iso] - K.T0);
-    } else {
-        R f2[NQ], g2[NQ];
-        pull<S, R>(src, K, x + 2 * dx, y + 2 * dy, z + 2 * dz, f2, g2);
-        R sg = R(0);
+    const C3<R> &c = cst3<R>(K);
+    const R cu2 = cu * cu;
+    Ae = w * (c.itf * (c.A15 * cSc + (t.k45 * cu2 + t.b0)) + (t.c9 * (cu * cF) + t.m3b5));
+    const R Ao = w3q * (c.itf * cu + c.fF * cF);
+    Ge = w * (c.itT * (t.T45 * cu2 + t.b1) + c.fT * c.Q);
+    const R Go = w3q * (t.sc * cu + (t.bsg * cg + c.fT * cV));
+    f[0] = c.of * f[0] + (Ae + Ao);
+    f[1] = c.of * f[1] + (Ae - Ao);
+    g[0] = c.og * g[0] + (Ge + Go);
+    g[1] = c.og * g[1] + (Ge - Go);
+}
+
+// Directions q and q + 1 (q odd).
+template <typename R>
+__device__ __forceinline__ void collide_pair(int q, R *f, R *g, const Mac<R> &m, const K3 &K, Coll<R> &t)
+{
+    R Ae, Ge;
+    collide_of<R>(R(W(q)), w3<R>(q), cdot<R>(q, m.u), cdot<R>(q, m.F), cdot<R>(q, t.V), cdot<R>(q, m.gT),
+                  cScq<R>(q, m.S), K, t, f + q, g + q, Ae, Ge);
+    t.Ef += Ae;
+    t.Eg += Ge;
+}
+
+template <typename R>
+__device__ __forceinline__ void collide_rest(R *f, R *g, const Mac<R> &m, const K3 &K, const Coll<R> &t)
+{
+    const C3<R> &c = cst3<R>(K);
+    f[0] = c.of * f[0] - R(2) * t.Ef;
+    g[0] = c.og * g[0] + (c.sig * m.Td * c.itT + c.fT * c.Q - R(2) * t.Eg);
+}
+
+// The boundary scheme, the non-equilibrium extrapolation from the next node inward x_f (and T
+// of x_ff on prescribed-gradient walls), whose state is the one the scheme assigns (T_b, u_b, p
+// and S of x_f, the boundary grad T).  On an edge or a vertex where two or three walls meet,
+// x_f is the inward diagonal neighbour, the wall is at rest, an isothermal wall's temperature
+// wins over a prescribed gradient (among isothermal walls x first, then y, then z), and each
+// prescribed gradient sets its own normal component of grad T, as at the corners in two
+// dimensions.
+// The walls of a node, the step towards x_f, and the isothermal wall that gives T (or -1).
+struct Wall3 { int xw, yw, zw, dx, dy, dz, iso; };
+
+__device__ __forceinline__ Wall3 wall3(const K3 &K, int x, int y, int z)
+{
+    Wall3 w;
+    wall_of(K, x, y, z, w.xw, w.yw, w.zw);
+    w.dx = w.xw == 2 ? 1 : (w.xw == 3 ? -1 : 0);
+    w.dy = w.yw == 4 ? 1 : (w.yw == 5 ? -1 : 0);
+    w.dz = w.zw == 0 ? 1 : (w.zw == 1 ? -1 : 0);
+    w.iso = (w.xw >= 0 && K.wkind[w.xw] == 0) ? w.xw
+          : ((w.yw >= 0 && K.wkind[w.yw] == 0) ? w.yw : ((w.zw >= 0 && K.wkind[w.zw] == 0) ? w.zw : -1));
+    return w;
+}
+
+// T - T0 of a node from its temperature populations.
+template <typename S, typename R>
+__device__ __forceinline__ R pull_Td(const S *__restrict__ src, const K3 &K, int x, int y, int z)
+{
+    R f[NQ], g[NQ];
+    pull<S, R>(src, K, x, y, z, f, g);
+    R sg = R(0);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) sg += g2[q];
-        const R Tdff = (sg + cst3<R>(K).halfQ) * cst3<R>(K).isig;
-        if (xw >= 0) gb[0] = R(dx * K.wdTdn[xw]);
-        if (yw >= 0) gb[1] = R(dy * K.wdTdn[yw]);
-        if (zw >= 0) gb[2] = R(dz * K.wdTdn[zw]);
-        Tdb = (R(4) * mf.Td - Tdff - R(2) * (R(dx) * gb[0] + R(dy) * gb[1] + R(dz) * gb[2])) * R(1.0 / 3.0);
+    for (int q = 0; q < NQ; ++q) sg += g[q];
+    return (sg + cst3<R>(K).halfQ) * cst3<R>(K).isig;
+}
+
+// State of a wall node from x_f's and, off the isothermal walls, T - T0 of x_ff.
+template <typename R>
+__device__ __forceinline__ void wall_mac(const K3 &K, const Wall3 &w, const Por<R> &e, const Mac<R> &mf, R Tdff, Mac<R> &m)
+{
+    R Tdb, gb[3] = {mf.gT[0], mf.gT[1], mf.gT[2]};
+    if (w.iso >= 0) {
+        Tdb = R(K.wT[w.iso] - K.T0);
+    } else {
+        if (w.xw >= 0) gb[0] = R(w.dx * K.wdTdn[w.xw]);
+        if (w.yw >= 0) gb[1] = R(w.dy * K.wdTdn[w.yw]);
+        if (w.zw >= 0) gb[2] = R(w.dz * K.wdTdn[w.zw]);
+        Tdb = (R(4) * mf.Td - Tdff - R(2) * (R(w.dx) * gb[0] + R(w.dy) * gb[1] + R(w.dz) * gb[2])) * R(1.0 / 3.0);
     }
     m.Td = Tdb;
     m.T = cst3<R>(K).T0 + Tdb;
-    const int nwall = (xw >= 0) + (yw >= 0) + (zw >= 0);
-    const int wu = nwall > 1 ? -1 : (xw >= 0 ? xw : (yw >= 0 ? yw : zw));   // an edge or a vertex is at rest
+    const int nwall = (w.xw >= 0) + (w.yw >= 0) + (w.zw >= 0);
+    const int wu = nwall > 1 ? -1 : (w.xw >= 0 ? w.xw : (w.yw >= 0 ? w.yw : w.zw));   // an edge or a vertex is at rest
     for (int a = 0; a < 3; ++a) { m.u[a] = wu < 0 ? R(0) : R(K.wu[wu][a]); m.gT[a] = gb[a]; }
     force<R>(K, e, m.u, m.Td, m.F);
     m.p = mf.p;
     for (int c = 0; c < 6; ++c) m.S[c] = mf.S[c];
+}
+
+// Populations q of a wall node in place of x_f's.
+template <typename R>
+__device__ __forceinline__ void wall_pop(int q, const K3 &K, const Por<R> &e, const Mac<R> &m, const Por<R> &ef,
+                                         const Mac<R> &mf, R *f, R *g)
+{
     const R epb = e.eps * mf.p, epf = ef.eps * mf.p;   // the wall node's porosity, x_f's pressure
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        f[q] = feq<R>(q, K, e, epb, m.u, mf.S) + (ff[q] - feq<R>(q, K, ef, epf, mf.u, mf.S));
-        g[q] = geq<R>(q, K, e, m.Td, m.T, epb, m.u, gb) + (gf[q] - geq<R>(q, K, ef, mf.Td, mf.T, epf, mf.u, mf.gT));
+    f[q] = feq<R>(q, K, e, epb, m.u, mf.S) + (f[q] - feq<R>(q, K, ef, epf, mf.u, mf.S));
+    g[q] = geq<R>(q, K, e, m.Td, m.T, epb, m.u, m.gT) + (g[q] - geq<R>(q, K, ef, mf.Td, mf.T, epf, mf.u, mf.gT));
+}
+
+// Pre-collision populations and state of node (x, y, z).  Interior: pulled populations
+// and their moments.  Wall node: the boundary scheme.
+template <typename S, typename R>
+__device__ __forceinline__ void node_state(const S *__restrict__ src, const K3 &K, int x, int y, int z,
+                                           R *f, R *g, Mac<R> &m, Por<R> &e)
+{
+    const long long plane = (long long)K.nx * K.ny, k = z * plane + (long long)y * K.nx + x;
+    e = por_of<R>(K, (size_t)k);
+    const Wall3 w = wall3(K, x, y, z);
+    pull<S, R>(src, K, x + w.dx, y + w.dy, z + w.dz, f, g);
+    if (w.xw < 0 && w.yw < 0 && w.zw < 0) {
+        macro3<R>(f, g, K, e, m);
+        return;
     }
+    R Tdff = R(0);
+    if (w.iso < 0) Tdff = pull_Td<S, R>(src, K, x + 2 * w.dx, y + 2 * w.dy, z + 2 * w.dz);
+    const Por<R> ef = por_of<R>(K, (size_t)(k + w.dz * plane + w.dy * (long long)K.nx + w.dx));
+    Mac<R> mf;
+    macro3<R>(f, g, K, ef, mf);
+    wall_mac<R>(K, w, e, mf, Tdff, m);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) wall_pop<R>(q, K, e, m, ef, mf, f, g);
 }
 
 __device__ __forceinline__ bool node_xyz(const K3 &K, int &x, int &y, int &z)
@@ -475,99 +549,265 @@ __device__ __forceinline__ bool node_xyz(const K3 &K, int &x, int &y, int &z)
 }
 
 // Post-collision populations (deviations) into the buffer.
-template <typename S, typename R>
+template <typename S, bool NT, typename R>
 __device__ __forceinline__ void store(S *__restrict__ dst, const K3 &K, unsigned k, const R *f, const R *g)
 {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        St3<S>::template st<R>(dst + (size_t)q * K.n + k, f[q]);
-        St3<S>::template st<R>(dst + (size_t)(NQ + q) * K.n + k, g[q]);
+        St3<S>::template st<NT, R>(dst + (size_t)q * K.n + k, f[q]);
+        St3<S>::template st<NT, R>(dst + (size_t)(NQ + q) * K.n + k, g[q]);
     }
 }
 
 constexpr int B3 = 256;
+constexpr unsigned SLAB_NODES = 4096;
 
-// Extent of the interior along x and z: all nodes of a periodic direction, all but the two
+// Extent of the interior along x, y and z: all nodes of a periodic direction, all but the two
 // wall nodes of a walled one.
 __host__ __device__ __forceinline__ int inner_x(const K3 &K) { return K.px ? K.nx : K.nx - 2; }
 __host__ __device__ __forceinline__ int inner_y(const K3 &K) { return K.py ? K.ny : K.ny - 2; }
 __host__ __device__ __forceinline__ int inner_z(const K3 &K) { return K.pz ? K.nz : K.nz - 2; }
 
-// One time step, pull, state, collide, store, in one launch: its first blocks take the
-// wall nodes (boundary scheme), the remaining ones the interior nodes (no boundary-scheme
-// code).  Run side by side, the short wall blocks no longer add a launch of their own to
-// every step.
-// Interior node i of interior plane `plane` (32-bit index arithmetic: planes and the grid
-// stay below 2^31 nodes, checked on the host).
-template <typename S>
-__device__ __forceinline__ void k3_interior_node(const S *__restrict__ src, S *__restrict__ dst, const K3 &K,
-                                                 unsigned i, int plane)
+// How one launch shares out a step: slabs of `planes` interior planes; a slab's first nbw
+// blocks take the wall nodes of its planes (`walls` each) and its share (zw nodes) of the two z
+// walls, the next nbi its interior nodes.
+// The wall nodes x = 0 and x = nx - 1 off the edges are left to the interior blocks that hold
+// their x_f (XW) where a row has XW_ROW interior nodes or more.  In wall blocks their lanes lie
+// a row apart, so that each load instruction touches 64 lines for one value each.  Time of a
+// step with the x walls in wall blocks and inside: 120 x 4 x 120 FP64 16.3 and 11.8 us,
+// 121 x 95 x 83 with porosity per node 186 and 162 (FP64), 95 and 73 (FP32), 54 and 48 (FP16);
+// 10 x 180 x 60, the shortest such row, 29.0 and 22.6 (FP64), 16.2 and 13.4 (FP32), 11.4 and 13.1
+// (FP16).  Below that a block would hold more than 68 such nodes.
+constexpr int XW_ROW = 8;
+struct Slabs {
+    unsigned planes, count;
+    unsigned inner, walls, zw;     // interior and wall nodes per plane, z wall nodes per slab
+    unsigned nbw, nbi;
+};
+
+// What an interior node hands over to the wall node next to it: x_f's pre-collision
+// populations, its state, T - T0 of x_ff, its porosity; [value][slot], two slots per row.
+constexpr int XW_SLOTS = 2 * (B3 / XW_ROW + 2), XW_VALS = 2 * NQ + 18;
+template <typename R> struct XWall {
+    R v[XW_VALS][XW_SLOTS];
+    R Ae[NQ / 2][XW_SLOTS], Ge[NQ / 2][XW_SLOTS];
+};
+
+// Components of the first direction of pair j (q = 2 j + 1) plus 1, two bits per pair.
+constexpr unsigned pair_code(int axis)
+{
+    unsigned r = 0;
+    for (int j = 0; j < NQ / 2; ++j) {
+        const int q = 2 * j + 1, c = axis == 0 ? CX[q] : (axis == 1 ? CY[q] : CZ[q]);
+        r |= (unsigned)(c + 1) << (2 * j);
+    }
+    return r | 1u << (2 * (NQ / 2));     // the rest direction, j = 9
+}
+
+// Wall node in slot s, its directions shared out over ten lanes: lane j < 9 extrapolates and
+// collides pair j, lane 9 the rest direction, after all even parts are there.  The
+// contractions are sums of the same terms in the same order as for compile-time directions
+// (products by 0 and +-1 are exact).
+template <typename S, typename R>
+__device__ __forceinline__ void x_wall_pair(S *__restrict__ dst, const K3 &K, XWall<R> &sh, bool on, int s, int j,
+                                            int x, int y, int z)
+{
+    const unsigned k = ((unsigned)z * (unsigned)K.ny + (unsigned)y) * (unsigned)K.nx + (unsigned)x;
+    Mac<R> mf, m;
+    Por<R> e, ef;
+    Coll<R> t;
+    R f[2], g[2];
+    const bool rest = j == NQ / 2;
+    const int q = rest ? 0 : 2 * j + 1;
+    if (on) {
+        mf.Td = sh.v[2 * NQ][s];
+        mf.T = sh.v[2 * NQ + 1][s];
+        for (int a = 0; a < 3; ++a) { mf.u[a] = sh.v[2 * NQ + 2 + a][s]; mf.gT[a] = sh.v[2 * NQ + 5 + a][s]; }
+        for (int a = 0; a < 6; ++a) mf.S[a] = sh.v[2 * NQ + 8 + a][s];
+        mf.p = sh.v[2 * NQ + 14][s];
+        ef.eps = sh.v[2 * NQ + 16][s];
+        ef.ieps = sh.v[2 * NQ + 17][s];
+        e = por_of<R>(K, k);
+        wall_mac<R>(K, wall3(K, x, y, z), e, mf, sh.v[2 * NQ + 15][s], m);
+        t = coll_of<R>(m, K, e);
+        const R c[3] = {R((int)(pair_code(0) >> (2 * j) & 3) - 1), R((int)(pair_code(1) >> (2 * j) & 3) - 1),
+                        R((int)(pair_code(2) >> (2 * j) & 3) - 1)};
+        auto dot = [&](const R *v) { return c[0] * v[0] + c[1] * v[1] + c[2] * v[2]; };
+        const R *A = mf.S;
+        const R cSc = c[0] * c[0] * A[0] + c[1] * c[1] * A[3] + c[2] * c[2] * A[5] + c[0] * c[1] * (R(2) * A[1])
+                    + c[0] * c[2] * (R(2) * A[2]) + c[1] * c[2] * (R(2) * A[4]);
+        const R w = rest ? R(W(0)) : (q < 7 ? R(W(1)) : R(W(7))), w3q = q < 7 ? w3a<R>() : w3e<R>();
+        const R epb = e.eps * mf.p, epf = ef.eps * mf.p;
+        const R ub = dot(m.u), uf = dot(mf.u), gb = dot(m.gT), gf = dot(mf.gT);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const R sg = o ? R(-1) : R(1);
+            const int qo = rest ? 0 : q + o;
+            f[o] = feq_of<R>(rest, w, w3q, sg * ub, cSc, K, e, epb, m.u, mf.S)
+                 + (sh.v[qo][s] - feq_of<R>(rest, w, w3q, sg * uf, cSc, K, ef, epf, mf.u, mf.S));
+            g[o] = geq_of<R>(rest, w, w3q, sg * ub, sg * gb, K, e, m.Td, m.T, epb, m.u)
+                 + (sh.v[NQ + qo][s] - geq_of<R>(rest, w, w3q, sg * uf, sg * gf, K, ef, mf.Td, mf.T, epf, mf.u));
+        }
+        if (!rest) {
+            collide_of<R>(w, w3q, ub, dot(m.F), dot(t.V), gb, cSc, K, t, f, g, sh.Ae[j][s], sh.Ge[j][s]);
+            for (int o = 0; o < 2; ++o) {
+                St3<S>::template st<false, R>(dst + (size_t)(q + o) * K.n + k, f[o]);
+                St3<S>::template st<false, R>(dst + (size_t)(NQ + q + o) * K.n + k, g[o]);
+            }
+        }
+    }
+    __syncthreads();
+    if (on && rest) {
+        for (int i = 0; i < NQ / 2; ++i) { t.Ef += sh.Ae[i][s]; t.Eg += sh.Ge[i][s]; }
+        collide_rest<R>(f, g, m, K, t);
+        St3<S>::template st<false, R>(dst + k, f[0]);
+        St3<S>::template st<false, R>(dst + (size_t)NQ * K.n + k, g[0]);
+    }
+}
+
+// An interior block: nodes i0 + threadIdx.x of np planes from z0, numbered over the interior
+// (no boundary-scheme code but for XW): pull, state, collide, store.
+template <typename S, bool XW, bool NT>
+__device__ __forceinline__ void k3_interior(const S *__restrict__ src, S *__restrict__ dst, const K3 &K, unsigned i0,
+                                            unsigned count, int z0)
 {
     using R = typename Arith<S>::R;
     const unsigned nxi = (unsigned)inner_x(K), nyi = (unsigned)inner_y(K);
-    if (i >= nxi * nyi) return;
-    const unsigned yi = i / nxi;
-    const int x = (int)(i - yi * nxi) + (K.px ? 0 : 1), y = (int)yi + (K.py ? 0 : 1);
-    const int z = plane + (K.pz ? 0 : 1);
-    const unsigned k = ((unsigned)z * (unsigned)K.ny + (unsigned)y) * (unsigned)K.nx + (unsigned)x;
-    R f[NQ], g[NQ];
-    Mac<R> m;
-    Por<R> e;
-    node_state<S, R, false>(src, K, x, y, z, f, g, m, e);
-    collide<R>(f, g, m, K, e);
-    store<S, R>(dst, K, k, f, g);
+    const unsigned ox = K.px ? 0 : 1, oy = K.py ? 0 : 1;
+    const unsigned i = i0 + threadIdx.x, row = i / nxi;
+    unsigned zi = row / nyi;
+    __shared__ XWall<R> sh[1];
+    if (i < count) {
+        const int x = (int)(i - row * nxi + ox), y = (int)(row - zi * nyi + oy), z = z0 + (int)zi;
+        const unsigned k = ((unsigned)z * (unsigned)K.ny + (unsigned)y) * (unsigned)K.nx + (unsigned)x;
+        R f[NQ], g[NQ];
+        Mac<R> m;
+        const Por<R> e = por_of<R>(K, k);
+        pull<S, R>(src, K, x, y, z, f, g);
+        macro3<R>(f, g, K, e, m);
+        if (XW && (x == 1 || x == K.nx - 2)) {
+            const int hi = x == 1 ? 0 : 1, s = (int)(2 * (row - i0 / nxi)) + hi;
+            R(*v)[XW_SLOTS] = sh[0].v;
+            for (int q = 0; q < NQ; ++q) { v[q][s] = f[q]; v[NQ + q][s] = g[q]; }
+            v[2 * NQ][s] = m.Td;
+            v[2 * NQ + 1][s] = m.T;
+            for (int a = 0; a < 3; ++a) { v[2 * NQ + 2 + a][s] = m.u[a]; v[2 * NQ + 5 + a][s] = m.gT[a]; }
+            for (int a = 0; a < 6; ++a) v[2 * NQ + 8 + a][s] = m.S[a];
+            v[2 * NQ + 14][s] = m.p;
+            const S *p = src;
+            asm volatile("" : "+s"(p));     // its own plane addresses: kept from pull() they spill
+            v[2 * NQ + 15][s] = (hi ? K.wkind[3] : K.wkind[2]) == 0 ? R(0) : pull_Td<S, R>(p, K, x + (hi ? -1 : 1), y, z);
+            v[2 * NQ + 16][s] = e.eps;
+            v[2 * NQ + 17][s] = e.ieps;
+        }
+        Coll<R> t = coll_of<R>(m, K, e);
+#pragma unroll
+        for (int q = 1; q < NQ; q += 2) collide_pair<R>(q, f, g, m, K, t);
+        collide_rest<R>(f, g, m, K, t);
+        store<S, NT, R>(dst, K, k, f, g);
+    }
+    if (!XW) return;
+    __syncthreads();
+    const unsigned row0 = i0 / nxi, end = min(i0 + B3, count);
+    const unsigned slots = 2 * ((end - 1) / nxi - row0 + 1);
+    for (unsigned s0 = 0; s0 < slots; s0 += B3 / 10) {
+        const unsigned s = s0 + threadIdx.x / 10, r = row0 + s / 2, at = r * nxi + (s & 1 ? nxi - 1 : 0);   // its x_f
+        const bool on = threadIdx.x < B3 / 10 * 10 && s < slots && at >= i0 && at < end;
+        zi = r / nyi;
+        x_wall_pair<S, R>(dst, K, sh[0], on, (int)s, (int)(threadIdx.x % 10), s & 1 ? K.nx - 1 : 0,
+                          (int)(r - zi * nyi + oy), z0 + (int)zi);
+    }
 }
 
-// Wall node i: the z wall planes first, then the x wall planes less their z rows, then the
-// y wall planes less both.
-template <typename S>
+// A wall node: as node_state, but a pair of directions is extrapolated, collided and stored
+// before the next, so that nothing but x_f's populations and the two states stays in
+// registers.
+template <typename S, bool NT>
 __device__ __forceinline__ void k3_wall_node(const S *__restrict__ src, S *__restrict__ dst, const K3 &K,
-                                             long long i)
+                                             int x, int y, int z)
 {
     using R = typename Arith<S>::R;
-    const long long plane = (long long)K.nx * K.ny, zn = K.pz ? 0 : 2 * plane;
-    const long long xside = K.px ? 0 : (long long)K.ny * inner_z(K);
-    const long long yside = K.py ? 0 : (long long)inner_x(K) * inner_z(K);
-    if (i >= zn + 2 * xside + 2 * yside) return;
-    int x, y, z;
-    if (i < zn) {
-        const long long k = i < plane ? i : (long long)(K.nz - 1) * plane + (i - plane);
-        x = (int)(k % K.nx); y = (int)((k / K.nx) % K.ny); z = (int)(k / plane);
-    } else if (i < zn + 2 * xside) {
-        const long long j = i - zn, r = j % xside;
-        x = j < xside ? 0 : K.nx - 1;
-        y = (int)(r % K.ny);
-        z = (int)(r / K.ny) + (K.pz ? 0 : 1);
-    } else {
-        const long long j = i - zn - 2 * xside, r = j % yside;
-        const int nxi = inner_x(K);
-        y = j < yside ? 0 : K.ny - 1;
-        x = (int)(r % nxi) + (K.px ? 0 : 1);
-        z = (int)(r / nxi) + (K.pz ? 0 : 1);
-    }
-    const long long k = ((long long)z * K.ny + y) * K.nx + x;
+    const unsigned k = ((unsigned)z * (unsigned)K.ny + (unsigned)y) * (unsigned)K.nx + (unsigned)x;
+    const Wall3 w = wall3(K, x, y, z);
+    const int xf = x + w.dx, yf = y + w.dy, zf = z + w.dz;
     R f[NQ], g[NQ];
-    Mac<R> m;
-    Por<R> e;
-    node_state<S, R>(src, K, x, y, z, f, g, m, e);
-    collide<R>(f, g, m, K, e);
-    store<S, R>(dst, K, (unsigned)k, f, g);
+    pull<S, R>(src, K, xf, yf, zf, f, g);
+    R Tdff = R(0);
+    if (w.iso < 0) Tdff = pull_Td<S, R>(src, K, xf + w.dx, yf + w.dy, zf + w.dz);
+    const Por<R> e = por_of<R>(K, k);
+    const Por<R> ef = por_of<R>(K, ((size_t)zf * K.ny + yf) * K.nx + xf);
+    Mac<R> mf, m;
+    macro3<R>(f, g, K, ef, mf);
+    wall_mac<R>(K, w, e, mf, Tdff, m);
+    Coll<R> t = coll_of<R>(m, K, e);
+    auto put = [&](int q) {
+        St3<S>::template st<NT, R>(dst + (size_t)q * K.n + k, f[q]);
+        St3<S>::template st<NT, R>(dst + (size_t)(NQ + q) * K.n + k, g[q]);
+    };
+#pragma unroll
+    for (int q = 1; q < NQ; q += 2) {
+        wall_pop<R>(q, K, e, m, ef, mf, f, g);
+        wall_pop<R>(q + 1, K, e, m, ef, mf, f, g);
+        collide_pair<R>(q, f, g, m, K, t);
+        put(q);
+        put(q + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    wall_pop<R>(0, K, e, m, ef, mf, f, g);
+    collide_rest<R>(f, g, m, K, t);
+    put(0);
 }
 
-// Blocks [0, nbw): wall nodes; then nbx blocks per interior plane.  Registers held to the
-// interior's own count (FP32/FP16 five waves per SIMD, FP64 three); the wall blocks, 2 %
-// of the nodes, absorb any spill.
-template <typename S>
+// One time step in one launch.  Where every wavefront writes whole cache lines (NT), stores
+// are non-temporal and blocks run in the dispatched order: 192 x 192 x 96 FP32 199 us a step
+// (5.4 TB/s; 210 us with plain stores, 215 in the order of the XCDs).  Elsewhere rows begin and
+// end inside cache lines whose other part another block writes: a plain store lets the L2 join
+// the two and the order of the XCDs puts neighbouring blocks on one L2, 121 x 95 x 83 with
+// porosity per node 68 -> 43 us (FP16), 97 -> 73 (FP32), 178 -> 162 (FP64), 185 x 171 x 90
+// periodic in x and y 268 -> 201 (FP32).  Registers are held to the
+// interior's own count (FP32/FP16 five waves per SIMD, FP64 three): the spills are in the wall
+// blocks.
+template <typename S, bool XW, bool NT>
 __global__ void __launch_bounds__(B3, sizeof(S) == 8 ? 3 : 5)
-k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, unsigned nbw, unsigned nbx)
+k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, Slabs L)
 {
-    const unsigned b = blockIdx.x;
-    if (b < nbw) {
-        k3_wall_node<S>(src, dst, K, (long long)b * B3 + threadIdx.x);
+    const unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const unsigned nb = L.nbw + L.nbi, slab = b / nb, r = b - slab * nb;
+    const unsigned p0 = slab * L.planes, np = min(L.planes, (unsigned)inner_z(K) - p0);   // interior planes p0, ...
+    const unsigned z0 = p0 + (K.pz ? 0 : 1);
+    if (r >= L.nbw) {
+        const unsigned i0 = (r - L.nbw) * B3;
+        if (i0 < np * L.inner) k3_interior<S, XW, NT>(src, dst, K, i0, np * L.inner, (int)z0);
         return;
     }
-    const unsigned bi = b - nbw, plane = bi / nbx, bx = bi - plane * nbx;
-    k3_interior_node<S>(src, dst, K, bx * B3 + threadIdx.x, (int)plane);
+    unsigned i = r * B3 + threadIdx.x;
+    const unsigned nx = (unsigned)K.nx, ny = (unsigned)K.ny;
+    unsigned x, y, z;
+    if (i < np * L.walls) {
+        // the x walls (all their rows), then the y walls' other nodes; XW: the y walls alone
+        const unsigned zi = i / L.walls, xs = XW || K.px ? 0 : 2 * ny, yw = XW ? nx : (unsigned)inner_x(K);
+        i -= zi * L.walls;
+        z = z0 + zi;
+        if (i < xs) {
+            x = i < ny ? 0 : nx - 1;
+            y = i < ny ? i : i - ny;
+        } else {
+            i -= xs;
+            y = i < yw ? 0 : ny - 1;
+            x = (i < yw ? i : i - yw) + (XW || K.px ? 0 : 1);
+        }
+    } else {
+        i = i - np * L.walls;
+        const unsigned pl = nx * ny, zn = K.pz ? 0 : 2 * pl;
+        if (i >= L.zw) return;
+        i += slab * L.zw;
+        if (i >= zn) return;
+        z = i < pl ? 0 : (unsigned)K.nz - 1;
+        i = i < pl ? i : i - pl;
+        y = i / nx;
+        x = i - y * nx;
+    }
+    k3_wall_node<S, NT>(src, dst, K, (int)x, (int)y, (int)z);
 }
 
 // Result area after the two buffers: the reduction's value and the number of its blocks that
@@ -604,7 +844,7 @@ __global__ void __launch_bounds__(B3) k3_init(S *__restrict__ dst, K3 K, const d
         f[q] = feq<double>(q, K, e, 0.0, u, S0);
         g[q] = geq<double>(q, K, e, T - K.T0, T, 0.0, u, g0);
     }
-    store<S, double>(dst, K, (unsigned)k, f, g);
+    store<S, true, double>(dst, K, (unsigned)k, f, g);
 }
 
 // Fixed-order sum of one value per thread over the block, returned to thread 0.
@@ -863,6 +1103,29 @@ lbm_status make_constants(const lbm3_params *p, K3 &K)
 
 unsigned blocks_for(long long n) { return (unsigned)((n + B3 - 1) / B3); }
 
+// Whether the runs of consecutive interior nodes (whole planes, or whole rows between y walls)
+// start and end on 128-byte lines.
+template <typename S> bool lines_whole(const K3 &K)
+{
+    return K.px && (long long)K.nx * (K.py ? K.ny : 1) * (long long)sizeof(S) % 128 == 0;
+}
+
+bool x_walls_inside(const K3 &K) { return !K.px && inner_x(K) >= XW_ROW; }
+
+Slabs slabs_of(const K3 &K)
+{
+    Slabs L;
+    const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, nz = (unsigned)inner_z(K);
+    L.inner = (unsigned)inner_x(K) * (unsigned)inner_y(K);
+    L.walls = x_walls_inside(K) ? (K.py ? 0 : 2 * (unsigned)K.nx) : pl - L.inner;
+    L.planes = std::min(nz, std::max(1u, (SLAB_NODES + L.inner - 1) / L.inner));
+    L.count = (nz + L.planes - 1) / L.planes;
+    L.zw = K.pz ? 0 : (unsigned)((2LL * pl + L.count - 1) / L.count);
+    L.nbw = blocks_for((long long)L.walls * L.planes + L.zw);
+    L.nbi = blocks_for((long long)L.inner * L.planes);
+    return L;
+}
+
 lbm_status launched(const char *what)
 {
     const hipError_t e = hipGetLastError();
@@ -920,19 +1183,16 @@ lbm_status lbm3_step(lbm3_ctx *c, int64_t nsteps)
 {
     if (!c) return fail3(LBM_ERR_INVALID, "ctx is NULL");
     if (nsteps < 0) return fail3(LBM_ERR_INVALID, "nsteps must be >= 0");
-    const K3 &K = c->K;
-    const long long n_plane = (long long)inner_x(K) * inner_y(K), n_w = K.n - n_plane * inner_z(K);
-    const unsigned nbx = n_plane > 0 ? blocks_for(n_plane) : 0, nbw = blocks_for(n_w);
-    const long long nb = (long long)nbw + (long long)nbx * (n_plane > 0 ? inner_z(K) : 0);
-    if (nb > 0x7fffffff) return fail3(LBM_ERR_INVALID, "grid too large for one launch");
+    const Slabs L = slabs_of(c->K);
+    const unsigned nb = L.count * (L.nbw + L.nbi);
     for (int64_t s = 0; s < nsteps; ++s) {
         by_storage(c->storage, [&](auto t) {
             using S = typename decltype(t)::type;
             const S *src = reinterpret_cast<const S *>(c->buf[c->cur]);
             S *dst = reinterpret_cast<S *>(c->buf[c->cur ^ 1]);
-            if (nb > 0)
-                hipLaunchKernelGGL((k3_step<S>), dim3((unsigned)nb), dim3(B3), 0, c->stream, src, dst, c->K, nbw,
-                                   nbx > 0 ? nbx : 1u);
+            const auto k = x_walls_inside(c->K) ? &k3_step<S, true, false>
+                         : (lines_whole<S>(c->K) ? &k3_step<S, false, true> : &k3_step<S, false, false>);
+            hipLaunchKernelGGL(k, dim3(nb), dim3(B3), 0, c->stream, src, dst, c->K, L);
         });
         c->cur ^= 1;
         c->t += 1;

@@ -14,6 +14,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "lbm_xcd.h"
+
 // Population layout per storage type: rows of tiles of T consecutive nodes, each tile
 // holding its 18 directions contiguously, [y][x / T][q][x % T], so that the 36 streams of a
 // wavefront touch one contiguous block of memory per row instead of 36 distant planes.
@@ -773,17 +775,6 @@ __device__ __forceinline__ void wall_populations(const S *__restrict__ src, cons
     R Tdff = R(0);
     if (thermal_dirichlet_wall(P, w) < 0) Tdff = gather_Td<S, R>(src, P, k, x + 2 * w.dx, y + 2 * w.dy);
     wall_from_ref<R, PRE>(P, k, x, y, eps_at<R>(P, x + w.dx, y + w.dy), eps_at<R>(P, x, y), ff, gf, Tdff, f, g, mb);
-}
-
-// Logical block of dispatched block b out of nb: blocks are dealt round-robin to the eight
-// XCDs, each with its own L2; this hands every XCD one contiguous range of logical blocks,
-// so that the neighbouring wavefronts whose halo columns and rows overlap share an L2.
-__device__ __forceinline__ int xcd_block(int b, int nb)
-{
-    constexpr int X = 8;
-    const int per = nb / X, rem = nb % X;
-    const int x = b % X, i = b / X;
-    return x * per + min(x, rem) + i;
 }
 
 // Wall-node slot s -> (x, y); returns false for slots that are not wall nodes of this
