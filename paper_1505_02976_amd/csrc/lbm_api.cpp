@@ -337,6 +337,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
         if (e != hipSuccess) { delete c; return hip_fail(e, "two-step wavefront lists"); }
     }
     e = hipMemsetAsync(c->ws + lay.off_b, 0, lay.pop_bytes, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws + lay.off_scalar, 0, 256, c->stream);
     if (e == hipSuccess)
         e = lbm::launch_init(params->storage, cur_buf(c), c->kp, params->T_init, params->p_init,
                              params->ux_init, params->uy_init, c->stream);
@@ -658,6 +659,9 @@ lbm_status lbm_gradients(lbm_ctx *c, int32_t out_dtype, void *Sxx, void *Sxy, vo
     return fields(c, out_dtype, o);
 }
 
+// Count of finished blocks of the reductions: zero between launches (set by lbm_init).
+static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>(c->ws + c->lay.off_scalar + 200); }
+
 static lbm_status check_nusselt_wall(const lbm_ctx *c, int32_t wall)
 {
     if (wall < 0 || wall > 3) return fail(LBM_ERR_INVALID, "wall must be 0..3");
@@ -676,7 +680,9 @@ lbm_status lbm_nusselt(lbm_ctx *c, int32_t wall, double *nu_host)
     const lbm_status chk = check_nusselt_wall(c, wall);
     if (chk != LBM_OK) return chk;
     double *dev = reinterpret_cast<double *>(c->ws + c->lay.off_scalar);
-    hipError_t e = lbm::launch_nusselt(c->prm.storage, cur_buf(c), c->kp, wall, c->d.L, c->d.dT, dev, c->stream);
+    double *part = reinterpret_cast<double *>(c->ws + c->lay.off_part);
+    hipError_t e = lbm::launch_nusselt(c->prm.storage, cur_buf(c), c->kp, wall, c->d.L, c->d.dT, part, done_of(c), dev,
+                                       c->stream);
     if (e != hipSuccess) return hip_fail(e, "nusselt launch");
     e = hipMemcpyAsync(nu_host, dev, sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

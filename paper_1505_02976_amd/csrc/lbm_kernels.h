@@ -53,7 +53,7 @@ hipError_t launch_fields(int storage, const void *src, const KParams &P, void *c
 hipError_t launch_residual(int storage, const void *src, const KParams &P, double *snap,
                            double *partial, double *out, hipStream_t st);
 hipError_t launch_nusselt(int storage, const void *src, const KParams &P, int wall, double L,
-                          double dT, double *out, hipStream_t st);
+                          double dT, double *partial, unsigned *done, double *out, hipStream_t st);
 hipError_t launch_state(int storage, void *buf, const KParams &P, double *io, bool get, hipStream_t st);
 // *flag |= 1 if some population of the grid is NaN or infinite (flag cleared by the caller).
 hipError_t launch_check(int storage, const void *buf, const KParams &P, int *flag, hipStream_t st);

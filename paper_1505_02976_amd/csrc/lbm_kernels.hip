@@ -7,6 +7,8 @@
 // [y][x / T][q][x % T].  A step reads buffer src and writes buffer dst; node (x, y) pulls
 // f_i from (x - c_i) and stores its post-collision populations at (x, y), so no two threads
 // write the same element and no thread reads what another thread writes in the same launch.
+#include <algorithm>
+
 #include "lbm_kernels.h"
 
 namespace lbm {
@@ -14,6 +16,7 @@ namespace lbm {
 constexpr int BULK_BX = 256;
 constexpr int WALL_B = 64;
 constexpr int RED_B = 256;
+constexpr int RESID_BLOCKS = 2048;   // eight per CU
 
 // ---------------------------------------------------------------------------------
 // Initialisation: post-collision populations before the first step are the equilibria
@@ -315,129 +318,171 @@ __device__ __forceinline__ void write_fields(const FieldOut &o, const KParams &P
     }
 }
 
+// Node threadIdx.x of logical block b, numbered along the rows of the grid (32-bit arithmetic but
+// for the block's first node on grids of 2^32 nodes and more).
+__device__ __forceinline__ bool node_of(const KParams &P, long long b, int &x, int &y)
+{
+    const unsigned long long i0 = (unsigned long long)b * blockDim.x;
+    const unsigned nx = (unsigned)P.nx;
+    unsigned y0, x0;
+    if (i0 >> 32) {
+        y0 = (unsigned)(i0 / nx);
+        x0 = (unsigned)(i0 - (unsigned long long)y0 * nx);
+    } else {
+        y0 = (unsigned)i0 / nx;
+        x0 = (unsigned)i0 - y0 * nx;
+    }
+    const unsigned c = x0 + threadIdx.x, r = c / nx;
+    x = (int)(c - r * nx);
+    y = (int)(y0 + r);
+    return y < P.ny;
+}
+
+// Populations and state of any node: every node gathers at its x_f (the node itself off the
+// walls), a wall node goes on with the state the boundary scheme assigns to it.
+template <typename S, typename R>
+__device__ __forceinline__ void node_any(const S *__restrict__ src, const KParams &P, int x, int y, R *f, R *g, Macro<R> &m)
+{
+    const WallInfo w = wall_info(P, x, y);
+    const Cst<R> &k = make_cst<R>(P);
+    gather<S, R>(src, P, x + w.dx, y + w.dy, f, g);
+    const EpsC<R> ef = eps_at<R>(P, x + w.dx, y + w.dy);
+    node_macro_full<R>(f, g, R(P.T0), k, ef, m);
+    if (w.xw < 0 && w.yw < 0) return;
+    R Tdff = R(0);
+    if (thermal_dirichlet_wall(P, w) < 0) Tdff = gather_Td<S, R>(src, P, k, x + 2 * w.dx, y + 2 * w.dy);
+    const Macro<R> mf = m;
+    wall_from_state<R>(R(P.T0), k, wall_consts<R>(P, w), ef, eps_at<R>(P, x, y), mf, f, g, Tdff, f, g, m);
+}
+
+// All nodes in one launch: a launch of their own for the wall nodes costs as much as the
+// interior's on small grids (moments and gradients of 4 x 64 FP64 43 -> 35 us a call, of
+// 600 x 700 FP64 58 -> 51, of 4096 x 4096 FP32 598 -> 580, which is bound by memory).
 template <typename S, typename R>
 __global__ void __launch_bounds__(BULK_BX)
-k_fields_bulk(const S *__restrict__ src, KParams P, FieldOut o)
+k_fields(const S *__restrict__ src, KParams P, FieldOut o)
 {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
-    if (x >= P.nx || on_wall(P, x, y)) return;
+    int x, y;
+    if (!node_of(P, (long long)blockIdx.y * gridDim.x + blockIdx.x, x, y)) return;
     using M = typename Prec<S>::M;
     M f[9], g[9];
-    gather<S, M>(src, P, x, y, f, g);
     Macro<M> m;
-    node_macro_full<M>(f, g, M(P.T0), make_cst<M>(P), eps_at<M>(P, x, y), m);
+    node_any<S, M>(src, P, x, y, f, g, m);
     write_fields<M>(o, P, x, y, m);
 }
 
-template <typename S, typename R>
-__global__ void __launch_bounds__(WALL_B)
-k_fields_wall(const S *__restrict__ src, KParams P, FieldOut o)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    int x, y;
-    if (s >= P.nwall || !wall_slot(P, s, x, y)) return;
-    using M = typename Prec<S>::M;
-    M f[9], g[9];
-    Macro<M> mb;   // a wall node's fields are the state the boundary scheme assigns
-    wall_populations<S, M>(src, P, make_cst<M>(P), x, y, f, g, mb);
-    write_fields<M>(o, P, x, y, mb);
-}
-
 // ---------------------------------------------------------------------------------
-// Residual against a snapshot (FP64, fixed-order reduction) and non-finite detection.
-// Each block writes 5 partial sums: |du|_2, |u|_2, |dT|, |T|, count of non-finite.
+// Reductions of V values per thread: fixed order over the block, then over the blocks by the
+// block that finishes last (the order does not depend on which one that is).  *done counts the
+// finished blocks and is zero between launches.
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ void block_sum5(double v[5], double *out)
+template <int V>
+__device__ __forceinline__ void block_sum(double v[V], double (*sm)[RED_B])
 {
-    __shared__ double sm[5][RED_B];
     const int t = threadIdx.x;
 #pragma unroll
-    for (int q = 0; q < 5; ++q) sm[q][t] = v[q];
+    for (int q = 0; q < V; ++q) sm[q][t] = v[q];
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+    for (int s = RED_B / 2; s > 0; s >>= 1) {
         if (t < s) {
 #pragma unroll
-            for (int q = 0; q < 5; ++q) sm[q][t] += sm[q][t + s];
+            for (int q = 0; q < V; ++q) sm[q][t] += sm[q][t + s];
         }
         __syncthreads();
     }
-    if (t < 5) out[t] = sm[t][0];
 }
 
-template <typename R>
-__device__ __forceinline__ void resid_node(const KParams &P, int x, int y, const R *f, const R *g,
-                                           const Macro<R> &m, double *snap, double v[5])
+// Sum over all threads of the grid: true in the block that finishes last, with the totals in
+// sm[q][0].  partial holds V values per block.
+template <int V>
+__device__ __forceinline__ bool grid_sum(double v[V], double (*sm)[RED_B], double *partial, unsigned *done)
 {
-    const long long n = (long long)y * P.nx + x;
-    const long long N = (long long)P.nx * P.ny;
-    bool bad = false;
+    const int t = threadIdx.x;
+    block_sum<V>(v, sm);
+    if (gridDim.x == 1) return true;
+    __shared__ bool last;
+    if (t < V)
+        __hip_atomic_store(partial + V * (long long)blockIdx.x + t, sm[t][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (t == 0)
+        last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return false;
+    if (t == 0) *done = 0;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) bad |= !isfinite(double(f[i])) || !isfinite(double(g[i]));
-    const double ux = double(m.ux), uy = double(m.uy), T = P.T0 + double(m.Td);
-    bad |= !isfinite(ux) || !isfinite(uy) || !isfinite(T);
-    const double dux = ux - snap[n], duy = uy - snap[N + n];
-    v[0] = sqrt(dux * dux + duy * duy);
-    v[1] = sqrt(ux * ux + uy * uy);
-    v[2] = fabs(T - snap[2 * N + n]);
-    v[3] = fabs(T);
-    v[4] = bad ? 1.0 : 0.0;
-    snap[n] = ux;
-    snap[N + n] = uy;
-    snap[2 * N + n] = T;
+    for (int q = 0; q < V; ++q) v[q] = 0.0;
+    for (unsigned b = t; b < gridDim.x; b += RED_B)
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+            v[q] += __hip_atomic_load(partial + V * (long long)b + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    block_sum<V>(v, sm);
+    return true;
 }
 
+// ---------------------------------------------------------------------------------
+// Residual against a snapshot (FP64) and non-finite detection: five sums, |du|_2, |u|_2, |dT|,
+// |T|, count of non-finite.
+// ---------------------------------------------------------------------------------
+// One launch over all nodes, at most RESID_BLOCKS blocks that each take every gridDim.x-th run
+// of RED_B nodes (dx, dy: that stride in columns and rows).  The pass is bound by memory; the
+// bounded number of blocks keeps the sum over them (a second launch) short.  Against one block
+// per RED_B nodes and another launch for the wall nodes a call takes 25 instead of 35 us
+// (4 x 64 FP64), 30 instead of 38 (250 x 250 FP32), 87 instead of 102 (1537 x 1025 FP64), 500
+// instead of 540 (4096 x 4096 FP32); 1024 to 4096 blocks differ by 2 %.  Adding up in the block
+// that finishes last (as k_nusselt does over its few blocks) is slower here: every block's
+// release flushes the snapshot it has just written out of the L2, 50 us over 1640 blocks.
 template <typename S, typename R>
 __global__ void __launch_bounds__(RED_B)
-k_resid_bulk(const S *__restrict__ src, KParams P, double *snap, double *partial)
+k_resid(const S *__restrict__ src, KParams P, int dx, int dy, double *snap, double *partial)
 {
-    // 1-D over nodes so that every block has a fixed slot in the partial array
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    double v[5] = {0, 0, 0, 0, 0};
-    if (idx < (long long)P.nx * P.ny) {
-        const int x = int(idx % P.nx), y = int(idx / P.nx);
-        if (!on_wall(P, x, y)) {
-            using M = typename Prec<S>::M;
-            M f[9], g[9];
-            gather<S, M>(src, P, x, y, f, g);
-            Macro<M> m;
-            node_macro_full<M>(f, g, M(P.T0), make_cst<M>(P), eps_at<M>(P, x, y), m);
-            resid_node<M>(P, x, y, f, g, m, snap, v);
-        }
-    }
-    block_sum5(v, partial + 5 * (long long)blockIdx.x);
-}
-
-template <typename S, typename R>
-__global__ void __launch_bounds__(RED_B)
-k_resid_wall(const S *__restrict__ src, KParams P, double *snap, double *partial)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    using M = typename Prec<S>::M;
+    __shared__ double sm[5][RED_B];
+    const long long N = (long long)P.nx * P.ny;
     double v[5] = {0, 0, 0, 0, 0};
     int x, y;
-    if (s < P.nwall && wall_slot(P, s, x, y)) {
-        using M = typename Prec<S>::M;
+    for (bool in = node_of(P, blockIdx.x, x, y); in; in = y < P.ny) {
+        double *const sn = snap + (long long)y * P.nx + x;
+        const double sx = sn[0], sy = sn[N], sT = sn[2 * N];
         M f[9], g[9];
-        Macro<M> mb;
-        wall_populations<S, M>(src, P, make_cst<M>(P), x, y, f, g, mb);
-        resid_node<M>(P, x, y, f, g, mb, snap, v);
+        Macro<M> m;
+        node_any<S, M>(src, P, x, y, f, g, m);
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) bad |= !isfinite(double(f[i])) || !isfinite(double(g[i]));
+        const double ux = double(m.ux), uy = double(m.uy), T = P.T0 + double(m.Td);
+        bad |= !isfinite(ux) || !isfinite(uy) || !isfinite(T);
+        const double dux = ux - sx, duy = uy - sy;
+        v[0] += sqrt(dux * dux + duy * duy);
+        v[1] += sqrt(ux * ux + uy * uy);
+        v[2] += fabs(T - sT);
+        v[3] += fabs(T);
+        v[4] += bad ? 1.0 : 0.0;
+        sn[0] = ux;
+        sn[N] = uy;
+        sn[2 * N] = T;
+        x += dx;
+        y += dy;
+        if (x >= P.nx) { x -= P.nx; ++y; }
     }
-    block_sum5(v, partial + 5 * (long long)blockIdx.x);
+    block_sum<5>(v, sm);
+    if (threadIdx.x < 5) partial[5 * (long long)blockIdx.x + threadIdx.x] = sm[threadIdx.x][0];
 }
 
 // Sums nparts partial 5-vectors in a fixed order (one block).
 __global__ void __launch_bounds__(RED_B) k_sum_partials(const double *partial, int nparts, double *out)
 {
+    __shared__ double sm[5][RED_B];
     double v[5] = {0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nparts; b += blockDim.x)
+    for (int b = threadIdx.x; b < nparts; b += RED_B)
 #pragma unroll
         for (int q = 0; q < 5; ++q) v[q] += partial[5 * (long long)b + q];
-    block_sum5(v, out);
+    block_sum<5>(v, sm);
+    if (threadIdx.x < 5) out[threadIdx.x] = sm[threadIdx.x][0];
 }
 
 // ---------------------------------------------------------------------------------
 // Nusselt number (Eq. AvNuss): T on the three node layers next to a wall, one-sided
-// second-order derivative, trapezoid rule; FP64, fixed-order reduction in one block.
+// second-order derivative, trapezoid rule; FP64, fixed-order reduction.
 // ---------------------------------------------------------------------------------
 template <typename S, typename R>
 __device__ __forceinline__ double node_Td_interior(const S *__restrict__ src, const KParams &P,
@@ -470,28 +515,34 @@ __device__ __forceinline__ double node_Td(const S *__restrict__ src, const KPara
     return (4.0 * Tdf - Tdff - 2.0 * dn) / 3.0;
 }
 
+// One thread per node of the three layers, NUS_J wall nodes per block: a call is one latency,
+// the loads of one node (of two on a prescribed-gradient wall).  With one block whose threads
+// took the three nodes one after the other and walked the wall a call took 31 us (128 x 128
+// FP64) and 108 us (4096 x 4096 FP32), now 26 and 28.
+constexpr int NUS_J = RED_B / 3;
+
 template <typename S, typename R>
 __global__ void __launch_bounds__(RED_B)
-k_nusselt(const S *__restrict__ src, KParams P, int wall, double L, double dT, double *out)
+k_nusselt(const S *__restrict__ src, KParams P, int wall, double L, double dT, double *partial, unsigned *done, double *out)
 {
     using M = typename Prec<S>::M;
-    const Cst<M> &k = make_cst<M>(P);
-    const int along = (wall < 2) ? P.ny : P.nx;
-    double acc = 0.0;
-    for (int j = threadIdx.x; j < along; j += blockDim.x) {
-        double t0, t1, t2, sgn;
-        if (wall == 0) { t0 = node_Td<S, M>(src, P, k, 0, j); t1 = node_Td<S, M>(src, P, k, 1, j); t2 = node_Td<S, M>(src, P, k, 2, j); sgn = 1.0; }
-        else if (wall == 1) { t0 = node_Td<S, M>(src, P, k, P.nx - 1, j); t1 = node_Td<S, M>(src, P, k, P.nx - 2, j); t2 = node_Td<S, M>(src, P, k, P.nx - 3, j); sgn = -1.0; }
-        else if (wall == 2) { t0 = node_Td<S, M>(src, P, k, j, 0); t1 = node_Td<S, M>(src, P, k, j, 1); t2 = node_Td<S, M>(src, P, k, j, 2); sgn = 1.0; }
-        else { t0 = node_Td<S, M>(src, P, k, j, P.ny - 1); t1 = node_Td<S, M>(src, P, k, j, P.ny - 2); t2 = node_Td<S, M>(src, P, k, j, P.ny - 3); sgn = -1.0; }
-        const double d = sgn * (-3.0 * t0 + 4.0 * t1 - t2) * 0.5;
-        const double nu = -L * d / dT;
-        acc += (j == 0 || j == along - 1) ? 0.5 * nu : nu;
+    __shared__ double sm[1][RED_B];
+    __shared__ double T[3][NUS_J];
+    const int along = wall < 2 ? P.ny : P.nx;
+    const int layer = threadIdx.x / NUS_J, jj = threadIdx.x - layer * NUS_J, j = blockIdx.x * NUS_J + jj;
+    if (layer < 3 && j < along) {
+        const int in = wall & 1 ? (wall < 2 ? P.nx : P.ny) - 1 - layer : layer;
+        T[layer][jj] = node_Td<S, M>(src, P, make_cst<M>(P), wall < 2 ? in : j, wall < 2 ? j : in);
     }
-    double v[5] = {acc, 0, 0, 0, 0};
-    __shared__ double res[5];
-    block_sum5(v, res);
-    if (threadIdx.x == 0) out[0] = res[0] / double(along - 1);
+    __syncthreads();
+    double v[1] = {0.0};
+    if (layer == 0 && j < along) {
+        const double sgn = wall & 1 ? -1.0 : 1.0;
+        const double d = sgn * (-3.0 * T[0][jj] + 4.0 * T[1][jj] - T[2][jj]) * 0.5;
+        const double nu = -L * d / dT;
+        v[0] = (j == 0 || j == along - 1) ? 0.5 * nu : nu;
+    }
+    if (grid_sum<1>(v, sm, partial, done) && threadIdx.x == 0) out[0] = sm[0][0] / double(along - 1);
 }
 
 // ---------------------------------------------------------------------------------
@@ -533,7 +584,6 @@ k_set_state(S *__restrict__ dst, KParams P, const double *__restrict__ in)
 // Launchers
 // ---------------------------------------------------------------------------------
 static dim3 bulk_grid(const KParams &P) { return dim3((P.nx + BULK_BX - 1) / BULK_BX, P.ny); }
-static int wall_blocks(const KParams &P, int b) { return (P.nwall + b - 1) / b; }
 
 template <typename S, typename R>
 static hipError_t launch_init_t(void *dst, const KParams &P, const double *T, const double *p,
@@ -590,10 +640,10 @@ static hipError_t launch_fields_t(const void *src, const KParams &P, void *const
     FieldOut o;
     for (int q = 0; q < 9; ++q) o.ptr[q] = out[q];
     o.f32 = f32;
-    hipLaunchKernelGGL((k_fields_bulk<S, R>), bulk_grid(P), dim3(BULK_BX), 0, st, (const S *)src, P, o);
-    if (P.nwall > 0)
-        hipLaunchKernelGGL((k_fields_wall<S, R>), dim3(wall_blocks(P, WALL_B)), dim3(WALL_B), 0, st,
-                           (const S *)src, P, o);
+    // two grid dimensions: one holds fewer than 2^32 threads
+    const long long nb = ((long long)P.nx * P.ny + BULK_BX - 1) / BULK_BX, nx = std::min(nb, 1LL << 22);
+    hipLaunchKernelGGL((k_fields<S, R>), dim3((unsigned)nx, (unsigned)((nb + nx - 1) / nx)), dim3(BULK_BX), 0, st,
+                       (const S *)src, P, o);
     return hipGetLastError();
 }
 
@@ -602,21 +652,21 @@ static hipError_t launch_resid_t(const void *src, const KParams &P, double *snap
                                  double *out, hipStream_t st)
 {
     const long long N = (long long)P.nx * P.ny;
-    const int nb = int((N + RED_B - 1) / RED_B);
-    const int nw = P.nwall > 0 ? wall_blocks(P, RED_B) : 0;
-    hipLaunchKernelGGL((k_resid_bulk<S, R>), dim3(nb), dim3(RED_B), 0, st, (const S *)src, P, snap, partial);
-    if (nw > 0)
-        hipLaunchKernelGGL((k_resid_wall<S, R>), dim3(nw), dim3(RED_B), 0, st, (const S *)src, P, snap,
-                           partial + 5 * (long long)nb);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(RED_B), 0, st, (const double *)partial, nb + nw, out);
+    const int nb = (int)std::min<long long>((N + RED_B - 1) / RED_B, RESID_BLOCKS);
+    const long long stride = (long long)nb * RED_B;
+    hipLaunchKernelGGL((k_resid<S, R>), dim3(nb), dim3(RED_B), 0, st, (const S *)src, P, (int)(stride % P.nx),
+                       (int)(stride / P.nx), snap, partial);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(RED_B), 0, st, (const double *)partial, nb, out);
     return hipGetLastError();
 }
 
 template <typename S, typename R>
 static hipError_t launch_nusselt_t(const void *src, const KParams &P, int wall, double L, double dT,
-                                   double *out, hipStream_t st)
+                                   double *partial, unsigned *done, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_nusselt<S, R>), dim3(1), dim3(RED_B), 0, st, (const S *)src, P, wall, L, dT, out);
+    const int along = wall < 2 ? P.ny : P.nx;
+    hipLaunchKernelGGL((k_nusselt<S, R>), dim3((along + NUS_J - 1) / NUS_J), dim3(RED_B), 0, st, (const S *)src, P, wall,
+                       L, dT, partial, done, out);
     return hipGetLastError();
 }
 
@@ -705,11 +755,11 @@ hipError_t launch_residual(int storage, const void *src, const KParams &P, doubl
 }
 
 hipError_t launch_nusselt(int storage, const void *src, const KParams &P, int wall, double L,
-                          double dT, double *out, hipStream_t st)
+                          double dT, double *partial, unsigned *done, double *out, hipStream_t st)
 {
-    LBM_DISPATCH(storage, (launch_nusselt_t<double, double>(src, P, wall, L, dT, out, st)),
-                 (launch_nusselt_t<float, float>(src, P, wall, L, dT, out, st)),
-                 (launch_nusselt_t<__half, float>(src, P, wall, L, dT, out, st)))
+    LBM_DISPATCH(storage, (launch_nusselt_t<double, double>(src, P, wall, L, dT, partial, done, out, st)),
+                 (launch_nusselt_t<float, float>(src, P, wall, L, dT, partial, done, out, st)),
+                 (launch_nusselt_t<__half, float>(src, P, wall, L, dT, partial, done, out, st)))
 }
 
 hipError_t launch_check(int storage, const void *buf, const KParams &P, int *flag, hipStream_t st)
