@@ -1327,9 +1327,13 @@ hipError_t batch_single(lbm_batch *b)
 hipError_t batch_tiles(lbm_batch *b, int ns)
 {
     int threads = 0;
-    for (const auto &h : b->hp) threads = std::max(threads, lbm::tile_threads(h.tile, ns));
-    const hipError_t e = lbm::launch_batch_tile(b->storage, b->probs, b->tile_items, b->ntiles, b->any_field, threads,
-                                                b->cur, ns, b->stream);
+    long long nodes = 0;
+    for (const auto &h : b->hp) {
+        threads = std::max(threads, lbm::tile_threads(h.tile, ns));
+        nodes += (long long)h.P.nx * h.P.ny;
+    }
+    const hipError_t e = lbm::launch_batch_tile(b->storage, b->probs, b->tile_items, b->ntiles, b->any_field, nodes,
+                                                threads, b->cur, ns, b->stream);
     if (e == hipSuccess) {
         b->t += ns;
         b->cur ^= 1;

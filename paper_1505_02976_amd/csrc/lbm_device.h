@@ -267,20 +267,41 @@ template <typename R> __device__ __forceinline__ EpsC<R> eps_uniform(const KPara
 
 // Coefficients at porosity eps: F_eps from the Ergun relation or as given, c0 and c1 of the
 // velocity solve, the drag coefficients of Eq. ForceEq and b = (1/eps - 1/sigma)/2 of Eq. MatrM.
-template <typename R> __device__ __forceinline__ EpsC<R> eps_coeffs(const KParams &P, double eps)
+// EpsK holds what takes a division or a square root; the rest follows from it.
+template <typename R> struct EpsK {
+    double eps, c1;
+    R ieps, bM;
+};
+
+template <typename R> __device__ __forceinline__ EpsK<R> eps_keep(const KParams &P, double eps)
 {
     const double ie = 1.0 / eps;
     const double Fe = P.ergun ? 1.75 / sqrt(150.0 * eps * eps * eps) : P.Feps;
-    EpsC<R> e;
-    e.epsd = eps;
-    e.eps = R(eps);
-    e.ieps = R(ie);
-    e.c0 = 0.5 * (1.0 + 0.5 * eps * P.nu_over_K);
+    EpsK<R> e;
+    e.eps = eps;
     e.c1 = 0.5 * eps * Fe * P.inv_sqrtK;
-    e.dlin = R(eps * P.nu_over_K);
-    e.dquad = R(eps * Fe * P.inv_sqrtK);
+    e.ieps = R(ie);
     e.bM = R(0.5 * (ie - P.cd.isig));   // isig = 1 / sigma, rounded once on the host
     return e;
+}
+
+template <typename R> __device__ __forceinline__ EpsC<R> eps_from(double nu_over_K, const EpsK<R> &h)
+{
+    EpsC<R> e;
+    e.epsd = h.eps;
+    e.eps = R(h.eps);
+    e.ieps = h.ieps;
+    e.c0 = 0.5 * (1.0 + 0.5 * h.eps * nu_over_K);
+    e.c1 = h.c1;
+    e.dlin = R(h.eps * nu_over_K);
+    e.dquad = R(2.0 * h.c1);            // eps F_eps / sqrt(K), the factor 2 being exact
+    e.bM = h.bM;
+    return e;
+}
+
+template <typename R> __device__ __forceinline__ EpsC<R> eps_coeffs(const KParams &P, double eps)
+{
+    return eps_from<R>(P.nu_over_K, eps_keep<R>(P, eps));
 }
 
 __device__ __forceinline__ double eps_value(const KParams &P, int x, int y)

@@ -21,10 +21,12 @@
 // whose halos share cache lines, share an L2: without it a 250 x 250 FP32 launch of one step
 // took 10.1 us instead of 6.7.
 //
-// Measured (one step, 100-step calls, two-step passes before): 128 x 128 FP64 27 -> 2.6 us,
-// 250 x 250 FP32 22 -> 3.0 us, 512 x 512 FP32 25 -> 7.5 us, 1300 x 1300 FP32 43 -> 34 us; a
+// Measured (one step, 100-step calls, two-step passes before): 128 x 128 FP64 27 -> 2.8 us,
+// 250 x 250 FP32 22 -> 3.1 us, 500 x 500 FP32 25 -> 7.3 us, 1350 x 1350 FP32 45 -> 36 us; a
 // grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
+#include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "lbm_tile.h"
 
@@ -61,10 +63,19 @@ __device__ __forceinline__ TileRegion tile_region(const KParams &P, const TileGr
     return t;
 }
 
+// The coefficients at a node's porosity for one step.  AGAIN: formed in every step from the few
+// that EpsK keeps (three operations), where registers are short; held across the steps otherwise
+// (the adjoint's forward states at 256 x 256 FP32: 3 % faster).
+template <bool AGAIN, typename R> __device__ __forceinline__ EpsC<R> eps_step(KConst pc, EpsK<R> &h)
+{
+    if (AGAIN) asm volatile("" : "+v"(h.eps), "+v"(h.c1));
+    return eps_from<R>(pc->nu_over_K, h);
+}
+
 // ns steps of one tile.  lds: 18 planes of TILE_NT values, [q][node of the region].  WALLS: the
 // region holds wall nodes.  WRAP: it spans the grid along a periodic direction (wx, wy),
 // whose pulls wrap inside it.  hist != 0: every step s is stored, at dst + (s - 1) hist.
-template <typename S, bool FIELD, bool WALLS, bool WRAP>
+template <typename S, bool FIELD, bool DENSE, bool WALLS, bool WRAP>
 __device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restrict__ dst, const KParams &P,
                                            KConst Pc, const TileRegion &t, bool wx, bool wy, int ns, long long hist,
                                            S *__restrict__ lds)
@@ -99,17 +110,23 @@ __device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restr
     const int lxr = lx + w.dx, lyr = ly + w.dy;
     const int cm = WRAP && wx && lxr == 0 ? rw - 1 : -1, cp = WRAP && wx && lxr == rw - 1 ? 1 - rw : 1;
     const int rm = WRAP && wy && lyr == 0 ? (rh - 1) * rw : -rw, rp = WRAP && wy && lyr == rh - 1 ? (1 - rh) * rw : rw;
-    EpsC<R> er, eo;                                       // at the pulled node, at the node itself
+    EpsK<R> hr, ho;                                       // at the pulled node, at the node itself
+    constexpr bool TAB = DENSE && WALLS;
+    __shared__ WallC<R> wtab[TAB ? 9 : 1];                // of the four walls and the four corners
+    const int wi = TAB ? (w.dx + 1) + 3 * (w.dy + 1) : 0;
     WallC<R> wc = {};
+    bool neumann = false;
     R f[9], g[9], Tdff = R(0);
     if (last > 0) {
-        if (FIELD) er = eo = eps_at<R>(P, xr, yr);
+        if (FIELD) hr = ho = eps_keep<R>(P, eps_value(P, xr, yr));
         if (wall) {
             wc = wall_consts<R>(P, w);
-            if (FIELD) eo = eps_at<R>(P, x, y);
+            if (TAB) wtab[wi] = wc;
+            neumann = !wc.iso;
+            if (FIELD) ho = eps_keep<R>(P, eps_value(P, x, y));
         }
     }
-    const bool neumann = wall && !wc.iso;
+    if (TAB) __syncthreads();
     if (last > 0) {
         gather<S, R>(src, P, xr, yr, f, g);
         if (neumann) Tdff = gather_Td<S, R>(src, P, cst<R>(P), x + 2 * w.dx, y + 2 * w.dy);
@@ -122,13 +139,25 @@ __device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restr
         load_consts(pc, k);
         const R T0 = R(pc->T0);
         const float hinv = pc->hinv, hscale = pc->hscale;
-        if (!FIELD) { load_eps(pc, er); eo = er; }
+        EpsC<R> er, eo;
+        if (FIELD) {
+            er = eps_step<DENSE, R>(pc, hr);
+            eo = WALLS ? eps_step<DENSE, R>(pc, ho) : er;
+        } else {
+            load_eps(pc, er);
+            eo = er;
+        }
         if (s <= last) {
             Macro<R> m;
             node_macro_full<R>(f, g, T0, k, er, m);
             if (wall) {
                 Macro<R> mb;
+                if (TAB) {
+                    wc = wtab[wi];
+                    __builtin_amdgcn_sched_barrier(0);    // not ahead of the state, which fills the registers
+                }
                 wall_from_state<R>(T0, k, wc, er, eo, m, f, g, Tdff, f, g, mb);
+                if (TAB) __builtin_amdgcn_sched_barrier(0);
                 m = mb;
             }
             node_collide<R>(f, g, m, T0, k, WALLS ? eo : er);
@@ -162,39 +191,53 @@ __device__ __forceinline__ void tile_steps(const S *__restrict__ src, S *__restr
     }
 }
 
-template <typename S, bool FIELD>
+template <typename S, bool FIELD, bool DENSE>
 __device__ __forceinline__ void tile_block(const S *__restrict__ src, S *__restrict__ dst, const KParams &P, KConst Pc,
                                            const TileGrid &g, int b, int ns, long long hist, S *__restrict__ lds)
 {
     const TileRegion t = tile_region(P, g, b, ns);
     const bool wx = P.px && g.nbx == 1, wy = P.py && g.nby == 1;
-    if (wx || wy) tile_steps<S, FIELD, true, true>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
-    else if (t.walls) tile_steps<S, FIELD, true, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
-    else tile_steps<S, FIELD, false, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+    if (wx || wy) tile_steps<S, FIELD, DENSE, true, true>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+    else if (t.walls) tile_steps<S, FIELD, DENSE, true, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
+    else tile_steps<S, FIELD, DENSE, false, false>(src, dst, P, Pc, t, wx, wy, ns, hist, lds);
 }
 
+// Wavefronts per SIMD that the kernels leave room for: four, except in FP64 off the dense
+// variant, whose wall tiles hold up to 226 registers.  FP32 and FP16 with a porosity field took 138
+// without the bound and ran three: 300 x 300 FP32 5.0 us per step against 4.0, 700 x 800 FP16 19.0
+// against 15.5.
+template <typename S, bool DENSE> struct TileWaves { static constexpr int v = sizeof(S) != 8 || DENSE ? 4 : 1; };
+
 // P is the third parameter: it starts 16 bytes into the kernel's parameter segment.
-template <typename S, bool FIELD>
-__global__ void __launch_bounds__(TILE_NT)
+template <typename S, bool FIELD, bool DENSE>
+__global__ void __launch_bounds__(TILE_NT, (TileWaves<S, DENSE>::v))
 k_tile(const S *__restrict__ src, S *__restrict__ dst, KParams P, TileGrid g, int ns, long long hist)
 {
     __shared__ S lds[18 * TILE_NT];
     const KConst Pc = (KConst)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + 16);
-    tile_block<S, FIELD>(src, dst, P, Pc, g, xcd_block(blockIdx.x, gridDim.x), ns, hist, lds);
+    tile_block<S, FIELD, DENSE>(src, dst, P, Pc, g, xcd_block(blockIdx.x, gridDim.x), ns, hist, lds);
 }
 
 // Batched: item (problem, tile).  FIELD: some problem has a porosity field.  The item, and
 // with it the problem's parameters, are wavefront-uniform.
-template <typename S, bool FIELD>
-__global__ void __launch_bounds__(TILE_NT)
+template <typename S, bool FIELD, bool DENSE>
+__global__ void __launch_bounds__(TILE_NT, (TileWaves<S, DENSE>::v))
 k_batch_tile(const BatchProblem *__restrict__ probs, const int2 *__restrict__ items, int parity, int ns)
 {
     __shared__ S lds[18 * TILE_NT];
     const int2 it = items[xcd_block(blockIdx.x, gridDim.x)];
     const BatchProblem &B = probs[__builtin_amdgcn_readfirstlane(it.x)];
-    tile_block<S, FIELD>(static_cast<const S *>(B.buf[parity]), static_cast<S *>(B.buf[parity ^ 1]), B.P,
-                         (KConst)&B.P, B.tile, __builtin_amdgcn_readfirstlane(it.y), ns, 0, lds);
+    tile_block<S, FIELD, DENSE>(static_cast<const S *>(B.buf[parity]), static_cast<S *>(B.buf[parity ^ 1]), B.P,
+                                (KConst)&B.P, B.tile, __builtin_amdgcn_readfirstlane(it.y), ns, 0, lds);
 }
+
+// The dense variant (DENSE, FP64) fits four wavefronts per SIMD instead of two: its wall tiles
+// spill and read the wall constants from LDS when they need them, which other blocks hide once
+// there are several rounds of them.  us per step without and with it: 1025 x 1025 45.4 and 37.1,
+// 1200 x 1100 55.2 and 44.9, 1537 x 1025 with a porosity field 66 and 57; but 800 x 700 with a field
+// 24.5 and 24.8, 600 x 500 17.5 and 21.2, 128 x 128 2.82 and 3.0.
+constexpr long long TILE_DENSE = 700000;
+static bool tile_dense(int storage, long long nodes) { return storage == 0 && nodes >= TILE_DENSE; }
 
 // Largest region of a launch of ns steps: its width and height.
 static void tile_extent(const TileGrid &g, int ns, int &w, int &h)
@@ -208,10 +251,10 @@ static hipError_t tile_t(const void *src, void *dst, const KParams &P, const Til
                          hipStream_t st)
 {
     const dim3 grid(g.nbx * g.nby), block(tile_threads(g, ns));
-    if (P.field)
-        hipLaunchKernelGGL((k_tile<S, true>), grid, block, 0, st, (const S *)src, (S *)dst, P, g, ns, hist);
-    else
-        hipLaunchKernelGGL((k_tile<S, false>), grid, block, 0, st, (const S *)src, (S *)dst, P, g, ns, hist);
+    const auto dense = P.field ? &k_tile<S, true, sizeof(S) == 8> : &k_tile<S, false, sizeof(S) == 8>;
+    const auto sparse = P.field ? &k_tile<S, true, false> : &k_tile<S, false, false>;
+    const auto k = tile_dense(sizeof(S) == 8 ? 0 : 1, (long long)P.nx * P.ny) ? dense : sparse;
+    hipLaunchKernelGGL(k, grid, block, 0, st, (const S *)src, (S *)dst, P, g, ns, hist);
     return hipGetLastError();
 }
 
@@ -228,23 +271,23 @@ hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P
 }
 
 template <typename S>
-static hipError_t batch_tile_t(const BatchProblem *probs, const int2 *items, int nitems, bool field, int threads,
-                               int parity, int ns, hipStream_t st)
+static hipError_t batch_tile_t(const BatchProblem *probs, const int2 *items, int nitems, bool field, long long nodes,
+                               int threads, int parity, int ns, hipStream_t st)
 {
-    if (field)
-        hipLaunchKernelGGL((k_batch_tile<S, true>), dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
-    else
-        hipLaunchKernelGGL((k_batch_tile<S, false>), dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
+    const auto dense = field ? &k_batch_tile<S, true, sizeof(S) == 8> : &k_batch_tile<S, false, sizeof(S) == 8>;
+    const auto sparse = field ? &k_batch_tile<S, true, false> : &k_batch_tile<S, false, false>;
+    const auto k = tile_dense(sizeof(S) == 8 ? 0 : 1, nodes) ? dense : sparse;
+    hipLaunchKernelGGL(k, dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
-                             int threads, int parity, int ns, hipStream_t st)
+                             long long nodes, int threads, int parity, int ns, hipStream_t st)
 {
     switch (storage) {
-    case 0: return batch_tile_t<double>(probs, items, nitems, field, threads, parity, ns, st);
-    case 1: return batch_tile_t<float>(probs, items, nitems, field, threads, parity, ns, st);
-    case 2: return batch_tile_t<__half>(probs, items, nitems, field, threads, parity, ns, st);
+    case 0: return batch_tile_t<double>(probs, items, nitems, field, nodes, threads, parity, ns, st);
+    case 1: return batch_tile_t<float>(probs, items, nitems, field, nodes, threads, parity, ns, st);
+    case 2: return batch_tile_t<__half>(probs, items, nitems, field, nodes, threads, parity, ns, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -260,54 +303,78 @@ hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 
 // every node update that a SIMD issues for a wavefront.  Over 875 measured combinations on
 // nine grids from 48 x 90 to 1300 x 1201 nodes the choice costs 3 % (FP64, FP16) and 5 % (FP32)
 // more on average than the best one.
+// It knows nothing of the memory system, which decides once the blocks come in rounds: regions of
+// 32 columns read whole lines, and more steps per launch read less.  From TILE_WIDE[0] nodes on
+// (grids several tiles across) it chooses between two such tiles, from TILE_WIDE[1] nodes on the
+// better one is fixed per type.  us per step with the estimate's choice of all shapes and with
+// these: FP32 380^2 6.4 and 4.4, 600^2 15.2 and 9.8, 1200^2 41.6 and 30.2, 1500^2 64 and 46.8 (the
+// two-step pass 51.5); FP64 850^2 36.7 and 26.8; FP16 1300^2 35.8 and 32.2; of (28, 12) in 3 and (26, 10) in 4
+// steps, FP32 1000^2 23.1 and 21.4, FP64 700^2 21.2 and 23.3, 1400^2 68.3 and 63.1, FP16 1000^2 20.2
+// and 23.2.
 //
-// More than TILE_NODES nodes take the two-step pass (FP16: single steps), which is bound by
-// HBM and recomputes less: FP32 1536^2 46 us per step here against 53, 2048^2 102 against 79;
-// FP64 1024^2 45 against 53, 1300 x 1201 65 against 63; FP16 1300 x 1201 30 against 35, 2048^2 73
-// against 68.  With a porosity field, whose coefficients a tile forms once per launch, FP64
-// gains up to 1537 x 1025 (66 against 74).  A batch's grids are narrower, which costs the
-// other ways more: cavities of 64-300 nodes a side, us per step here and there: FP64 1.19 M nodes
-// 59 and 63, 2.13 M 125 and 129, 2.38 M 118 and 108; FP32 2.38 M 59 and 89, 4.0 M 102 and 103-120,
-// 5.1 M 193 and 135; FP16 1.19 M 29 and 47, 5.1 M 117 and 145, sides of 64-512 with 25.6 M nodes 513
-// and 562.
+// Larger grids (TILE_NODES) take the two-step pass (FP16: single steps), which is bound by
+// HBM and recomputes less.  us per step here and there: FP32 1800 x 1900 66 and 67, 2500^2 120 and
+// 113; FP64 1300^2 53 and 65, 1700^2 91 and 98, 2400^2 177-184 and 182, 3000^2 275 and 276; FP16 1500^2 41
+// and 44, 2000^2 75 and 71.  With a porosity field, whose coefficients a tile forms once per launch,
+// FP32 2000 x 2100 90 and 102, 3500^2 259 and 264; FP64 2000^2 135 and 153, 3500^2 399 and 419; FP16 2500^2
+// 120 and 122.  Batches: FP64 cavities of 180-300 nodes a side, 3.7 M in all, 150 and 156, 8.6 M 354 and
+// 346; FP32 5 M 122 and 125, 8.6 M 213 and 213, 25.6 M 567 and 534; FP16 10.6 M 268 and 270.
 constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
-constexpr long long TILE_NODES[3] = {1400000, 2500000, 2000000}, TILE_NODES_FIELD = 2000000;
-constexpr long long TILE_NODES_BATCH[2] = {2000000, 4000000};   // FP16: the mean grid at most TILE_NODES
+constexpr long long TILE_WIDE[2] = {120000, 350000};
+constexpr int TILE_ACROSS = 48;                   // shorter sides: any shape
+constexpr long long TILE_NODES[3] = {5000000, 3500000, 2300000};
+constexpr long long TILE_NODES_FIELD[3] = {12500000, 12500000, 6500000};
+constexpr long long TILE_NODES_BATCH[2] = {4000000, 6000000};   // FP16: the mean grid at most TILE_MEAN
+constexpr long long TILE_MEAN = 2000000;
 
 static long long tile_nodes_limit(int storage, int n, bool field)
 {
-    if (n > 1) return storage == 2 ? n * TILE_NODES[2] : TILE_NODES_BATCH[storage];
-    return storage == 0 && field ? TILE_NODES_FIELD : TILE_NODES[storage];
+    if (n > 1) return storage == 2 ? n * TILE_MEAN : TILE_NODES_BATCH[storage];
+    return field ? TILE_NODES_FIELD[storage] : TILE_NODES[storage];
+}
+
+struct TileShape { int tw, th, ns0, ns1; };       // tile and the range of steps per launch
+
+// The shapes that tile_plan chooses from, for grids of `nodes` nodes together.
+static std::vector<TileShape> tile_shapes(int storage, long long nodes, bool narrow)
+{
+    const TileShape wide = {28, 12, 3, 3}, deep = {26, 10, 4, 4};
+    if (!narrow && nodes >= TILE_WIDE[1]) return {storage == 1 || tile_dense(storage, nodes) ? deep : wide};
+    if (!narrow && nodes >= TILE_WIDE[0]) return {wide, deep};
+    std::vector<TileShape> v;
+    static const int all[][2] = {{8, 8}, {12, 8}, {16, 8}, {32, 8}, {12, 12}, {16, 12}, {16, 16},
+                                 {20, 20}, {28, 12}, {26, 10}, {30, 14}};
+    for (const auto &sh : all) v.push_back({sh[0], sh[1], 1, TILE_MAX_STEPS});
+    return v;
 }
 
 int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
 {
     long long nodes = 0;
-    bool field = true, one_block = true;
+    bool field = true, one_block = true, narrow = false;
     for (int k = 0; k < n; ++k) {
         const long long nk = (long long)P[k].nx * P[k].ny;
         nodes += nk;
         field = field && P[k].field;
         one_block = one_block && nk <= TILE_NT;
+        narrow = narrow || std::min(P[k].nx, P[k].ny) < TILE_ACROSS;
     }
     if (nodes > tile_nodes_limit(storage, n, field)) return 0;
     if (one_block) {
         for (int k = 0; k < n; ++k) grids[k] = tile_grid(P[k], P[k].nx, P[k].ny);
         return TILE_ALL_STEPS;
     }
-    static const int shapes[][2] = {{8, 8}, {12, 8}, {16, 8}, {32, 8}, {12, 12}, {16, 12}, {16, 16},
-                                    {20, 20}, {28, 12}, {26, 10}, {30, 14}};
     const int resident = storage == 0 ? 8 : 16;   // wavefronts of this kernel that a CU's registers hold
     const double cus = 256.0;
-    const int *shape = nullptr;
+    TileShape shape = {};
     int best = 0;
     double cost = 0.0;
-    for (const auto &sh : shapes) {
-        for (int ns = 1; ns <= TILE_MAX_STEPS; ++ns) {
+    for (const TileShape &sh : tile_shapes(storage, nodes, narrow)) {
+        for (int ns = sh.ns0; ns <= sh.ns1; ++ns) {
             double blocks = 0.0, updates = 0.0;   // over all grids: blocks; node updates of a wavefront
             int waves = 0;                        // of the largest block
             for (int k = 0; k < n && waves >= 0; ++k) {
-                const TileGrid g = tile_grid(P[k], sh[0], sh[1]);
+                const TileGrid g = tile_grid(P[k], sh.tw, sh.th);
                 int w, h;
                 tile_extent(g, ns, w, h);
                 if ((g.nbx > 1 && g.tw < 4) || (g.nby > 1 && g.th < 4) || w * h > TILE_NT) {
@@ -333,7 +400,7 @@ int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
             }
         }
     }
-    for (int k = 0; k < n && best; ++k) grids[k] = tile_grid(P[k], shape[0], shape[1]);
+    for (int k = 0; k < n && best; ++k) grids[k] = tile_grid(P[k], shape.tw, shape.th);
     return best;
 }
 
