@@ -560,7 +560,7 @@ __device__ __forceinline__ void store(S *__restrict__ dst, const K3 &K, unsigned
 }
 
 constexpr int B3 = 256;
-constexpr unsigned SLAB_NODES = 4096;
+constexpr unsigned SLAB_NODES = 2048;      // interior nodes of a slab, at least (whole planes)
 
 // Extent of the interior along x, y and z: all nodes of a periodic direction, all but the two
 // wall nodes of a walled one.
@@ -759,16 +759,20 @@ __device__ __forceinline__ void k3_wall_node(const S *__restrict__ src, S *__res
 }
 
 // One time step in one launch.  Where every wavefront writes whole cache lines (NT), stores
-// are non-temporal and blocks run in the dispatched order: 192 x 192 x 96 FP32 199 us a step
-// (5.4 TB/s; 210 us with plain stores, 215 in the order of the XCDs).  Elsewhere rows begin and
+// are non-temporal and blocks run in the dispatched order: 192 x 192 x 96 FP32 195 us a step
+// (5.5 TB/s; 6 % more with plain stores, 8 % more in the order of the XCDs).  Elsewhere rows begin and
 // end inside cache lines whose other part another block writes: a plain store lets the L2 join
 // the two and the order of the XCDs puts neighbouring blocks on one L2, 121 x 95 x 83 with
 // porosity per node 68 -> 43 us (FP16), 97 -> 73 (FP32), 178 -> 162 (FP64), 185 x 171 x 90
-// periodic in x and y 268 -> 201 (FP32).  Registers are held to the
-// interior's own count (FP32/FP16 five waves per SIMD, FP64 three): the spills are in the wall
-// blocks.
+// periodic in x and y 268 -> 201 (FP32).
+// Wavefronts per SIMD: as many as leave nothing to spill (FP64 204 registers, FP32 114); one more, with the wall blocks' spills,
+// takes longer also where the step is bound by memory: 192 x 192 x 96 FP64 416 against 401 us,
+// FP32 199 against 195, the FP64 box 162 against 146, 120 x 4 x 120 FP64 11.8 against 10.7.  FP16
+// runs five with 10 spilled registers: 42 us against 44 with four, 75 with six.
+template <typename S> struct StepWaves { static constexpr int v = sizeof(S) == 8 ? 2 : (sizeof(S) == 4 ? 4 : 5); };
+
 template <typename S, bool XW, bool NT>
-__global__ void __launch_bounds__(B3, sizeof(S) == 8 ? 3 : 5)
+__global__ void __launch_bounds__(B3, (StepWaves<S>::v))
 k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, Slabs L)
 {
     const unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
