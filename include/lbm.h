@@ -131,7 +131,9 @@ size_t lbm_workspace_bytes(const lbm_params *params);
  * lbm_workspace_bytes(params) bytes, 256-byte aligned, owned by the caller and kept alive
  * until lbm_destroy; the library owns its contents.  hip_stream: a hipStream_t (NULL =
  * default stream).  Enqueues the initialisation.  *out receives a context that the
- * caller releases with lbm_destroy. */
+ * caller releases with lbm_destroy.  The first context of a process (lbm3_init as well) allocates
+ * 64 KiB of pinned host memory, held until the process ends, through which up to 1024 contexts
+ * return the values of lbm_residual and lbm_nusselt; further ones copy them from the device. */
 lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_bytes,
                     void *hip_stream, lbm_ctx **out);
 

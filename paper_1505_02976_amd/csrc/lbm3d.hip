@@ -19,6 +19,7 @@
 
 #include "../../include/lbm3d.h"
 #include "lbm_error.h"
+#include "lbm_hostslot.h"
 #include "lbm_xcd.h"
 
 namespace lbm3 {
@@ -876,7 +877,7 @@ __device__ __forceinline__ double block_sum(double v, double *part)
 // Each block leaves its sum in part[], the block that finishes last adds those in
 // a fixed order: the FP64 result does not depend on which one that is.
 template <typename S>
-__global__ void __launch_bounds__(B3) k3_nusselt(const S *__restrict__ src, K3 K, int w, double *part, Result3 *out)
+__global__ void __launch_bounds__(B3) k3_nusselt(const S *__restrict__ src, K3 K, int w, double *part, Result3 *res, double *out)
 {
     using R = typename Arith<S>::R;
     __shared__ double sh[B3];
@@ -912,7 +913,7 @@ __global__ void __launch_bounds__(B3) k3_nusselt(const S *__restrict__ src, K3 K
     v = block_sum(v, sh);
     if (threadIdx.x == 0) {
         __hip_atomic_store(part + blockIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = __hip_atomic_fetch_add(&out->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        last = __hip_atomic_fetch_add(&res->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();
     if (!last) return;
@@ -921,8 +922,8 @@ __global__ void __launch_bounds__(B3) k3_nusselt(const S *__restrict__ src, K3 K
         v += __hip_atomic_load(part + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     v = block_sum(v, sh);
     if (threadIdx.x == 0) {
-        out->value = v / (double(p0 ? n0 : n0 - 1) * double(p1 ? n1 : n1 - 1));
-        out->done = 0;
+        *out = v / (double(p0 ? n0 : n0 - 1) * double(p1 ? n1 : n1 - 1));
+        res->done = 0;
     }
 }
 
@@ -976,6 +977,7 @@ struct lbm3_ctx {
     int storage;
     char *buf[2];
     Result3 *result;
+    double *host;                  // pinned slot for the reduction's value, or NULL
     int cur;
     hipStream_t stream;
     int64_t t;
@@ -1179,6 +1181,7 @@ lbm_status lbm3_init(const lbm3_params *params, void *workspace, size_t workspac
         if (e != hipSuccess) st = fail3(LBM_ERR_DEVICE, "initial populations: %s", hipGetErrorString(e));
     }
     if (st != LBM_OK) { delete c; return st; }
+    c->host = lbm::host_slot_take();
     *out = c;
     return LBM_OK;
 }
@@ -1239,15 +1242,18 @@ lbm_status lbm3_nusselt(lbm3_ctx *c, int32_t wall, double *nu_host)
     const K3 &K = c->K;
     const long long cells = K.n / (wall < 2 ? K.nz : (wall < 4 ? K.nx : K.ny));
     double *part = reinterpret_cast<double *>(c->buf[c->cur ^ 1]);
+    double *out = c->host ? c->host : &c->result->value;
     by_storage(c->storage, [&](auto t) {
         using S = typename decltype(t)::type;
         hipLaunchKernelGGL((k3_nusselt<S>), dim3(blocks_for(cells)), dim3(B3), 0, c->stream,
-                           reinterpret_cast<const S *>(c->buf[c->cur]), K, (int)wall, part, c->result);
+                           reinterpret_cast<const S *>(c->buf[c->cur]), K, (int)wall, part, c->result, out);
     });
     lbm_status st = launched("3-D Nusselt number");
     if (st != LBM_OK) return st;
-    hipError_t e = hipMemcpyAsync(nu_host, &c->result->value, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    hipError_t e = hipSuccess;
+    if (!c->host) e = hipMemcpyAsync(nu_host, out, sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess && c->host) *nu_host = *out;
     if (e != hipSuccess) return fail3(LBM_ERR_DEVICE, "3-D Nusselt number: %s", hipGetErrorString(e));
     return LBM_OK;
 }
@@ -1267,6 +1273,7 @@ void lbm3_destroy(lbm3_ctx *c)
 {
     if (!c) return;
     (void)hipStreamSynchronize(c->stream);
+    lbm::host_slot_give(c->host);
     delete c;
 }
 

@@ -12,6 +12,7 @@
 
 #include "../../include/lbm.h"
 #include "lbm_error.h"
+#include "lbm_hostslot.h"
 #include "lbm_kernels.h"
 
 namespace {
@@ -213,6 +214,7 @@ struct lbm_ctx {
     hipStream_t stream;
     int64_t t;
     int have_snap;
+    double *host;        // pinned slot for the results of the reductions, or NULL
     int device;
     int in_batch;
     int cur;             // buffer holding the current populations (0: a, 1: b)
@@ -299,6 +301,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
     c->check_every = 0;
     c->side = nullptr;
     c->ev_join = c->ev_main = c->ev_side = nullptr;
+    c->host = nullptr;
     if (hipGetDevice(&c->device) != hipSuccess) c->device = -1;
     // the address of this device's static scratch array (lbm_residual_noalloc), once per
     // device; a failure here surfaces only in that entry point
@@ -342,6 +345,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
         e = lbm::launch_init(params->storage, cur_buf(c), c->kp, params->T_init, params->p_init,
                              params->ux_init, params->uy_init, c->stream);
     if (e != hipSuccess) { delete c; return hip_fail(e, "initialisation"); }
+    c->host = lbm::host_slot_take();
     *out = c;
     return LBM_OK;
 }
@@ -662,6 +666,17 @@ lbm_status lbm_gradients(lbm_ctx *c, int32_t out_dtype, void *Sxx, void *Sxy, vo
 // Count of finished blocks of the reductions: zero between launches (set by lbm_init).
 static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>(c->ws + c->lay.off_scalar + 200); }
 
+// The n results that a launch on the context's stream leaves at dev (its pinned slot, or device
+// memory), once the stream is done.
+static hipError_t read_back(lbm_ctx *c, double *dst, const double *dev, int n)
+{
+    hipError_t e = hipSuccess;
+    if (dev != c->host) e = hipMemcpyAsync(dst, dev, n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess && dev == c->host) std::copy(dev, dev + n, dst);
+    return e;
+}
+
 static lbm_status check_nusselt_wall(const lbm_ctx *c, int32_t wall)
 {
     if (wall < 0 || wall > 3) return fail(LBM_ERR_INVALID, "wall must be 0..3");
@@ -679,13 +694,12 @@ lbm_status lbm_nusselt(lbm_ctx *c, int32_t wall, double *nu_host)
     if (!nu_host) return fail(LBM_ERR_INVALID, "nu_host is NULL");
     const lbm_status chk = check_nusselt_wall(c, wall);
     if (chk != LBM_OK) return chk;
-    double *dev = reinterpret_cast<double *>(c->ws + c->lay.off_scalar);
+    double *dev = c->host ? c->host : reinterpret_cast<double *>(c->ws + c->lay.off_scalar);
     double *part = reinterpret_cast<double *>(c->ws + c->lay.off_part);
     hipError_t e = lbm::launch_nusselt(c->prm.storage, cur_buf(c), c->kp, wall, c->d.L, c->d.dT, part, done_of(c), dev,
                                        c->stream);
     if (e != hipSuccess) return hip_fail(e, "nusselt launch");
-    e = hipMemcpyAsync(nu_host, dev, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    e = read_back(c, nu_host, dev, 1);
     if (e != hipSuccess) return hip_fail(e, "nusselt");
     if (!std::isfinite(*nu_host)) return fail(LBM_ERR_NONFINITE, "Nusselt number is not finite");
     return LBM_OK;
@@ -696,11 +710,11 @@ lbm_status lbm_nusselt(lbm_ctx *c, int32_t wall, double *nu_host)
 static lbm_status residual_into(lbm_ctx *c, double *part, double *res, double *r_u, double *r_T)
 {
     double *snap = reinterpret_cast<double *>(c->ws + c->lay.off_snap);
+    if (c->host) res = c->host;
     hipError_t e = lbm::launch_residual(c->prm.storage, cur_buf(c), c->kp, snap, part, res, c->stream);
     if (e != hipSuccess) return hip_fail(e, "residual launch");
     double h[5];
-    e = hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    e = read_back(c, h, res, 5);
     if (e != hipSuccess) return hip_fail(e, "residual");
     const bool first = !c->have_snap;
     c->have_snap = 1;
@@ -764,6 +778,7 @@ static void release_ctx(lbm_ctx *c)
     if (c->ev_main) (void)hipEventDestroy(c->ev_main);
     if (c->ev_side) (void)hipEventDestroy(c->ev_side);
     destroy_step_events(c->tev);
+    lbm::host_slot_give(c->host);
     delete c;
 }
 

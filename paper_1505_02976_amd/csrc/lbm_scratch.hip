@@ -5,8 +5,10 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <vector>
 
 #include "../../include/lbm.h"
+#include "lbm_hostslot.h"
 #include "lbm_kernels.h"
 
 namespace lbm {
@@ -44,6 +46,39 @@ void *static_scratch(int device)
     if (device < 0 || device >= MAX_DEVICES) return nullptr;
     std::lock_guard<std::mutex> guard(g_lock);
     return g_looked_up[device] ? g_addr[device] : nullptr;
+}
+
+namespace {
+
+std::mutex g_slot_lock;
+bool g_slot_tried;
+std::vector<double *> g_slot_free;
+
+}  // namespace
+
+double *host_slot_take()
+{
+    std::lock_guard<std::mutex> guard(g_slot_lock);
+    if (!g_slot_tried) {
+        g_slot_tried = true;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, (size_t)HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            for (int i = HOST_SLOTS - 1; i >= 0; --i)
+                g_slot_free.push_back(reinterpret_cast<double *>(static_cast<char *>(p) + (size_t)i * HOST_SLOT_BYTES));
+        else
+            (void)hipGetLastError();
+    }
+    if (g_slot_free.empty()) return nullptr;
+    double *s = g_slot_free.back();
+    g_slot_free.pop_back();
+    return s;
+}
+
+void host_slot_give(double *s)
+{
+    if (!s) return;
+    std::lock_guard<std::mutex> guard(g_slot_lock);
+    g_slot_free.push_back(s);
 }
 
 }  // namespace lbm
