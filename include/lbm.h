@@ -146,8 +146,8 @@ lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_
  * context's stream and, on a second stream created by the library (default priority,
  * ordered with the caller's stream by events), the launches next to the walled rows.  A
  * single step is two launches: the interior columns, then the columns next to the walls
- * x = 0, x = nx - 1 together with the walled rows.  Grids up to about 1.4 (FP64), 2.5 (FP32)
- * and 2 (FP16) million nodes run, until lbm_set_fusion is called, as launches of several
+ * x = 0, x = nx - 1 together with the walled rows.  Grids up to about 5 (FP64), 3.5 (FP32)
+ * and 2.3 (FP16) million nodes (with a porosity field 12.5, 12.5 and 6.5) run, until lbm_set_fusion is called, as launches of several
  * steps (up to 8, any number on a grid of at most 512 nodes) whose blocks keep a tile of the
  * grid in LDS; the results are again bitwise those of single steps. */
 lbm_status lbm_step(lbm_ctx *ctx, int64_t nsteps);
@@ -253,7 +253,7 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
  * stream of the batch beside its main launch, ordered by events; the call is ordered like
  * launches on the batch's stream), then one single step if nsteps is odd.  With one step
  * per pass: whole HIP graphs of 64 steps (built on the first call that needs one), then
- * single steps.  Batches of up to about 2 (FP64) and 4 (FP32) million nodes, and FP16 batches of
+ * single steps.  Batches of up to about 4 (FP64) and 6 (FP32) million nodes, and FP16 batches of
  * grids of up to about 2 million each on average, run, until lbm_batch_set_fusion or
  * lbm_batch_set_width is called, as launches of several steps on tiles, as lbm_step's small grids
  * do.  Results are bitwise those of lbm_step on each problem alone.  Asynchronous. */
