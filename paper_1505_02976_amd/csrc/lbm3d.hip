@@ -770,10 +770,11 @@ __device__ __forceinline__ void k3_wall_node(const S *__restrict__ src, S *__res
 // the two and the order of the XCDs puts neighbouring blocks on one L2, 121 x 95 x 83 with
 // porosity per node 68 -> 43 us (FP16), 97 -> 73 (FP32), 178 -> 162 (FP64), 185 x 171 x 90
 // periodic in x and y 268 -> 201 (FP32).
-// Wavefronts per SIMD: as many as leave nothing to spill (FP64 204 registers, FP32 114); one more, with the wall blocks' spills,
-// takes longer also where the step is bound by memory: 192 x 192 x 96 FP64 416 against 401 us,
-// FP32 199 against 195, the FP64 box 162 against 146, 120 x 4 x 120 FP64 11.8 against 10.7.  FP16
-// runs five with 10 spilled registers: 42 us against 44 with four, 75 with six.
+// Wavefronts per SIMD: as many as leave nothing to spill (FP64 204 registers, FP32 105); one
+// more, with the wall blocks' spills, takes longer also where the step is bound by memory:
+// 192 x 192 x 96 FP64 416 against 401 us, FP32 199 against 195, the FP64 box 162 against 146,
+// 120 x 4 x 120 FP64 11.8 against 10.7.  FP16 runs five with 10 spilled registers: 42 us against
+// 44 with four, 75 with six.
 template <typename S> struct StepWaves { static constexpr int v = sizeof(S) == 8 ? 2 : (sizeof(S) == 4 ? 4 : 5); };
 
 template <typename S, bool XW, bool NT>
