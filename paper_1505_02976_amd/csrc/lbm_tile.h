@@ -55,10 +55,14 @@ inline TileGrid tile_grid(const KParams &P, int tw, int th)
     return g;
 }
 
-// Row of tiles that tile b belongs to (b / nbx).
-__device__ __forceinline__ int tile_row(const TileGrid &g, int b)
+// Row of tiles that tile b belongs to (b / nbx).  magic exceeds 2^32 / nbx by at most 1, so the
+// product is b / nbx plus less than 1/2: its whole part is the row or, in the last tiles of rows
+// of more than 65,000 tiles, the next one.
+__host__ __device__ __forceinline__ int tile_row(const TileGrid &g, int b)
 {
-    return g.nbx == 1 ? b : (int)(((unsigned long long)(unsigned)b * g.magic) >> 32);
+    if (g.nbx == 1) return b;
+    const unsigned q = (unsigned)(((unsigned long long)(unsigned)b * g.magic) >> 32);
+    return (int)(q * (unsigned)g.nbx > (unsigned)b ? q - 1 : q);
 }
 
 }  // namespace lbm
