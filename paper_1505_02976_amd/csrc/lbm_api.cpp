@@ -982,7 +982,7 @@ struct lbm_batch {
     int2 *tile_items;           // (problem, tile) of the launches of several steps
     int ntiles;
     int tile_steps;             // their steps per launch (0: passes), until lbm_batch_set_fusion is called
-    bool any_field;             // some problem has a porosity field
+    int fields;                 // which problems have a porosity field (FIELDS_NONE, ...)
     hipGraph_t graph;           // one-step mode: GRAPH_STEPS steps replayed as one graph
     hipGraphExec_t exec;
     int graph_steps;
@@ -1254,7 +1254,6 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
     b->ev_join = b->ev_main = b->ev_side = nullptr;
     b->bx = lbm::batch_width(0);
     b->w2 = lbm::STEP2_WAVES_PER_BLOCK;
-    b->any_field = false;
     b->tile_steps = B.tile_steps;
     b->tile_items = reinterpret_cast<int2 *>(ws + B.off_tiles);
     b->ntiles = (int)B.tiles.size();
@@ -1278,8 +1277,9 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
         hp[k].scr = c->ws + c->lay.off_scr;
         hp[k].tiles_x = B.tiles_x[k];
         hp[k].tile = B.tile[k];
-        b->any_field = b->any_field || c->kp.field;
     }
+    const auto nfield = std::count_if(hp.begin(), hp.end(), [](const lbm::BatchProblem &h) { return h.P.field; });
+    b->fields = nfield == 0 ? lbm::FIELDS_NONE : nfield == n ? lbm::FIELDS_ALL : lbm::FIELDS_SOME;
     b->probs = reinterpret_cast<lbm::BatchProblem *>(ws + B.off_probs);
     b->bulk_items = reinterpret_cast<int2 *>(ws + B.off_bulk);
     b->edge_items = reinterpret_cast<int2 *>(ws + B.off_edge);
@@ -1347,7 +1347,7 @@ hipError_t batch_tiles(lbm_batch *b, int ns)
         threads = std::max(threads, lbm::tile_threads(h.tile, ns));
         nodes += (long long)h.P.nx * h.P.ny;
     }
-    const hipError_t e = lbm::launch_batch_tile(b->storage, b->probs, b->tile_items, b->ntiles, b->any_field, nodes,
+    const hipError_t e = lbm::launch_batch_tile(b->storage, b->probs, b->tile_items, b->ntiles, b->fields, nodes,
                                                 threads, b->cur, ns, b->stream);
     if (e == hipSuccess) {
         b->t += ns;

@@ -122,8 +122,10 @@ int tile_threads(const TileGrid &g, int ns);   // threads of a block of a launch
 // (s - 1) hist of dst.
 hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P, const TileGrid &g, int ns,
                        long long hist, hipStream_t st);
-// Batched: items (problem, tile); nodes: of all problems; threads: the largest of the problems' tile_threads.
-hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
+// Batched: items (problem, tile); fields: which problems have a porosity field; nodes: of all
+// problems; threads: the largest of the problems' tile_threads.
+enum : int { FIELDS_NONE = 0, FIELDS_ALL = 1, FIELDS_SOME = 2 };
+hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, int fields,
                              long long nodes, int threads, int parity, int ns, hipStream_t st);
 
 // Adjoint sweep.  adjoint_plan picks the tiles and returns the steps a launch may take;

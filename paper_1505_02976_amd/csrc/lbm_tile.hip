@@ -218,17 +218,23 @@ k_tile(const S *__restrict__ src, S *__restrict__ dst, KParams P, TileGrid g, in
     tile_block<S, FIELD, DENSE>(src, dst, P, Pc, g, xcd_block(blockIdx.x, gridDim.x), ns, hist, lds);
 }
 
-// Batched: item (problem, tile).  FIELD: some problem has a porosity field.  The item, and
-// with it the problem's parameters, are wavefront-uniform.
-template <typename S, bool FIELD, bool DENSE>
+// Batched: item (problem, tile).  FIELDS: no problem, all, or some have a porosity field.  Those of
+// uniform porosity take the host's coefficients, as alone (the device's of the same porosity differ
+// in the last bit).  The item, and with it the problem's parameters, are wavefront-uniform.
+template <typename S, int FIELDS, bool DENSE>
 __global__ void __launch_bounds__(TILE_NT, (TileWaves<S, DENSE>::v))
 k_batch_tile(const BatchProblem *__restrict__ probs, const int2 *__restrict__ items, int parity, int ns)
 {
     __shared__ S lds[18 * TILE_NT];
     const int2 it = items[xcd_block(blockIdx.x, gridDim.x)];
     const BatchProblem &B = probs[__builtin_amdgcn_readfirstlane(it.x)];
-    tile_block<S, FIELD, DENSE>(static_cast<const S *>(B.buf[parity]), static_cast<S *>(B.buf[parity ^ 1]), B.P,
-                                (KConst)&B.P, B.tile, __builtin_amdgcn_readfirstlane(it.y), ns, 0, lds);
+    const S *const src = static_cast<const S *>(B.buf[parity]);
+    S *const dst = static_cast<S *>(B.buf[parity ^ 1]);
+    const int b = __builtin_amdgcn_readfirstlane(it.y);
+    if (FIELDS == FIELDS_ALL || (FIELDS == FIELDS_SOME && B.P.field))
+        tile_block<S, true, DENSE>(src, dst, B.P, (KConst)&B.P, B.tile, b, ns, 0, lds);
+    else
+        tile_block<S, false, DENSE>(src, dst, B.P, (KConst)&B.P, B.tile, b, ns, 0, lds);
 }
 
 // The dense variant (DENSE, FP64) fits four wavefronts per SIMD instead of two: its wall tiles
@@ -271,23 +277,25 @@ hipError_t launch_tile(int storage, const void *src, void *dst, const KParams &P
 }
 
 template <typename S>
-static hipError_t batch_tile_t(const BatchProblem *probs, const int2 *items, int nitems, bool field, long long nodes,
+static hipError_t batch_tile_t(const BatchProblem *probs, const int2 *items, int nitems, int fields, long long nodes,
                                int threads, int parity, int ns, hipStream_t st)
 {
-    const auto dense = field ? &k_batch_tile<S, true, sizeof(S) == 8> : &k_batch_tile<S, false, sizeof(S) == 8>;
-    const auto sparse = field ? &k_batch_tile<S, true, false> : &k_batch_tile<S, false, false>;
-    const auto k = tile_dense(sizeof(S) == 8 ? 0 : 1, nodes) ? dense : sparse;
+    constexpr bool D = sizeof(S) == 8;
+    const bool d = tile_dense(D ? 0 : 1, nodes);
+    const auto k = fields == FIELDS_NONE ? (d ? &k_batch_tile<S, FIELDS_NONE, D> : &k_batch_tile<S, FIELDS_NONE, false>)
+                 : fields == FIELDS_ALL ? (d ? &k_batch_tile<S, FIELDS_ALL, D> : &k_batch_tile<S, FIELDS_ALL, false>)
+                                        : (d ? &k_batch_tile<S, FIELDS_SOME, D> : &k_batch_tile<S, FIELDS_SOME, false>);
     hipLaunchKernelGGL(k, dim3(nitems), dim3(threads), 0, st, probs, items, parity, ns);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, bool field,
+hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 *items, int nitems, int fields,
                              long long nodes, int threads, int parity, int ns, hipStream_t st)
 {
     switch (storage) {
-    case 0: return batch_tile_t<double>(probs, items, nitems, field, nodes, threads, parity, ns, st);
-    case 1: return batch_tile_t<float>(probs, items, nitems, field, nodes, threads, parity, ns, st);
-    case 2: return batch_tile_t<__half>(probs, items, nitems, field, nodes, threads, parity, ns, st);
+    case 0: return batch_tile_t<double>(probs, items, nitems, fields, nodes, threads, parity, ns, st);
+    case 1: return batch_tile_t<float>(probs, items, nitems, fields, nodes, threads, parity, ns, st);
+    case 2: return batch_tile_t<__half>(probs, items, nitems, fields, nodes, threads, parity, ns, st);
     default: return hipErrorInvalidValue;
     }
 }
