@@ -254,9 +254,9 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
  * launches on the batch's stream), then one single step if nsteps is odd.  With one step
  * per pass: whole HIP graphs of 64 steps (built on the first call that needs one), then
  * single steps.  Batches of up to about 4 (FP64) and 6 (FP32) million nodes, and FP16 batches of
- * grids of up to about 2 million each on average, run, until lbm_batch_set_fusion or
- * lbm_batch_set_width is called, as launches of several steps on tiles, as lbm_step's small grids
- * do.  Results are bitwise those of lbm_step on each problem alone.  Asynchronous. */
+ * grids of up to about 2 million each on average, run, until lbm_batch_set_fusion,
+ * lbm_batch_set_width or lbm_batch_autotune is called, as launches of several steps on tiles, as
+ * lbm_step's small grids do.  Results are bitwise those of lbm_step on each problem alone.  Asynchronous. */
 lbm_status lbm_batch_step(lbm_batch *batch, int64_t nsteps);
 
 /* Time steps per batched pass, 1 or 2 (as lbm_set_fusion, for all problems at once).  The
@@ -276,7 +276,9 @@ lbm_status lbm_batch_check(lbm_batch *batch, int32_t *nonfinite_host);
  * with two steps per pass, the threads per block of the two-step main launch (64, 128 or
  * 256, i.e. 1, 2 or 4 independent wavefronts per block); with one step per pass, the block
  * width along x of the one-step update (64, 128, 256).  Times each candidate, in that
- * order, over `steps` steps and keeps the fastest for later lbm_batch_step calls.  The
+ * order, over `steps` steps and keeps the fastest for later lbm_batch_step calls, which run
+ * those passes from then on (a batch that steps on tiles by default is usually faster there
+ * and has nothing to tune).  The
  * problems' states are unchanged (the timed launches read the current populations and
  * overwrite only the buffers the next step writes anyway) and the results of later steps
  * do not depend on the width.  *width (optional) receives the chosen width; ms_per_step

@@ -981,7 +981,7 @@ struct lbm_batch {
     int nitems2[lbm::STEP2_LAUNCHES], nrows2;
     int2 *tile_items;           // (problem, tile) of the launches of several steps
     int ntiles;
-    int tile_steps;             // their steps per launch (0: passes), until lbm_batch_set_fusion is called
+    int tile_steps;             // their steps per launch (0: passes), until the passes are chosen or tuned
     int fields;                 // which problems have a porosity field (FIELDS_NONE, ...)
     hipGraph_t graph;           // one-step mode: GRAPH_STEPS steps replayed as one graph
     hipGraphExec_t exec;
@@ -1523,6 +1523,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t steps, int32_t *width, doubl
     if (e != hipSuccess) return hip_fail(e, "batch autotune");
     st = two ? batch_set_waves2(b, lbm::batch_width(best) / 64) : batch_set_width(b, lbm::batch_width(best));
     if (st != LBM_OK) return st;
+    b->tile_steps = 0;
     if (width) *width = two ? 64 * b->w2 : b->bx;
     return LBM_OK;
 }

@@ -493,7 +493,8 @@ class Batch:
     def autotune(self, steps: int = 10):
         """Times the candidate block widths (64, 128, 256 threads) of the launches that run
         under the current steps per pass (the two-step main launch, or the one-step update)
-        and keeps the fastest; returns (chosen width, {width: ms per step}).  The problems'
+        and keeps the fastest, which later steps run; returns (chosen width, {width: ms per
+        step}).  A batch that steps on tiles by default is usually faster there.  The problems'
         states are unchanged."""
         w = C.c_int32()
         ms = (C.c_double * 3)()
