@@ -1264,7 +1264,7 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
         lbm_ctx *c = nullptr;
         st = init_ctx(&params[k], ws + B.off[k], workspace_bytes - B.off[k], hip_stream, &c);
         if (st != LBM_OK) {
-            for (lbm_ctx *q : b->ctx) delete q;
+            for (lbm_ctx *q : b->ctx) release_ctx(q);
             delete b;
             return fail(st, "problem %d: %s", k, g_err);
         }
@@ -1316,7 +1316,7 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
     // the layout's host vectors are released on return: wait for the copies
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
-        for (lbm_ctx *q : b->ctx) delete q;
+        for (lbm_ctx *q : b->ctx) release_ctx(q);
         delete b;
         return hip_fail(e, "batch tables");
     }
