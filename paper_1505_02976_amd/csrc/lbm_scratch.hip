@@ -5,7 +5,6 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
-#include <vector>
 
 #include "../../include/lbm.h"
 #include "lbm_hostslot.h"
@@ -50,35 +49,39 @@ void *static_scratch(int device)
 
 namespace {
 
+// Plain arrays: nothing to construct, to run out of or to destroy before the last context.
 std::mutex g_slot_lock;
-bool g_slot_tried;
-std::vector<double *> g_slot_free;
+bool g_slots_made;
+double *g_slot_free[HOST_SLOTS];
+int g_slots_free;
 
 }  // namespace
 
 double *host_slot_take()
 {
     std::lock_guard<std::mutex> guard(g_slot_lock);
-    if (!g_slot_tried) {
-        g_slot_tried = true;
+    if (!g_slots_made) {
+        // the allocation would invalidate a stream capture that is under way elsewhere in the process
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         void *p = nullptr;
-        if (hipHostMalloc(&p, (size_t)HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+        g_slots_made =
+            hipHostMalloc(&p, (size_t)HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess;
+        if (g_slots_made)
             for (int i = HOST_SLOTS - 1; i >= 0; --i)
-                g_slot_free.push_back(reinterpret_cast<double *>(static_cast<char *>(p) + (size_t)i * HOST_SLOT_BYTES));
+                g_slot_free[g_slots_free++] = reinterpret_cast<double *>(static_cast<char *>(p) + (size_t)i * HOST_SLOT_BYTES);
         else
             (void)hipGetLastError();
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
-    if (g_slot_free.empty()) return nullptr;
-    double *s = g_slot_free.back();
-    g_slot_free.pop_back();
-    return s;
+    return g_slots_free > 0 ? g_slot_free[--g_slots_free] : nullptr;
 }
 
 void host_slot_give(double *s)
 {
     if (!s) return;
     std::lock_guard<std::mutex> guard(g_slot_lock);
-    g_slot_free.push_back(s);
+    g_slot_free[g_slots_free++] = s;
 }
 
 }  // namespace lbm

@@ -4,7 +4,8 @@ kernels a call launches, what an error path gives back) that need no GPU.
 
 run(script, tmp_path) runs `script` in a process of its own, in which `calls` is the stand-in (a
 CDLL), `lib` the library, `lbm` its binding, `W` the workloads, and log() returns the names of the
-calls since the last log(): "launch <kernel>", "copy", "set" or "host alloc"."""
+calls since the last log(): "launch <kernel>", "copy", "set" or "host alloc <the thread's capture
+mode>" (0 global, 2 relaxed)."""
 import os
 import subprocess
 import sys
@@ -17,9 +18,11 @@ SOURCE = r"""
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <utility>
 struct dim3 { unsigned x, y, z; };
 static std::string text;
 static int left_copies = -1, left_allocs = -1;      // calls until one fails, -1: none does
+static int mode = 0;
 static dim3 g_grid, g_block;
 static void note(const std::string &s) { text += s + "\n"; }
 static bool failing(int &n) { return n >= 0 && n-- == 0; }
@@ -53,11 +56,13 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *)
 int hipMemsetAsync(void *d, int v, size_t n, void *) { note("set"); memset(d, v, n); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned)
 {
-    note("host alloc");
+    note("host alloc " + std::to_string(mode));
     if (failing(left_allocs)) return 2;
     *p = calloc(1, n);
     return 0;
 }
+int hipThreadExchangeStreamCaptureMode(int *m) { std::swap(*m, mode); return 0; }
+int calls_mode() { return mode; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipGetSymbolAddress(void **p, const void *) { *p = calloc(1, 1 << 22); return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1.0f; return 0; }

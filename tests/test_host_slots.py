@@ -23,6 +23,21 @@ print(failed, free)
 assert failed > 3 and free == 1024, (failed, free)
 """
 
+INIT = r"""
+# a failed allocation is not the last one, and no allocation can disturb a stream capture
+calls.calls_fail_alloc(0)
+for i in range(3):
+    log()
+    s = Sim(W.cavity(12))
+    allocs = [c for c in log() if c.startswith("host alloc")]
+    assert allocs == (["host alloc 2"] if i < 2 else []), (i, allocs)
+    assert calls.calls_mode() == 0
+"""
+
 
 def test_failed_batches_give_their_slots_back(tmp_path):
     run(BATCH, tmp_path)
+
+
+def test_slots_are_allocated_outside_captures_and_tried_again(tmp_path):
+    run(INIT, tmp_path)
