@@ -26,7 +26,6 @@
 // grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "lbm_tile.h"
 
@@ -343,17 +342,18 @@ static long long tile_nodes_limit(int storage, int n, bool field)
 
 struct TileShape { int tw, th, ns0, ns1; };       // tile and the range of steps per launch
 
+struct TileShapes { const TileShape *first; int n; };
+
 // The shapes that tile_plan chooses from, for grids of `nodes` nodes together.
-static std::vector<TileShape> tile_shapes(int storage, long long nodes, bool narrow)
+static TileShapes tile_shapes(int storage, long long nodes, bool narrow)
 {
-    const TileShape wide = {28, 12, 3, 3}, deep = {26, 10, 4, 4};
-    if (!narrow && nodes >= TILE_WIDE[1]) return {storage == 1 || tile_dense(storage, nodes) ? deep : wide};
-    if (!narrow && nodes >= TILE_WIDE[0]) return {wide, deep};
-    std::vector<TileShape> v;
-    static const int all[][2] = {{8, 8}, {12, 8}, {16, 8}, {32, 8}, {12, 12}, {16, 12}, {16, 16},
-                                 {20, 20}, {28, 12}, {26, 10}, {30, 14}};
-    for (const auto &sh : all) v.push_back({sh[0], sh[1], 1, TILE_MAX_STEPS});
-    return v;
+    constexpr int M = TILE_MAX_STEPS;
+    static constexpr TileShape all[] = {{8, 8, 1, M}, {12, 8, 1, M}, {16, 8, 1, M}, {32, 8, 1, M}, {12, 12, 1, M}, {16, 12, 1, M},
+                                        {16, 16, 1, M}, {20, 20, 1, M}, {28, 12, 1, M}, {26, 10, 1, M}, {30, 14, 1, M}};
+    static constexpr TileShape large[] = {{28, 12, 3, 3}, {26, 10, 4, 4}};
+    if (!narrow && nodes >= TILE_WIDE[1]) return {large + (storage == 1 || tile_dense(storage, nodes)), 1};
+    if (!narrow && nodes >= TILE_WIDE[0]) return {large, 2};
+    return {all, (int)(sizeof(all) / sizeof(all[0]))};
 }
 
 int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
@@ -377,7 +377,9 @@ int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
     TileShape shape = {};
     int best = 0;
     double cost = 0.0;
-    for (const TileShape &sh : tile_shapes(storage, nodes, narrow)) {
+    const TileShapes shapes = tile_shapes(storage, nodes, narrow);
+    for (int i = 0; i < shapes.n; ++i) {
+        const TileShape &sh = shapes.first[i];
         for (int ns = sh.ns0; ns <= sh.ns1; ++ns) {
             double blocks = 0.0, updates = 0.0;   // over all grids: blocks; node updates of a wavefront
             int waves = 0;                        // of the largest block

@@ -17,6 +17,7 @@ SOURCE = r"""
 #include <dlfcn.h>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <utility>
 struct dim3 { unsigned x, y, z; };
@@ -24,12 +25,24 @@ static std::string text;
 static int left_copies = -1, left_allocs = -1;      // calls until one fails, -1: none does
 static int mode = 0;
 static dim3 g_grid, g_block;
-static void note(const std::string &s) { text += s + "\n"; }
 static bool failing(int &n) { return n >= 0 && n-- == 0; }
+static int left_news = -1;
+static bool own = false;        // the stand-in's own allocations
+void *operator new(size_t n)
+{
+    void *p = left_news == 0 && !own ? nullptr : malloc(n ? n : 1);
+    if (left_news > 0 && !own) --left_news;
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+static void note(const std::string &s) { text += s + "\n"; }
 #define OK(name) int name() { return 0; }
 extern "C" {
 const char *calls_text() { return text.c_str(); }
 void calls_clear() { text.clear(); }
+void calls_fail_new(int n) { text.reserve(1 << 16); left_news = n; }      // that many succeed, then none (-1: all)
 void calls_fail_copy(int n) { left_copies = n; }
 void calls_fail_alloc(int n) { left_allocs = n; }
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t, void *) { g_grid = g; g_block = b; return 0; }
@@ -37,13 +50,15 @@ int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *s, void **st) { *g = g_g
 int hipLaunchKernel(const void *f, dim3, dim3, void **, size_t, void *)
 {
     Dl_info i;
-    if (!dladdr(f, &i) || !i.dli_sname) { note("launch ?"); return 0; }
+    own = true;
+    if (!dladdr(f, &i) || !i.dli_sname) i.dli_sname = "::?";
     int st;
     char *n = abi::__cxa_demangle(i.dli_sname, nullptr, nullptr, &st);
     const std::string s = st == 0 ? n : i.dli_sname;
     const size_t a = s.rfind("::", s.find('<')) + 2;
     note("launch " + s.substr(a, s.find_first_of("<(", a) - a));
     free(n);
+    own = false;
     return 0;
 }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *)
@@ -56,7 +71,9 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *)
 int hipMemsetAsync(void *d, int v, size_t n, void *) { note("set"); memset(d, v, n); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned)
 {
+    own = true;
     note("host alloc " + std::to_string(mode));
+    own = false;
     if (failing(left_allocs)) return 2;
     *p = calloc(1, n);
     return 0;
