@@ -237,6 +237,9 @@ struct lbm_ctx {
 static void *cur_buf(lbm_ctx *c) { return c->ws + (c->cur ? c->lay.off_b : c->lay.off_a); }
 static void *next_buf(lbm_ctx *c) { return c->ws + (c->cur ? c->lay.off_a : c->lay.off_b); }
 
+// Count of finished blocks of the reductions: zero between launches (set by lbm_init).
+static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>(c->ws + c->lay.off_scalar + 200); }
+
 // nsteps in as few launches of at most `most` steps as it takes, of equal numbers of steps to
 // within one.  f(n) enqueues n steps.
 template <typename F> hipError_t by_launches(int64_t nsteps, int most, F &&f)
@@ -340,10 +343,9 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
         if (e != hipSuccess) { delete c; return hip_fail(e, "two-step wavefront lists"); }
     }
     e = hipMemsetAsync(c->ws + lay.off_b, 0, lay.pop_bytes, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->ws + lay.off_scalar, 0, 256, c->stream);
     if (e == hipSuccess)
         e = lbm::launch_init(params->storage, cur_buf(c), c->kp, params->T_init, params->p_init,
-                             params->ux_init, params->uy_init, c->stream);
+                             params->ux_init, params->uy_init, done_of(c), c->stream);
     if (e != hipSuccess) { delete c; return hip_fail(e, "initialisation"); }
     c->host = lbm::host_slot_take();
     *out = c;
@@ -662,9 +664,6 @@ lbm_status lbm_gradients(lbm_ctx *c, int32_t out_dtype, void *Sxx, void *Sxy, vo
     void *const o[9] = {nullptr, nullptr, nullptr, nullptr, Sxx, Sxy, Syy, dTdx, dTdy};
     return fields(c, out_dtype, o);
 }
-
-// Count of finished blocks of the reductions: zero between launches (set by lbm_init).
-static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>(c->ws + c->lay.off_scalar + 200); }
 
 // The n results that a launch on the context's stream leaves at dev (its pinned slot, or device
 // memory), once the stream is done.

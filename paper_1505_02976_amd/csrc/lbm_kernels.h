@@ -42,8 +42,9 @@ struct BatchKernels {
     int bulk_threads, wall_threads;
 };
 
+// Initial populations; *done, the reductions' count of finished blocks, is set to zero.
 hipError_t launch_init(int storage, void *dst, const KParams &P, const double *T, const double *p,
-                       const double *ux, const double *uy, hipStream_t st);
+                       const double *ux, const double *uy, unsigned *done, hipStream_t st);
 hipError_t launch_step(int storage, const void *src, void *dst, const KParams &P, hipStream_t st);
 // The launches of one step separately: interior tiles; edge tiles and walled rows.
 hipError_t launch_step_bulk(int storage, const void *src, void *dst, const KParams &P, hipStream_t st);

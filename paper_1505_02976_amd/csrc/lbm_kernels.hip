@@ -26,10 +26,11 @@ template <typename S, typename R>
 __global__ void __launch_bounds__(BULK_BX)
 k_init(S *__restrict__ dst, KParams P, const double *__restrict__ T_init,
        const double *__restrict__ p_init, const double *__restrict__ ux_init,
-       const double *__restrict__ uy_init)
+       const double *__restrict__ uy_init, unsigned *done)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y;
+    if (x == 0 && y == 0) *done = 0;
     if (x >= P.nx) return;
     const long long n = (long long)y * P.nx + x;
     const Cst<R> &k = make_cst<R>(P);
@@ -587,9 +588,9 @@ static dim3 bulk_grid(const KParams &P) { return dim3((P.nx + BULK_BX - 1) / BUL
 
 template <typename S, typename R>
 static hipError_t launch_init_t(void *dst, const KParams &P, const double *T, const double *p,
-                                const double *ux, const double *uy, hipStream_t st)
+                                const double *ux, const double *uy, unsigned *done, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_init<S, R>), bulk_grid(P), dim3(BULK_BX), 0, st, (S *)dst, P, T, p, ux, uy);
+    hipLaunchKernelGGL((k_init<S, R>), bulk_grid(P), dim3(BULK_BX), 0, st, (S *)dst, P, T, p, ux, uy, done);
     return hipGetLastError();
 }
 
@@ -710,11 +711,11 @@ static hipError_t launch_state_t(void *buf, const KParams &P, double *io, bool g
     }
 
 hipError_t launch_init(int storage, void *dst, const KParams &P, const double *T, const double *p,
-                       const double *ux, const double *uy, hipStream_t st)
+                       const double *ux, const double *uy, unsigned *done, hipStream_t st)
 {
-    LBM_DISPATCH(storage, (launch_init_t<double, double>(dst, P, T, p, ux, uy, st)),
-                 (launch_init_t<float, float>(dst, P, T, p, ux, uy, st)),
-                 (launch_init_t<__half, float>(dst, P, T, p, ux, uy, st)))
+    LBM_DISPATCH(storage, (launch_init_t<double, double>(dst, P, T, p, ux, uy, done, st)),
+                 (launch_init_t<float, float>(dst, P, T, p, ux, uy, done, st)),
+                 (launch_init_t<__half, float>(dst, P, T, p, ux, uy, done, st)))
 }
 
 hipError_t launch_step(int storage, const void *src, void *dst, const KParams &P, hipStream_t st)
