@@ -219,7 +219,7 @@ struct lbm_ctx {
     int in_batch;
     int cur;             // buffer holding the current populations (0: a, 1: b)
     int fuse;            // time steps per pass over the populations (1 or 2)
-    int tile_steps;      // steps per launch on tiles (0: passes); lbm_step's way until lbm_set_fusion is called
+    lbm::TileSteps tsteps;      // steps per launch on tiles (0: passes); lbm_step's way until lbm_set_fusion is called
     lbm::TileGrid tile;
     int64_t check_every; // lbm_step checks for non-finite populations at multiples of this time (0: never)
     lbm::KParams kpm;    // parameters of the eight-row scratch grid of the two-step pass
@@ -245,12 +245,21 @@ static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>
 template <typename F> hipError_t by_launches(int64_t nsteps, int most, F &&f)
 {
     hipError_t e = hipSuccess;
-    for (int64_t left = nsteps, l = (nsteps + most - 1) / most; l > 0 && e == hipSuccess; --l) {
+    for (int64_t left = nsteps, l = nsteps > 0 ? (nsteps + most - 1) / most : 0; l > 0 && e == hipSuccess; --l) {
         const int n = (int)((left + l - 1) / l);
         e = f(n);
         left -= n;
     }
     return e;
+}
+
+// How many of nsteps steps go by launches on tiles (the first ones): all where equal launches take
+// `least` steps or more each, otherwise those of full launches.
+static int64_t tile_share(int64_t nsteps, const lbm::TileSteps &t)
+{
+    if (t.most < 1 || nsteps < 1) return 0;
+    const int64_t launches = (nsteps + t.most - 1) / t.most;
+    return nsteps / launches >= t.least ? nsteps : nsteps / t.most * t.most;
 }
 
 extern "C" {
@@ -325,7 +334,7 @@ static lbm_status init_ctx(const lbm_params *params, void *workspace, size_t wor
     // two-step passes by default where they are faster: FP32 and FP64 storage, whose tiles
     // match the two-step wavefronts (see lbm_step2.hip)
     c->fuse = (params->storage != LBM_F16 && lbm::step2_supported(kp)) ? 2 : 1;
-    c->tile_steps = lbm::tile_plan(params->storage, &kp, 1, &c->tile);
+    c->tsteps = lbm::tile_plan(params->storage, &kp, 1, &c->tile);
     c->n_main2 = c->n_full2 = 0;
     c->main_nodes2 = 0;
     if (lbm::step2_supported(kp)) {
@@ -435,7 +444,7 @@ hipError_t run_passes(lbm_ctx *c, int64_t npass, const StepEvents *tev, int ever
 // nsteps steps as launches of several steps on tiles.
 hipError_t tile_steps(lbm_ctx *c, int64_t nsteps)
 {
-    return by_launches(nsteps, c->tile_steps, [&](int n) {
+    return by_launches(nsteps, c->tsteps.most, [&](int n) {
         const hipError_t e = lbm::launch_tile(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
         if (e == hipSuccess) {
             c->t += n;
@@ -449,9 +458,9 @@ hipError_t tile_steps(lbm_ctx *c, int64_t nsteps)
 // grid takes them).
 hipError_t single_steps(lbm_ctx *c, int64_t n)
 {
-    if (c->tile_steps > 0) return tile_steps(c, n);
-    hipError_t e = hipSuccess;
-    for (; n > 0 && e == hipSuccess; --n) {
+    const int64_t tiles = tile_share(n, c->tsteps);
+    hipError_t e = tile_steps(c, tiles);
+    for (n -= tiles; n > 0 && e == hipSuccess; --n) {
         e = lbm::launch_step(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->stream);
         if (e == hipSuccess) {
             c->t += 1;
@@ -465,16 +474,15 @@ hipError_t single_steps(lbm_ctx *c, int64_t n)
 hipError_t states_after(const lbm_ctx *c, const char *src, char *dst, size_t stride, int64_t n)
 {
     const int sto = c->prm.storage;
-    if (c->tile_steps > 0)
-        return by_launches(n, c->tile_steps, [&](int k) {
-            const hipError_t r = lbm::launch_tile(sto, src, dst, c->kp, c->tile, k,
-                                                  (long long)(stride / elem_size(sto)), c->stream);
-            src = dst + (size_t)(k - 1) * stride;
-            dst += (size_t)k * stride;
-            return r;
-        });
-    hipError_t e = hipSuccess;
-    for (; n > 0 && e == hipSuccess; --n) {
+    const int64_t tiles = tile_share(n, c->tsteps);
+    hipError_t e = by_launches(tiles, c->tsteps.most, [&](int k) {
+        const hipError_t r = lbm::launch_tile(sto, src, dst, c->kp, c->tile, k,
+                                              (long long)(stride / elem_size(sto)), c->stream);
+        src = dst + (size_t)(k - 1) * stride;
+        dst += (size_t)k * stride;
+        return r;
+    });
+    for (n -= tiles; n > 0 && e == hipSuccess; --n) {
         e = lbm::launch_step(sto, src, dst, c->kp, c->stream);
         src = dst;
         dst += stride;
@@ -492,14 +500,14 @@ hipError_t run_steps(lbm_ctx *c, int64_t nsteps, const StepEvents *tev, int ever
     hipError_t e = hipSuccess;
     const int sto = c->prm.storage;
     int64_t s = 0, gi = 0;
-    if (c->tile_steps > 0 && !tev) {
-        e = tile_steps(c, nsteps);
-        s = nsteps;
+    if (!tev) {
+        s = tile_share(nsteps, c->tsteps);
+        e = tile_steps(c, s);
     }
     if (c->fuse == 2 && nsteps - s >= 2 && e == hipSuccess) {
-        const int64_t npass = nsteps / 2;
+        const int64_t npass = (nsteps - s) / 2;
         e = run_passes(c, npass, tev, every, 0);
-        s = 2 * npass;
+        s += 2 * npass;
         gi = npass;
     }
     while (s < nsteps && e == hipSuccess) {
@@ -636,7 +644,7 @@ lbm_status lbm_set_fusion(lbm_ctx *c, int32_t steps_per_pass)
     if (steps_per_pass == 2 && !lbm::step2_supported(c->kp))
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need nx >= 4 and ny >= 8");
     c->fuse = steps_per_pass;
-    c->tile_steps = 0;
+    c->tsteps = {0, 0};
     return LBM_OK;
 }
 
@@ -980,7 +988,7 @@ struct lbm_batch {
     int nitems2[lbm::STEP2_LAUNCHES], nrows2;
     int2 *tile_items;           // (problem, tile) of the launches of several steps
     int ntiles;
-    int tile_steps;             // their steps per launch (0: passes), until the passes are chosen or tuned
+    lbm::TileSteps tsteps;      // their steps per launch (0: passes), until the passes are chosen or tuned
     int fields;                 // which problems have a porosity field (FIELDS_NONE, ...)
     hipGraph_t graph;           // one-step mode: GRAPH_STEPS steps replayed as one graph
     hipGraphExec_t exec;
@@ -1007,7 +1015,7 @@ struct BatchLayout {
     size_t off_probs, off_bulk, off_edge, off_wall, off_all, off_flags, off_items2[lbm::STEP2_LAUNCHES], off_rows2, off_tiles, total;
     std::vector<int2> bulk, edge, wall, all, items2[lbm::STEP2_LAUNCHES], rows2, tiles;
     bool two;
-    int tile_steps;
+    lbm::TileSteps tsteps;
     std::vector<lbm::TileGrid> tile;
     std::vector<lbm::KParams> kp;
     std::vector<int> tiles_x;
@@ -1106,9 +1114,9 @@ lbm_status batch_layout(const lbm_params *params, int32_t n, BatchLayout &B)
     }
     B.off_rows2 = o; o += align_up(B.rows2.size() * sizeof(int2), 256);
     B.tile.resize(n);
-    B.tile_steps = lbm::tile_plan(params[0].storage, B.kp.data(), n, B.tile.data());
+    B.tsteps = lbm::tile_plan(params[0].storage, B.kp.data(), n, B.tile.data());
     B.tiles.clear();
-    for (int k = 0; k < n && B.tile_steps; ++k)
+    for (int k = 0; k < n && B.tsteps.most; ++k)
         for (int b = 0; b < B.tile[k].nbx * B.tile[k].nby; ++b) B.tiles.push_back(make_int2(k, b));
     B.off_tiles = o; o += align_up(B.tiles.size() * sizeof(int2), 256);
     B.total = o;
@@ -1253,7 +1261,7 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
     b->ev_join = b->ev_main = b->ev_side = nullptr;
     b->bx = lbm::batch_width(0);
     b->w2 = lbm::STEP2_WAVES_PER_BLOCK;
-    b->tile_steps = B.tile_steps;
+    b->tsteps = B.tsteps;
     b->tile_items = reinterpret_cast<int2 *>(ws + B.off_tiles);
     b->ntiles = (int)B.tiles.size();
     b->edge_cap = B.edge.size();
@@ -1402,17 +1410,14 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
 {
     if (!b) return fail(LBM_ERR_INVALID, "batch is NULL");
     if (nsteps < 0) return fail(LBM_ERR_INVALID, "nsteps < 0");
-    int64_t left = nsteps;
-    hipError_t e = hipSuccess;
-    if (b->tile_steps > 0) {
-        e = by_launches(nsteps, b->tile_steps, [&](int n) { return batch_tiles(b, n); });
-        if (e != hipSuccess) return hip_fail(e, "batch tiles");
-        left = 0;
-    } else if (b->fuse == 2) {
+    int64_t left = nsteps - tile_share(nsteps, b->tsteps);
+    hipError_t e = by_launches(nsteps - left, b->tsteps.most, [&](int n) { return batch_tiles(b, n); });
+    if (e != hipSuccess) return hip_fail(e, "batch tiles");
+    if (b->fuse == 2 && left > 1) {
         e = batch_passes(b, left / 2, true, b->w2);
         if (e != hipSuccess) return hip_fail(e, "batch passes");
         left %= 2;
-    } else {
+    } else if (b->fuse != 2) {
         // a graph replays from the buffer it was built for: one single step realigns `cur`
         if (b->exec && b->cur != b->graph_cur && left > GRAPH_STEPS) {
             e = batch_single(b);
@@ -1447,7 +1452,7 @@ lbm_status lbm_batch_set_fusion(lbm_batch *b, int32_t steps_per_pass)
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need FP32/FP64 storage and every grid at least 4 x 8 nodes");
     if (b->fuse != steps_per_pass) batch_drop_graph(b);
     b->fuse = steps_per_pass;
-    b->tile_steps = 0;
+    b->tsteps = {0, 0};
     return LBM_OK;
 }
 
@@ -1522,7 +1527,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t steps, int32_t *width, doubl
     if (e != hipSuccess) return hip_fail(e, "batch autotune");
     st = two ? batch_set_waves2(b, lbm::batch_width(best) / 64) : batch_set_width(b, lbm::batch_width(best));
     if (st != LBM_OK) return st;
-    b->tile_steps = 0;
+    b->tsteps = {0, 0};
     if (width) *width = two ? 64 * b->w2 : b->bx;
     return LBM_OK;
 }
@@ -1532,7 +1537,7 @@ lbm_status lbm_batch_set_width(lbm_batch *b, int32_t width)
     if (!b) return fail(LBM_ERR_INVALID, "batch is NULL");
     for (int i = 0; i < LBM_BATCH_NUM_WIDTHS; ++i)
         if (lbm::batch_width(i) == width) {
-            b->tile_steps = 0;
+            b->tsteps = {0, 0};
             return b->fuse == 2 ? batch_set_waves2(b, width / 64) : batch_set_width(b, width);
         }
     return fail(LBM_ERR_INVALID, "width %d is not one of 64, 128, 256", width);

@@ -26,6 +26,7 @@
 // grid of at most 512 nodes (one block, any number of steps per launch) 17 -> 1.7 us.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 
 #include "lbm_tile.h"
 
@@ -319,13 +320,15 @@ hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 
 // steps, FP32 1000^2 23.1 and 21.4, FP64 700^2 21.2 and 23.3, 1400^2 68.3 and 63.1, FP16 1000^2 20.2
 // and 23.2.
 //
-// Larger grids (TILE_NODES) take the two-step pass (FP16: single steps), which is bound by
-// HBM and recomputes less.  us per step here and there: FP32 1800 x 1900 66 and 67, 2500^2 120 and
+// Larger grids take the two-step pass (FP16: single steps), which is bound by HBM and recomputes less
+// (TILE_NODES).  us per step here and there: FP32 1800 x 1900 66 and 67, 2500^2 120 and
 // 113; FP64 1300^2 53 and 65, 1700^2 91 and 98, 2400^2 177-184 and 182, 3000^2 275 and 276; FP16 1500^2 41
 // and 44, 2000^2 75 and 71.  With a porosity field, whose coefficients a tile forms once per launch,
-// FP32 2000 x 2100 90 and 102, 3500^2 259 and 264; FP64 2000^2 135 and 153, 3500^2 399 and 419; FP16 2500^2
-// 120 and 122.  Batches: FP64 cavities of 180-300 nodes a side, 3.7 M in all, 150 and 156, 8.6 M 354 and
-// 346; FP32 5 M 122 and 125, 8.6 M 213 and 213, 25.6 M 567 and 534; FP16 10.6 M 268 and 270.
+// FP32 2000 x 2100 90 and 102, 3500^2 259 and 264; FP64 2000^2 135 and 153, 3500^2 399 and 419; FP16 1800 x 1900
+// 71 and 77, 2200^2 97 and 94.
+// Batches: FP64 cavities of 180-300 nodes a side, 3.7 M in all, 150 and 156, 8.6 M 354 and 346; FP32 of 200^2
+// 4 M 112 and 123, of 500^2 3.75 M 103 and 102, of 1000^2 5 M 104 and 99; FP16 10.6 M 268 and 270, two of 1300^2 64
+// and 64.
 constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
 constexpr long long TILE_WIDE[2] = {120000, 350000};
 constexpr int TILE_ACROSS = 48;                   // shorter sides: any shape
@@ -333,51 +336,123 @@ constexpr long long TILE_NODES[3] = {5000000, 3500000, 2300000};
 constexpr long long TILE_NODES_FIELD[3] = {12500000, 12500000, 6500000};
 constexpr long long TILE_NODES_BATCH[2] = {4000000, 6000000};   // FP16: the mean grid at most TILE_MEAN
 constexpr long long TILE_MEAN = 2000000;
+constexpr long long TILE_LARGE = 150000;
 
-static long long tile_nodes_limit(int storage, int n, bool field)
+// What the plan looks at in the grids of a launch.
+struct TileSet {
+    int storage, n;
+    long long nodes;
+    bool field;                  // all with a porosity field
+    bool narrow, thin;           // some grid is narrow; those of fewer than TILE_ACROSS columns hold most of the nodes
+    int nx, ny;                  // n = 1
+    bool px, py;
+};
+
+static long long tile_nodes_limit(const TileSet &t)
 {
-    if (n > 1) return storage == 2 ? n * TILE_MEAN : TILE_NODES_BATCH[storage];
-    return field ? TILE_NODES_FIELD[storage] : TILE_NODES[storage];
+    if (t.n > 1) return t.storage == 2 ? t.n * TILE_MEAN : TILE_NODES_BATCH[t.storage];
+    return (t.field ? TILE_NODES_FIELD : TILE_NODES)[t.storage];
+}
+
+// Fewest steps of a launch.  A launch costs about the same for any number of steps once a grid fills
+// the chip (FP32 1800 x 1900 245 us for one step, 264 for four): the steps that are left over from
+// full launches, and short calls, go to the passes where those are faster: from TILE_STEPS1, 2 and 3
+// nodes on for one, two and three steps.  us per step here and there: one, FP64 420 x 427 19.2 and
+// 21.0, 500 x 507 27.1 and 24.2, FP32 500 x 507 15.2 and 17.1, 640 x 647 28.6 and 22.3, FP16 720 x 727 18.9 and
+// 21.0, 850 x 857 28.9 and 23.6; two, FP64 850 x 857 40 and 44, 1150 x 1157 70 and 61, FP32 950 x 957 34.5 and
+// 39.1, 1150 x 1157 49.5 and 39.0, FP16 950 x 957 24.0 and 26.4, 1150 x 1157 33.7 and 30.6; three, FP32 1550 x 1557
+// 62 and 63, 1750 x 1757 81 and 75, with a field 1650 x 1657 75 and 80, 1850 x 1857 100 and 95 (FP64: never,
+// 2200^2 191 and 195).
+// Walls few nodes apart make tiles slower as above (one step, FP64 124 x 1209 17.2 and 13.8, FP32 14,705 x 17
+// 19.0 and 15.5; two, FP32 30,303 x 33 40.8 and 34.6; three 60,606 x 33 64 and 57, FP64 with a field 27,777 x 36
+// 69 and 59): such grids count TILE_NEAR_BY times.  A pass's wavefronts take 62 columns (FP16: 64) and leave
+// lanes idle beside a grid that is not a multiple (one step, FP64 with a field 64 x 3906 32 and 42, FP32
+// 64 x 9375 51 and 42; two, FP32 64 x 37,500 99 and 126, 80 x 30,000 0.9 times): the square of the share of the
+// lanes in use enters.  Up to TILE_THIN columns tiles are faster in any case (one step, 32 x 100,000
+// FP64 309 and 388), below TILE_ACROSS for two steps and more (40 x 60,000 158 and 186), in FP16 below
+// TILE_NEAR (80 x 30,000 with a field 77 and 144).
+// Batches: one step, FP64 16 of 200^2 0.99 times, FP32 10 of 200^2 1.02 and 16 0.84, FP16 10 of 200^2 1.27 and
+// 16 0.92; two, FP64 25 of 200^2 1.04 and 40 0.86, FP32 1.05 and 0.93, FP16 six of 500^2 1.11 and 12
+// 0.99; three, FP32 ten of 500^2 1.03 and 12 0.99; 200 of 47 x 400, FP32, one step 276 and 336 us.
+constexpr long long TILE_STEPS1[3] = {180000, 270000, 450000}, TILE_STEPS2[3] = {800000, 1000000, 850000};
+constexpr long long TILE_STEPS3[2] = {2500000, 3000000};                        // FP32; with a field
+constexpr long long TILE_STEPS3_FLAT[3] = {900000, 1800000, 1500000};           // FP64 with a field, FP32, FP16 one or two tiles high
+constexpr int TILE_THIN = 32, TILE_NEAR = 150;
+constexpr double TILE_NEAR_BY[2][3] = {{2.0, 1.5, 1.6}, {1.2, 1.15, 1.5}};      // for one and for two steps
+constexpr long long TILE_STEPS1_BATCH[3] = {550000, 430000, 600000}, TILE_STEPS2_BATCH[3] = {1050000, 1200000, 2500000};
+constexpr long long TILE_STEPS3_BATCH = 2800000;                                // FP32, grids of TILE_LARGE on average
+constexpr long long TILE_SMALL = 100000;                                        // FP16: grids below on average, any two
+
+static int tile_least_batch(const TileSet &t)
+{
+    if ((t.thin && t.storage != 0) || t.nodes < TILE_STEPS1_BATCH[t.storage]) return 1;
+    if (t.nodes < TILE_STEPS2_BATCH[t.storage] || (t.storage == 2 && t.nodes < t.n * TILE_SMALL)) return 2;
+    return t.storage == 1 && t.nodes >= std::max(TILE_STEPS3_BATCH, t.n * TILE_LARGE) ? 4 : 3;
+}
+
+static int tile_least(const TileSet &t)
+{
+    if (t.n > 1) return tile_least_batch(t);
+    if (t.nx <= TILE_THIN) return 1;
+    const int s = t.storage, cols = s == 2 ? 64 : 62, chunks = (t.nx + cols - 1) / cols;
+    const double used = (double)t.nx / ((double)chunks * cols), nodes = (double)t.nodes * used * used;
+    const bool flat = !t.py && t.ny < TILE_NEAR, tall = !t.px && t.nx < TILE_NEAR;
+    const bool near = tall || (flat && (s == 0 || t.ny > 16));  // FP32 and FP16: not if one tile holds both walls
+    if (nodes * (near ? TILE_NEAR_BY[0][s] : 1.0) < (double)TILE_STEPS1[s]) return 1;
+    if (t.nx < TILE_ACROSS || (s == 2 && tall)) return 2;
+    if (nodes * (near ? TILE_NEAR_BY[1][s] : 1.0) < (double)TILE_STEPS2[s]) return 2;
+    const bool by_flat = flat && (s == 0 ? t.field : (s == 1 ? t.ny > 16 : t.narrow));
+    if (by_flat && t.nodes >= TILE_STEPS3_FLAT[s]) return 4;
+    return s == 1 && t.ny > 16 && nodes >= (double)TILE_STEPS3[t.field] ? 4 : 3;
 }
 
 struct TileShape { int tw, th, ns0, ns1; };       // tile and the range of steps per launch
-
 struct TileShapes { const TileShape *first; int n; };
 
-// The shapes that tile_plan chooses from, for grids of `nodes` nodes together.
-static TileShapes tile_shapes(int storage, long long nodes, bool narrow)
+// The shapes that tile_plan chooses from.
+static TileShapes tile_shapes(const TileSet &t)
 {
     constexpr int M = TILE_MAX_STEPS;
     static constexpr TileShape all[] = {{8, 8, 1, M}, {12, 8, 1, M}, {16, 8, 1, M}, {32, 8, 1, M}, {12, 12, 1, M}, {16, 12, 1, M},
                                         {16, 16, 1, M}, {20, 20, 1, M}, {28, 12, 1, M}, {26, 10, 1, M}, {30, 14, 1, M}};
     static constexpr TileShape large[] = {{28, 12, 3, 3}, {26, 10, 4, 4}};
-    if (!narrow && nodes >= TILE_WIDE[1]) return {large + (storage == 1 || tile_dense(storage, nodes)), 1};
-    if (!narrow && nodes >= TILE_WIDE[0]) return {large, 2};
+    if (!t.narrow && t.nodes >= TILE_WIDE[1]) return {large + (t.storage == 1 || tile_dense(t.storage, t.nodes)), 1};
+    if (!t.narrow && t.nodes >= TILE_WIDE[0]) return {large, 2};
     return {all, (int)(sizeof(all) / sizeof(all[0]))};
 }
 
-int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
+TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
 {
-    long long nodes = 0;
-    bool field = true, one_block = true, narrow = false;
+    TileSet t = {};
+    t.storage = storage;
+    t.n = n;
+    t.field = true;
+    t.nx = P[0].nx; t.ny = P[0].ny; t.px = P[0].px; t.py = P[0].py;
+    bool one_block = true;
+    for (int k = 0; k < n; ++k) {
+        t.nodes += (long long)P[k].nx * P[k].ny;
+        t.field = t.field && P[k].field;
+    }
+    long long narrow = 0, thin = 0;
     for (int k = 0; k < n; ++k) {
         const long long nk = (long long)P[k].nx * P[k].ny;
-        nodes += nk;
-        field = field && P[k].field;
         one_block = one_block && nk <= TILE_NT;
-        narrow = narrow || std::min(P[k].nx, P[k].ny) < TILE_ACROSS;
+        if (P[k].nx < TILE_ACROSS) thin += nk;
+        if (P[k].nx < TILE_ACROSS || P[k].ny < TILE_ACROSS) narrow += nk;
     }
-    if (nodes > tile_nodes_limit(storage, n, field)) return 0;
+    t.narrow = narrow > 0;
+    t.thin = 2 * thin > t.nodes;
+    if (t.nodes > tile_nodes_limit(t)) return {0, 0};
     if (one_block) {
         for (int k = 0; k < n; ++k) grids[k] = tile_grid(P[k], P[k].nx, P[k].ny);
-        return TILE_ALL_STEPS;
+        return {TILE_ALL_STEPS, 1};
     }
     const int resident = storage == 0 ? 8 : 16;   // wavefronts of this kernel that a CU's registers hold
     const double cus = 256.0;
     TileShape shape = {};
     int best = 0;
     double cost = 0.0;
-    const TileShapes shapes = tile_shapes(storage, nodes, narrow);
+    const TileShapes shapes = tile_shapes(t);
     for (int i = 0; i < shapes.n; ++i) {
         const TileShape &sh = shapes.first[i];
         for (int ns = sh.ns0; ns <= sh.ns1; ++ns) {
@@ -411,7 +486,7 @@ int tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
         }
     }
     for (int k = 0; k < n && best; ++k) grids[k] = tile_grid(P[k], shape.tw, shape.th);
-    return best;
+    return {best, std::min(best, tile_least(t))};
 }
 
 int tile_threads(const TileGrid &g, int ns)

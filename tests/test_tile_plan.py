@@ -1,0 +1,80 @@
+"""What the plan of the launches on tiles decides (lbm_tile.hip), on the host: the fewest steps of a
+launch.  The sizes lie well off the lines, on the side where the measured times are."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+F64, F32, F16 = 0, 1, 2
+
+SOURCE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "lbm_kernels.h"
+// arguments: storage field periodic_x periodic_y, then nx ny count for every kind of problem; prints the
+// most and the fewest steps of a launch and the largest tile of the first problem
+int main(int n, char **v)
+{
+    std::vector<lbm::KParams> P;
+    for (int i = 5; i + 2 < n; i += 3) {
+        lbm::KParams k = {};
+        k.nx = atoi(v[i]);
+        k.ny = atoi(v[i + 1]);
+        k.field = atoi(v[2]);
+        k.px = atoi(v[3]);
+        k.py = atoi(v[4]);
+        for (int m = 0; m < atoi(v[i + 2]); ++m) P.push_back(k);
+    }
+    std::vector<lbm::TileGrid> g(P.size());
+    const lbm::TileSteps t = lbm::tile_plan(atoi(v[1]), P.data(), (int)P.size(), g.data());
+    printf("%d %d %d %d\n", t.most, t.least, t.most ? g[0].tw + (g[0].rx > 0) : 0, t.most ? g[0].th + (g[0].ry > 0) : 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    from paper_1505_02976_amd import build, lbm
+    if not os.path.exists(lbm.LIB_PATH):
+        build.build()
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = str(d / "plan.hip"), str(d / "plan")
+    with open(src, "w") as fh:
+        fh.write(SOURCE)
+    libdir = os.path.dirname(lbm.LIB_PATH)
+    subprocess.run([build.HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(libdir, "csrc"), "-x", "hip", src,
+                    "-x", "none", lbm.LIB_PATH, "-Wl,-rpath," + libdir, "-o", exe], check=True, stderr=subprocess.DEVNULL)
+
+    def call(storage, grids, field=0, px=0, py=0):
+        a = [storage, field, px, py] + [x for g in grids for x in g]
+        out = subprocess.run([exe] + [str(x) for x in a], check=True, capture_output=True, text=True).stdout
+        return tuple(map(int, out.split()))
+    return call
+
+
+@pytest.mark.parametrize("storage,nx,ny,field,least", [
+    (F64, 128, 128, 0, 1), (F64, 350, 350, 0, 1), (F64, 500, 507, 0, 2), (F64, 1150, 1157, 0, 3), (F64, 2200, 2200, 0, 3),
+    (F32, 250, 250, 0, 1), (F32, 460, 467, 0, 1), (F32, 640, 647, 0, 2), (F32, 950, 957, 0, 2), (F32, 1250, 1257, 0, 3),
+    (F32, 1800, 1900, 0, 4), (F32, 1650, 1657, 1, 3), (F32, 2200, 2200, 1, 4),
+    (F16, 640, 647, 0, 1), (F16, 850, 857, 0, 2), (F16, 1250, 1257, 0, 3),
+    # walls few nodes apart; one wavefront of the passes across, one and a little
+    (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 30303, 33, 0, 3),
+    (F64, 32, 100000, 0, 1), (F64, 64, 3906, 1, 1), (F64, 40, 60000, 0, 2), (F16, 80, 30000, 1, 2),
+    # one block: any number
+    (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 1),
+])
+def test_fewest_steps_of_a_launch(plan, storage, nx, ny, field, least):
+    most, got, _, _ = plan(storage, [(nx, ny, 1)], field)
+    assert got == least and most >= got
+
+
+@pytest.mark.parametrize("storage,grid,count,field,least", [
+    (F64, (200, 203), 10, 0, 1), (F64, (200, 203), 20, 0, 2), (F64, (200, 203), 52, 0, 3),
+    (F32, (200, 203), 6, 0, 1), (F32, (200, 203), 16, 0, 2), (F32, (200, 203), 65, 0, 3), (F32, (500, 503), 12, 1, 4),
+    (F16, (200, 203), 10, 0, 1), (F16, (500, 503), 6, 0, 2), (F16, (500, 503), 15, 0, 3), (F16, (47, 400), 200, 0, 1),
+])
+def test_fewest_steps_of_a_batch(plan, storage, grid, count, field, least):
+    most, got, _, _ = plan(storage, [grid + (count,)], field)
+    assert got == least and most >= got
