@@ -320,6 +320,12 @@ hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 
 // steps, FP32 1000^2 23.1 and 21.4, FP64 700^2 21.2 and 23.3, 1400^2 68.3 and 63.1, FP16 1000^2 20.2
 // and 23.2.
 //
+// A narrow grid (fewer than TILE_ACROSS columns or tile_rows rows) is one or two tiles across and
+// takes any shape; a batch does where such problems hold more than half of its nodes.  With the
+// estimate's choice, us per step, and the wide tiles: 20,000 x 40 FP64 52.8 and 36.7, FP32 36.4 and
+// 20.0, 123,076 x 26 FP32 99 and 75; but 12,121 x 33 FP64 20.1 and 22.7, 20,000 x 20 FP16 8.2 and 11.0, 7,500 x 20
+// FP32 4.3 and 5.3; 64 cavities of 200^2 and one of 40^2, FP64 162 and 110, FP32 104 and 64 (the passes 117 and 73).
+//
 // Larger grids take the two-step pass (FP16: single steps), which is bound by HBM and recomputes less
 // (TILE_NODES).  us per step here and there: FP32 1800 x 1900 66 and 67, 2500^2 120 and
 // 113; FP64 1300^2 53 and 65, 1700^2 91 and 98, 2400^2 177-184 and 182, 3000^2 275 and 276; FP16 1500^2 41
@@ -331,7 +337,7 @@ hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 
 // and 64.
 constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
 constexpr long long TILE_WIDE[2] = {120000, 350000};
-constexpr int TILE_ACROSS = 48;                   // shorter sides: any shape
+constexpr int TILE_ACROSS = 48;
 constexpr long long TILE_NODES[3] = {5000000, 3500000, 2300000};
 constexpr long long TILE_NODES_FIELD[3] = {12500000, 12500000, 6500000};
 constexpr long long TILE_NODES_BATCH[2] = {4000000, 6000000};   // FP16: the mean grid at most TILE_MEAN
@@ -343,10 +349,16 @@ struct TileSet {
     int storage, n;
     long long nodes;
     bool field;                  // all with a porosity field
-    bool narrow, thin;           // some grid is narrow; those of fewer than TILE_ACROSS columns hold most of the nodes
+    bool narrow, thin;           // the narrow grids, those of fewer than TILE_ACROSS columns, hold most of the nodes
     int nx, ny;                  // n = 1
     bool px, py;
 };
+
+// Rows below which a grid is narrow, in a launch of `nodes` nodes.
+static int tile_rows(int storage, long long nodes)
+{
+    return nodes < TILE_WIDE[1] ? TILE_ACROSS : (storage == 1 && nodes >= 1200000 ? 18 : 36);
+}
 
 static long long tile_nodes_limit(const TileSet &t)
 {
@@ -434,13 +446,14 @@ TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
         t.field = t.field && P[k].field;
     }
     long long narrow = 0, thin = 0;
+    const int rows = tile_rows(storage, t.nodes);
     for (int k = 0; k < n; ++k) {
         const long long nk = (long long)P[k].nx * P[k].ny;
         one_block = one_block && nk <= TILE_NT;
         if (P[k].nx < TILE_ACROSS) thin += nk;
-        if (P[k].nx < TILE_ACROSS || P[k].ny < TILE_ACROSS) narrow += nk;
+        if (P[k].nx < TILE_ACROSS || P[k].ny < rows) narrow += nk;
     }
-    t.narrow = narrow > 0;
+    t.narrow = 2 * narrow > t.nodes;
     t.thin = 2 * thin > t.nodes;
     if (t.nodes > tile_nodes_limit(t)) return {0, 0};
     if (one_block) {

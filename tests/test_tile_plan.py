@@ -1,5 +1,5 @@
 """What the plan of the launches on tiles decides (lbm_tile.hip), on the host: the fewest steps of a
-launch.  The sizes lie well off the lines, on the side where the measured times are."""
+launch, and whether one small problem changes the tiles of a whole batch.  The sizes lie well off the lines, on the side where the measured times are."""
 import os
 import subprocess
 
@@ -60,7 +60,7 @@ def plan(tmp_path_factory):
     (F32, 1800, 1900, 0, 4), (F32, 1650, 1657, 1, 3), (F32, 2200, 2200, 1, 4),
     (F16, 640, 647, 0, 1), (F16, 850, 857, 0, 2), (F16, 1250, 1257, 0, 3),
     # walls few nodes apart; one wavefront of the passes across, one and a little
-    (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 30303, 33, 0, 3),
+    (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 30303, 33, 0, 3), (F32, 60606, 33, 0, 4),
     (F64, 32, 100000, 0, 1), (F64, 64, 3906, 1, 1), (F64, 40, 60000, 0, 2), (F16, 80, 30000, 1, 2),
     # one block: any number
     (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 1),
@@ -78,3 +78,17 @@ def test_fewest_steps_of_a_launch(plan, storage, nx, ny, field, least):
 def test_fewest_steps_of_a_batch(plan, storage, grid, count, field, least):
     most, got, _, _ = plan(storage, [grid + (count,)], field)
     assert got == least and most >= got
+
+
+@pytest.mark.parametrize("storage", [F64, F32, F16])
+@pytest.mark.parametrize("grid,count", [((200, 203), 64), ((1000, 1000), 3)])
+def test_one_small_problem_does_not_change_the_tiles(plan, storage, grid, count):
+    assert plan(storage, [grid + (count,), (40, 40, 1)]) == plan(storage, [grid + (count,)])
+
+
+@pytest.mark.parametrize("storage,nx,ny,tile", [
+    (F64, 20000, 40, (26, 10)), (F32, 20000, 40, (26, 10)), (F32, 123076, 26, (26, 9)), (F16, 20000, 40, (28, 10)),
+])
+def test_tiles_of_a_few_rows(plan, storage, nx, ny, tile):
+    most, _, tw, th = plan(storage, [(nx, ny, 1)])
+    assert most >= 3 and (tw, th) == tile
