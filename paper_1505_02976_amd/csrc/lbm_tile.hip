@@ -332,6 +332,14 @@ hipError_t launch_batch_tile(int storage, const BatchProblem *probs, const int2 
 // and 44, 2000^2 75 and 71.  With a porosity field, whose coefficients a tile forms once per launch,
 // FP32 2000 x 2100 90 and 102, 3500^2 259 and 264; FP64 2000^2 135 and 153, 3500^2 399 and 419; FP16 1800 x 1900
 // 71 and 77, 2200^2 97 and 94.
+// Between walls few rows apart a third of the tiles and more hold wall nodes, whose chain is the
+// longer one: there the limit is TILE_FLAT nodes, more in one or two rows of tiles, or TILE_PER_ROW per
+// row.  21,276 x 47 FP64 44 and 51, 34,042 x 47 71 and 70, with a field 90 and 78, 26,666 x 60 69 and 67, 88 and 77,
+// 8,000 x 200 57 and 63, 66 and 73, 16,000 x 200 113 and 111, 135 and 126, 15,000 x 400 189 and 187, 219 and 212,
+// 61,538 x 26 66 and 77, 96,969 x 33 143 and 136, 333,333 x 12 108 and 211, 200,000 x 4 with a field 0.94 times;
+// FP16 26,666 x 60 33.5 and 31.7, 8,000 x 200 30.6 and 31.8, 16,000 x 200 60 and 50; FP32 with a field
+// 60,000 x 200 279 and 264.  FP64 grids of 48 to 63 columns, of which two tiles in three hold wall nodes and
+// which fill the one wavefront of a pass: 62 x 25,806 80 and 81, with a field 96 and 93.
 // Batches: FP64 cavities of 180-300 nodes a side, 3.7 M in all, 150 and 156, 8.6 M 354 and 346; FP32 of 200^2
 // 4 M 112 and 123, of 500^2 3.75 M 103 and 102, of 1000^2 5 M 104 and 99; FP16 10.6 M 268 and 270, two of 1300^2 64
 // and 64.
@@ -339,10 +347,13 @@ constexpr int TILE_MAX_STEPS = 8, TILE_ALL_STEPS = 1024;
 constexpr long long TILE_WIDE[2] = {120000, 350000};
 constexpr int TILE_ACROSS = 48;
 constexpr long long TILE_NODES[3] = {5000000, 3500000, 2300000};
-constexpr long long TILE_NODES_FIELD[3] = {12500000, 12500000, 6500000};
+constexpr long long TILE_NODES_FIELD[3] = {12500000, 12500000, 4200000};
+constexpr long long TILE_FLAT[3] = {1200000, 6000000, 1100000};
+constexpr long long TILE_FLAT_FIELD[3] = {1200000, 6000000, 1700000};
+constexpr int TILE_PER_ROW[3] = {8000, 6000, 8000};
 constexpr long long TILE_NODES_BATCH[2] = {4000000, 6000000};   // FP16: the mean grid at most TILE_MEAN
-constexpr long long TILE_MEAN = 2000000;
-constexpr long long TILE_LARGE = 150000;
+constexpr long long TILE_MEAN = 1700000;
+constexpr long long TILE_LARGE = 150000, TILE_NODES_LARGE = 3500000;   // FP32 batches of grids of TILE_LARGE on average
 
 // What the plan looks at in the grids of a launch.
 struct TileSet {
@@ -352,18 +363,33 @@ struct TileSet {
     bool narrow, thin;           // the narrow grids, those of fewer than TILE_ACROSS columns, hold most of the nodes
     int nx, ny;                  // n = 1
     bool px, py;
+    long long flat;              // limit of the nodes between walls few rows apart
 };
 
 // Rows below which a grid is narrow, in a launch of `nodes` nodes.
 static int tile_rows(int storage, long long nodes)
 {
-    return nodes < TILE_WIDE[1] ? TILE_ACROSS : (storage == 1 && nodes >= 1200000 ? 18 : 36);
+    return nodes < TILE_WIDE[1] ? TILE_ACROSS : (storage == 1 && nodes >= TILE_FLAT[0] ? 18 : 36);
+}
+
+static long long tile_flat_limit(int storage, bool field, int ny)
+{
+    const long long flat = (field ? TILE_FLAT_FIELD : TILE_FLAT)[storage];
+    if (ny < 6 && storage == 0) return 750000;
+    if (ny < 20) return INT64_MAX;
+    return std::max(ny < 36 ? flat * 4 / 3 : flat, (long long)TILE_PER_ROW[storage] * ny);
 }
 
 static long long tile_nodes_limit(const TileSet &t)
 {
-    if (t.n > 1) return t.storage == 2 ? t.n * TILE_MEAN : TILE_NODES_BATCH[t.storage];
-    return (t.field ? TILE_NODES_FIELD : TILE_NODES)[t.storage];
+    if (t.n > 1) {
+        if (t.storage == 2) return std::min(t.flat, t.n * TILE_MEAN);
+        const bool large = t.storage == 1 && !t.field && t.nodes >= t.n * TILE_LARGE;
+        return std::min(t.flat, large ? TILE_NODES_LARGE : TILE_NODES_BATCH[t.storage]);
+    }
+    const long long most = (t.field ? TILE_NODES_FIELD : TILE_NODES)[t.storage];
+    if (t.storage == 0 && !t.px && t.nx >= TILE_ACROSS && t.nx < 64) return std::min(most, TILE_FLAT[0]);
+    return std::min(most, t.flat);
 }
 
 // Fewest steps of a launch.  A launch costs about the same for any number of steps once a grid fills
@@ -440,6 +466,7 @@ TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
     t.n = n;
     t.field = true;
     t.nx = P[0].nx; t.ny = P[0].ny; t.px = P[0].px; t.py = P[0].py;
+    t.flat = INT64_MAX;
     bool one_block = true;
     for (int k = 0; k < n; ++k) {
         t.nodes += (long long)P[k].nx * P[k].ny;
@@ -452,6 +479,9 @@ TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
         one_block = one_block && nk <= TILE_NT;
         if (P[k].nx < TILE_ACROSS) thin += nk;
         if (P[k].nx < TILE_ACROSS || P[k].ny < rows) narrow += nk;
+        // a batch of grids that are not flat has the same share of wall nodes in its passes
+        if (!P[k].py && (n == 1 || P[k].nx >= 8 * (long long)P[k].ny))
+            t.flat = std::min(t.flat, tile_flat_limit(storage, t.field, P[k].ny));
     }
     t.narrow = 2 * narrow > t.nodes;
     t.thin = 2 * thin > t.nodes;

@@ -1,5 +1,6 @@
 """What the plan of the launches on tiles decides (lbm_tile.hip), on the host: the fewest steps of a
-launch, and whether one small problem changes the tiles of a whole batch.  The sizes lie well off the lines, on the side where the measured times are."""
+launch, where a grid or a batch leaves tiles, and whether one small problem changes the tiles of a
+whole batch.  The sizes lie well off the lines, on the side where the measured times are."""
 import os
 import subprocess
 
@@ -92,3 +93,19 @@ def test_one_small_problem_does_not_change_the_tiles(plan, storage, grid, count)
 def test_tiles_of_a_few_rows(plan, storage, nx, ny, tile):
     most, _, tw, th = plan(storage, [(nx, ny, 1)])
     assert most >= 3 and (tw, th) == tile
+
+
+@pytest.mark.parametrize("storage,nx,ny,count,field,tiles", [
+    (F64, 26666, 60, 1, 0, False), (F64, 10000, 60, 1, 0, True), (F64, 16000, 200, 1, 1, False), (F64, 8000, 200, 1, 1, True),
+    (F64, 15000, 400, 1, 0, False), (F64, 333333, 12, 1, 0, True), (F64, 96969, 33, 1, 0, False), (F64, 200000, 4, 1, 1, False),
+    (F64, 62, 25806, 1, 1, False), (F64, 124, 12903, 1, 0, True), (F64, 1537, 1025, 1, 1, True), (F64, 3500, 3400, 1, 1, True),
+    (F16, 26666, 60, 1, 0, False), (F16, 16000, 200, 1, 0, False), (F16, 13333, 60, 1, 1, True), (F16, 2500, 2507, 1, 1, False),
+    (F32, 60000, 200, 1, 1, False), (F32, 30000, 200, 1, 1, True), (F32, 1800, 1900, 1, 0, True),
+    (F64, 6000, 47, 12, 0, False), (F64, 500, 503, 12, 0, True), (F32, 1000, 1000, 5, 0, False), (F32, 1000, 1000, 5, 1, True),
+])
+def test_where_grids_leave_tiles(plan, storage, nx, ny, count, field, tiles):
+    assert (plan(storage, [(nx, ny, count)], field)[0] > 0) == tiles
+
+
+def test_rows_between_no_walls_have_no_limit(plan):
+    assert plan(F64, [(26666, 60, 1)], 0, 0, 1)[0] > 0
