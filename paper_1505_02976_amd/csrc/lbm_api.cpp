@@ -474,7 +474,7 @@ hipError_t single_steps(lbm_ctx *c, int64_t n)
 hipError_t states_after(const lbm_ctx *c, const char *src, char *dst, size_t stride, int64_t n)
 {
     const int sto = c->prm.storage;
-    const int64_t tiles = tile_share(n, c->tsteps);
+    const int64_t tiles = c->tsteps.every ? tile_share(n, c->tsteps) : 0;
     hipError_t e = by_launches(tiles, c->tsteps.most, [&](int k) {
         const hipError_t r = lbm::launch_tile(sto, src, dst, c->kp, c->tile, k,
                                               (long long)(stride / elem_size(sto)), c->stream);
@@ -644,7 +644,7 @@ lbm_status lbm_set_fusion(lbm_ctx *c, int32_t steps_per_pass)
     if (steps_per_pass == 2 && !lbm::step2_supported(c->kp))
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need nx >= 4 and ny >= 8");
     c->fuse = steps_per_pass;
-    c->tsteps = {0, 0};
+    c->tsteps = {0, 0, false};
     return LBM_OK;
 }
 
@@ -1452,7 +1452,7 @@ lbm_status lbm_batch_set_fusion(lbm_batch *b, int32_t steps_per_pass)
         return fail(LBM_ERR_UNSUPPORTED, "two-step passes need FP32/FP64 storage and every grid at least 4 x 8 nodes");
     if (b->fuse != steps_per_pass) batch_drop_graph(b);
     b->fuse = steps_per_pass;
-    b->tsteps = {0, 0};
+    b->tsteps = {0, 0, false};
     return LBM_OK;
 }
 
@@ -1527,7 +1527,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t steps, int32_t *width, doubl
     if (e != hipSuccess) return hip_fail(e, "batch autotune");
     st = two ? batch_set_waves2(b, lbm::batch_width(best) / 64) : batch_set_width(b, lbm::batch_width(best));
     if (st != LBM_OK) return st;
-    b->tsteps = {0, 0};
+    b->tsteps = {0, 0, false};
     if (width) *width = two ? 64 * b->w2 : b->bx;
     return LBM_OK;
 }
@@ -1537,7 +1537,7 @@ lbm_status lbm_batch_set_width(lbm_batch *b, int32_t width)
     if (!b) return fail(LBM_ERR_INVALID, "batch is NULL");
     for (int i = 0; i < LBM_BATCH_NUM_WIDTHS; ++i)
         if (lbm::batch_width(i) == width) {
-            b->tsteps = {0, 0};
+            b->tsteps = {0, 0, false};
             return b->fuse == 2 ? batch_set_waves2(b, width / 64) : batch_set_width(b, width);
         }
     return fail(LBM_ERR_INVALID, "width %d is not one of 64, 128, 256", width);

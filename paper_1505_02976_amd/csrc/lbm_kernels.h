@@ -116,8 +116,9 @@ hipError_t launch_batch_step2(int storage, const BatchProblem *probs, const int2
 
 // Several steps per launch, one LDS-resident tile per block (lbm_tile.hip).  tile_plan picks
 // the tiles of the n grids of a launch and returns the steps of a launch: at most `most` (0: these
-// grids do not take the path); fewer than `least` are faster by passes.
-struct TileSteps { int most, least; };
+// grids do not take the path); fewer than `least` are faster by passes.  every: launches that store
+// every step pay as well.
+struct TileSteps { int most, least; bool every; };
 TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids);
 int tile_threads(const TileGrid &g, int ns);   // threads of a block of a launch of ns steps
 // ns steps from src into dst; hist != 0 stores every step, step s at element offset

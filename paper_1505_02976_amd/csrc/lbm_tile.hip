@@ -421,6 +421,12 @@ constexpr long long TILE_STEPS1_BATCH[3] = {550000, 430000, 600000}, TILE_STEPS2
 constexpr long long TILE_STEPS3_BATCH = 2800000;                                // FP32, grids of TILE_LARGE on average
 constexpr long long TILE_SMALL = 100000;                                        // FP16: grids below on average, any two
 
+// Launches that store every step (the adjoint's forward states) write tiles of 24-28 columns, parts of
+// cache lines, once per step.  us per reverse step by tiles and by single steps: FP64 576^2 75.6 and 77.0,
+// 768^2 125 and 122, 1024^2 212 and 188; FP32 450^2 38.0 and 40.6, 576^2 65.0 and 61.9, 1024^2 181 and 144, 1536^2
+// 400 and 314; FP16 768^2 91 and 94, 1024^2 143 and 139.
+constexpr long long TILE_EVERY[3] = {500000, 280000, 800000};
+
 static int tile_least_batch(const TileSet &t)
 {
     if ((t.thin && t.storage != 0) || t.nodes < TILE_STEPS1_BATCH[t.storage]) return 1;
@@ -485,10 +491,10 @@ TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
     }
     t.narrow = 2 * narrow > t.nodes;
     t.thin = 2 * thin > t.nodes;
-    if (t.nodes > tile_nodes_limit(t)) return {0, 0};
+    if (t.nodes > tile_nodes_limit(t)) return {0, 0, false};
     if (one_block) {
         for (int k = 0; k < n; ++k) grids[k] = tile_grid(P[k], P[k].nx, P[k].ny);
-        return {TILE_ALL_STEPS, 1};
+        return {TILE_ALL_STEPS, 1, true};
     }
     const int resident = storage == 0 ? 8 : 16;   // wavefronts of this kernel that a CU's registers hold
     const double cus = 256.0;
@@ -529,7 +535,7 @@ TileSteps tile_plan(int storage, const KParams *P, int n, TileGrid *grids)
         }
     }
     for (int k = 0; k < n && best; ++k) grids[k] = tile_grid(P[k], shape.tw, shape.th);
-    return {best, std::min(best, tile_least(t))};
+    return {best, std::min(best, tile_least(t)), t.nodes < TILE_EVERY[storage]};
 }
 
 int tile_threads(const TileGrid &g, int ns)

@@ -1,5 +1,5 @@
 """What the plan of the launches on tiles decides (lbm_tile.hip), on the host: the fewest steps of a
-launch, where a grid or a batch leaves tiles, and whether one small problem changes the tiles of a
+launch, whether every step of a launch is stored, where a grid or a batch leaves tiles, and whether one small problem changes the tiles of a
 whole batch.  The sizes lie well off the lines, on the side where the measured times are."""
 import os
 import subprocess
@@ -15,7 +15,8 @@ SOURCE = r"""
 #include <vector>
 #include "lbm_kernels.h"
 // arguments: storage field periodic_x periodic_y, then nx ny count for every kind of problem; prints the
-// most and the fewest steps of a launch and the largest tile of the first problem
+// most and the fewest steps of a launch, the largest tile of the first problem and whether launches
+// that store every step pay
 int main(int n, char **v)
 {
     std::vector<lbm::KParams> P;
@@ -30,7 +31,7 @@ int main(int n, char **v)
     }
     std::vector<lbm::TileGrid> g(P.size());
     const lbm::TileSteps t = lbm::tile_plan(atoi(v[1]), P.data(), (int)P.size(), g.data());
-    printf("%d %d %d %d\n", t.most, t.least, t.most ? g[0].tw + (g[0].rx > 0) : 0, t.most ? g[0].th + (g[0].ry > 0) : 0);
+    printf("%d %d %d %d %d\n", t.most, t.least, t.most ? g[0].tw + (g[0].rx > 0) : 0, t.most ? g[0].th + (g[0].ry > 0) : 0, (int)t.every);
 }
 """
 
@@ -67,7 +68,7 @@ def plan(tmp_path_factory):
     (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 1),
 ])
 def test_fewest_steps_of_a_launch(plan, storage, nx, ny, field, least):
-    most, got, _, _ = plan(storage, [(nx, ny, 1)], field)
+    most, got, _, _, _ = plan(storage, [(nx, ny, 1)], field)
     assert got == least and most >= got
 
 
@@ -77,7 +78,7 @@ def test_fewest_steps_of_a_launch(plan, storage, nx, ny, field, least):
     (F16, (200, 203), 10, 0, 1), (F16, (500, 503), 6, 0, 2), (F16, (500, 503), 15, 0, 3), (F16, (47, 400), 200, 0, 1),
 ])
 def test_fewest_steps_of_a_batch(plan, storage, grid, count, field, least):
-    most, got, _, _ = plan(storage, [grid + (count,)], field)
+    most, got, _, _, _ = plan(storage, [grid + (count,)], field)
     assert got == least and most >= got
 
 
@@ -91,7 +92,7 @@ def test_one_small_problem_does_not_change_the_tiles(plan, storage, grid, count)
     (F64, 20000, 40, (26, 10)), (F32, 20000, 40, (26, 10)), (F32, 123076, 26, (26, 9)), (F16, 20000, 40, (28, 10)),
 ])
 def test_tiles_of_a_few_rows(plan, storage, nx, ny, tile):
-    most, _, tw, th = plan(storage, [(nx, ny, 1)])
+    most, _, tw, th, _ = plan(storage, [(nx, ny, 1)])
     assert most >= 3 and (tw, th) == tile
 
 
@@ -109,3 +110,11 @@ def test_where_grids_leave_tiles(plan, storage, nx, ny, count, field, tiles):
 
 def test_rows_between_no_walls_have_no_limit(plan):
     assert plan(F64, [(26666, 60, 1)], 0, 0, 1)[0] > 0
+
+
+@pytest.mark.parametrize("storage,n,every", [
+    (F64, 640, True), (F64, 1024, False), (F32, 450, True), (F32, 640, False), (F16, 768, True), (F16, 1024, False),
+])
+def test_where_states_come_from_tiles(plan, storage, n, every):
+    most, _, _, _, got = plan(storage, [(n, n, 1)], 1)
+    assert most > 0 and bool(got) == every
