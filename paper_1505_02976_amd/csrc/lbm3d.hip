@@ -580,10 +580,14 @@ __host__ __device__ __forceinline__ int inner_z(const K3 &K) { return K.pz ? K.n
 // 10 x 180 x 60, the shortest such row, 29.0 and 22.6 (FP64), 16.2 and 13.4 (FP32), 11.4 and 13.1
 // (FP16).  Below that a block would hold more than 68 such nodes.
 constexpr int XW_ROW = 8;
+// FP16 layers of whole cache lines (the z walls alone) have the blocks of both walls ahead of the first
+// slab instead (`lead`): 192 x 192 x 96 107.5 us a step, spread over the slabs 108.7, 64 x 64 x 96 with porosity
+// per node 16.8 and 17.3, 192 x 100 x 50 33.3 and 34.1.
 struct Slabs {
     unsigned planes, count;
     unsigned inner, walls, zw;     // interior and wall nodes per plane, z wall nodes per slab
     unsigned nbw, nbi;
+    unsigned lead;
 };
 
 // What an interior node hands over to the wall node next to it: x_f's pre-collision
@@ -781,7 +785,17 @@ template <typename S, bool XW, bool NT>
 __global__ void __launch_bounds__(B3, (StepWaves<S>::v))
 k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, Slabs L)
 {
-    const unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
+    unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
+    if (NT && sizeof(S) == 2) {
+        if (b < L.lead) {
+            const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, i = b * B3 + threadIdx.x;
+            if (i >= 2 * pl) return;
+            const unsigned k = i < pl ? i : i - pl, y = k / (unsigned)K.nx;
+            k3_wall_node<S, NT>(src, dst, K, (int)(k - y * (unsigned)K.nx), (int)y, i < pl ? 0 : K.nz - 1);
+            return;
+        }
+        b -= L.lead;
+    }
     const unsigned nb = L.nbw + L.nbi, slab = b / nb, r = b - slab * nb;
     const unsigned p0 = slab * L.planes, np = min(L.planes, (unsigned)inner_z(K) - p0);   // interior planes p0, ...
     const unsigned z0 = p0 + (K.pz ? 0 : 1);
@@ -1123,7 +1137,7 @@ template <typename S> bool lines_whole(const K3 &K)
 
 bool x_walls_inside(const K3 &K) { return !K.px && inner_x(K) >= XW_ROW; }
 
-Slabs slabs_of(const K3 &K, bool whole)
+Slabs slabs_of(const K3 &K, bool whole, bool half)
 {
     Slabs L;
     const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, nz = (unsigned)inner_z(K);
@@ -1131,12 +1145,14 @@ Slabs slabs_of(const K3 &K, bool whole)
     L.walls = x_walls_inside(K) ? (K.py ? 0 : 2 * (unsigned)K.nx) : pl - L.inner;
     L.planes = std::min(nz, std::max(1u, (SLAB_NODES + L.inner - 1) / L.inner));
     L.count = (nz + L.planes - 1) / L.planes;
-    L.zw = K.pz ? 0 : (unsigned)((2LL * pl + L.count - 1) / L.count);
+    const bool lead = half && whole && K.py && !K.pz;
+    L.lead = lead ? blocks_for(2LL * pl) : 0;
+    L.zw = K.pz || lead ? 0 : (unsigned)((2LL * pl + L.count - 1) / L.count);
     L.nbw = blocks_for((long long)L.walls * L.planes + L.zw);
     // large layers are bound by memory: wall blocks are filled (the last slabs have no z wall nodes
     // left), 192 x 192 x 96 FP32 192 us a step instead of 193.5, 64 x 64 x 96 FP16 16.9 instead of 19.4;
     // on rows with x walls the grids are often too small for that, 120 x 4 x 120 12.1 instead of 10.5
-    if (whole && !K.pz) L.zw = L.nbw * B3 - L.walls * L.planes;
+    if (whole && !K.pz && !lead) L.zw = L.nbw * B3 - L.walls * L.planes;
     L.nbi = blocks_for((long long)L.inner * L.planes);
     return L;
 }
@@ -1201,8 +1217,8 @@ lbm_status lbm3_step(lbm3_ctx *c, int64_t nsteps)
     if (nsteps < 0) return fail3(LBM_ERR_INVALID, "nsteps must be >= 0");
     bool whole = false;
     by_storage(c->storage, [&](auto t) { whole = lines_whole<typename decltype(t)::type>(c->K); });
-    const Slabs L = slabs_of(c->K, whole);
-    const unsigned nb = L.count * (L.nbw + L.nbi);
+    const Slabs L = slabs_of(c->K, whole, c->storage == LBM_F16);
+    const unsigned nb = L.lead + L.count * (L.nbw + L.nbi);
     for (int64_t s = 0; s < nsteps; ++s) {
         by_storage(c->storage, [&](auto t) {
             using S = typename decltype(t)::type;

@@ -1,0 +1,39 @@
+"""FP16 layers whose planes are whole cache lines, heated from below and periodic in x and y (the wall
+blocks lead the launch), against the 3-D oracle: planes smaller and larger than a block, walls that
+leave the last wall block unfilled, one interior plane per slab and many.
+
+Tolerance on the populations, from 12 steps of rounding, relative to the largest deviation from the
+state of rest: a stored value is rounded to 2^-11 of itself, and twice that is allowed per step."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+STEPS = 12
+
+
+@pytest.mark.parametrize("seed,nx,ny,nz,ef", [
+    (61, 64, 1, 4, False), (62, 16, 12, 33, True), (63, 32, 10, 20, False), (64, 64, 40, 6, True), (65, 192, 11, 5, False),
+])
+def test_step_matches_oracle(seed, nx, ny, nz, ef):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle.oracle3 as O3
+    from paper_1505_02976_amd import lbm3d
+    cfg = W.random_case3d(seed, nx, ny, nz, eps_field=ef, storage="f16")
+    print(f"case: f16 {nx} x {ny} x {nz} field {ef}", flush=True)
+    sim = lbm3d.Sim3(cfg)
+    sim.step(STEPS)
+    ref = O3.Oracle3(dict(cfg, storage="f64"))
+    ref.step(STEPS)
+    order = [tuple(int(v) for v in c) for c in O3.lattice()[0]]
+    perm = [order.index(c) for c in lbm3d.lattice()]
+    rest = [1.0] + [0.0] * 18
+    w = np.array([1 / 3] + [1 / 18] * 6 + [1 / 36] * 12) * cfg["sigma"] * 0.5 * (cfg["T_hot"] + cfg["T_cold"])
+    dev = [r[perm].reshape(19, -1) - np.array(o)[:, None] for r, o in zip(ref.populations(), (rest, w))]
+    scale = max(float(np.abs(d).max()) for d in dev)
+    for a, b in zip(sim.populations(), ref.populations()):
+        assert float(np.abs(a.cpu().numpy() - b[perm]).max()) < STEPS * 2.0 ** -10 * scale
