@@ -577,9 +577,11 @@ __host__ __device__ __forceinline__ int inner_z(const K3 &K) { return K.pz ? K.n
 // a row apart, so that each load instruction touches 64 lines for one value each.  Time of a
 // step with the x walls in wall blocks and inside: 120 x 4 x 120 FP64 16.3 and 11.8 us,
 // 121 x 95 x 83 with porosity per node 186 and 162 (FP64), 95 and 73 (FP32), 54 and 48 (FP16);
-// 10 x 180 x 60, the shortest such row, 29.0 and 22.6 (FP64), 16.2 and 13.4 (FP32), 11.4 and 13.1
-// (FP16).  Below that a block would hold more than 68 such nodes.
-constexpr int XW_ROW = 8;
+// 10 x 180 x 60, the shortest such row, 29.0 and 22.6 (FP64), 17.6 and 14.3 (FP32).  In FP16 rows of
+// 8 to 10 are faster with them in wall blocks, 10 x 40 x 40 9.3 and 10.8, 12 x 40 x 200 11.9 and 14.2, rows of 14
+// are not: 14 x 180 x 60 14.2 and 14.1, 16 x 40 x 40 12.2 and 9.4.  Below XW_ROW a block would hold more than
+// 68 such nodes.
+constexpr int XW_ROW = 8, XW_ROW_F16 = 14;
 // FP16 layers of whole cache lines (the z walls alone) have the blocks of both walls ahead of the first
 // slab instead (`lead`): 192 x 192 x 96 107.5 us a step, spread over the slabs 108.7, 64 x 64 x 96 with porosity
 // per node 16.8 and 17.3, 192 x 100 x 50 33.3 and 34.1.
@@ -1135,14 +1137,14 @@ template <typename S> bool lines_whole(const K3 &K)
     return K.px && (long long)K.nx * (K.py ? K.ny : 1) * (long long)sizeof(S) % 128 == 0;
 }
 
-bool x_walls_inside(const K3 &K) { return !K.px && inner_x(K) >= XW_ROW; }
+template <typename S> bool x_walls_inside(const K3 &K) { return !K.px && inner_x(K) >= (sizeof(S) == 2 ? XW_ROW_F16 : XW_ROW); }
 
-Slabs slabs_of(const K3 &K, bool whole, bool half)
+Slabs slabs_of(const K3 &K, bool whole, bool half, bool inside)
 {
     Slabs L;
     const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, nz = (unsigned)inner_z(K);
     L.inner = (unsigned)inner_x(K) * (unsigned)inner_y(K);
-    L.walls = x_walls_inside(K) ? (K.py ? 0 : 2 * (unsigned)K.nx) : pl - L.inner;
+    L.walls = inside ? (K.py ? 0 : 2 * (unsigned)K.nx) : pl - L.inner;
     L.planes = std::min(nz, std::max(1u, (SLAB_NODES + L.inner - 1) / L.inner));
     L.count = (nz + L.planes - 1) / L.planes;
     const bool lead = half && whole && K.py && !K.pz;
@@ -1215,17 +1217,20 @@ lbm_status lbm3_step(lbm3_ctx *c, int64_t nsteps)
 {
     if (!c) return fail3(LBM_ERR_INVALID, "ctx is NULL");
     if (nsteps < 0) return fail3(LBM_ERR_INVALID, "nsteps must be >= 0");
-    bool whole = false;
-    by_storage(c->storage, [&](auto t) { whole = lines_whole<typename decltype(t)::type>(c->K); });
-    const Slabs L = slabs_of(c->K, whole, c->storage == LBM_F16);
+    bool whole = false, inside = false;
+    by_storage(c->storage, [&](auto t) {
+        whole = lines_whole<typename decltype(t)::type>(c->K);
+        inside = x_walls_inside<typename decltype(t)::type>(c->K);
+    });
+    const Slabs L = slabs_of(c->K, whole, c->storage == LBM_F16, inside);
     const unsigned nb = L.lead + L.count * (L.nbw + L.nbi);
     for (int64_t s = 0; s < nsteps; ++s) {
         by_storage(c->storage, [&](auto t) {
             using S = typename decltype(t)::type;
             const S *src = reinterpret_cast<const S *>(c->buf[c->cur]);
             S *dst = reinterpret_cast<S *>(c->buf[c->cur ^ 1]);
-            const auto k = x_walls_inside(c->K) ? &k3_step<S, true, false>
-                         : (lines_whole<S>(c->K) ? &k3_step<S, false, true> : &k3_step<S, false, false>);
+            const auto k = inside ? &k3_step<S, true, false>
+                         : (whole ? &k3_step<S, false, true> : &k3_step<S, false, false>);
             hipLaunchKernelGGL(k, dim3(nb), dim3(B3), 0, c->stream, src, dst, c->K, L);
         });
         c->cur ^= 1;

@@ -1,6 +1,7 @@
-"""FP16 layers whose planes are whole cache lines, heated from below and periodic in x and y (the wall
-blocks lead the launch), against the 3-D oracle: planes smaller and larger than a block, walls that
-leave the last wall block unfilled, one interior plane per slab and many.
+"""FP16 steps against the 3-D oracle: layers whose planes are whole cache lines, heated from below and
+periodic in x and y (the wall blocks lead the launch), with planes smaller and larger than a block,
+walls that leave the last wall block unfilled, one interior plane per slab and many; and x walls on
+both sides of the row length from which the interior blocks take them.
 
 Tolerance on the populations, from 12 steps of rounding, relative to the largest deviation from the
 state of rest: a stored value is rounded to 2^-11 of itself, and twice that is allowed per step."""
@@ -14,16 +15,19 @@ pytestmark = pytest.mark.gpu
 STEPS = 12
 
 
-@pytest.mark.parametrize("seed,nx,ny,nz,ef", [
-    (61, 64, 1, 4, False), (62, 16, 12, 33, True), (63, 32, 10, 20, False), (64, 64, 40, 6, True), (65, 192, 11, 5, False),
+@pytest.mark.parametrize("seed,nx,ny,nz,px,py,ef", [
+    (61, 64, 1, 4, 1, 1, False), (62, 16, 12, 33, 1, 1, True), (63, 32, 10, 20, 1, 1, False), (64, 64, 40, 6, 1, 1, True),
+    (65, 192, 11, 5, 1, 1, False),
+    (66, 10, 9, 8, 0, 0, True), (67, 15, 14, 6, 0, 1, False), (68, 15, 6, 7, 0, 0, True), (69, 16, 14, 6, 0, 1, False),
+    (70, 16, 6, 7, 0, 0, True),
 ])
-def test_step_matches_oracle(seed, nx, ny, nz, ef):
+def test_step_matches_oracle(seed, nx, ny, nz, px, py, ef):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import oracle.oracle3 as O3
     from paper_1505_02976_amd import lbm3d
-    cfg = W.random_case3d(seed, nx, ny, nz, eps_field=ef, storage="f16")
+    cfg = W.random_case3d(seed, nx, ny, nz, eps_field=ef, storage="f16", periodic_x=px, periodic_y=py)
     print(f"case: f16 {nx} x {ny} x {nz} field {ef}", flush=True)
     sim = lbm3d.Sim3(cfg)
     sim.step(STEPS)
