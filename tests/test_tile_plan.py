@@ -64,8 +64,8 @@ def plan(tmp_path_factory):
     # walls few nodes apart; one wavefront of the passes across, one and a little
     (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 30303, 33, 0, 3), (F32, 60606, 33, 0, 4),
     (F64, 32, 100000, 0, 1), (F64, 64, 3906, 1, 1), (F64, 40, 60000, 0, 2), (F16, 80, 30000, 1, 2),
-    # one block: any number
-    (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 1),
+    # one block: any number, but for one step between walls
+    (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 2), (F16, 22, 22, 0, 1),
 ])
 def test_fewest_steps_of_a_launch(plan, storage, nx, ny, field, least):
     most, got, _, _, _ = plan(storage, [(nx, ny, 1)], field)
