@@ -39,7 +39,6 @@ template <typename R> struct AdjK {
     Cst<R> k;
     R T0;
     double nuK, isqK;            // nu / K, 1 / sqrt(K)
-    bool ergun;
 };
 
 // Porosity of a node: coefficients, F_eps and d(eps F_eps) / d eps (Sec. 2: F_eps from the Ergun
@@ -528,7 +527,6 @@ template <typename R> __device__ __forceinline__ void adj_consts(KConst p, AdjK<
     c.T0 = R(p->T0);
     c.nuK = p->nu_over_K;
     c.isqK = p->inv_sqrtK;
-    c.ergun = p->ergun != 0;
 }
 
 // What the two kinds of wavefronts of a block share.
