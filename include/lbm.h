@@ -149,7 +149,11 @@ lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_
  * x = 0, x = nx - 1 together with the walled rows.  Grids up to about 5 (FP64), 3.5 (FP32)
  * and 2.3 (FP16) million nodes (with a porosity field 12.5, 12.5 and 6.5) run, until lbm_set_fusion is called, as launches of several
  * steps (up to 8, any number on a grid of at most 512 nodes) whose blocks keep a tile of the
- * grid in LDS; the results are again bitwise those of single steps. */
+ * grid in LDS; the results are again bitwise those of single steps.
+ * A call may be captured into a graph (after one call outside a capture, which creates the second
+ * stream).  Replays go on where the last one ended if the call leaves the state in the buffer it started
+ * from: calls of two steps and more on tiles do, calls of passes if they take an even number of
+ * passes and single steps. */
 lbm_status lbm_step(lbm_ctx *ctx, int64_t nsteps);
 
 /* Non-finite detection inside lbm_step: with every > 0, whenever the context's time

@@ -240,12 +240,11 @@ static void *next_buf(lbm_ctx *c) { return c->ws + (c->cur ? c->lay.off_a : c->l
 // Count of finished blocks of the reductions: zero between launches (set by lbm_init).
 static unsigned *done_of(const lbm_ctx *c) { return reinterpret_cast<unsigned *>(c->ws + c->lay.off_scalar + 200); }
 
-// nsteps in as few launches of at most `most` steps as it takes, of equal numbers of steps to
-// within one.  f(n) enqueues n steps.
-template <typename F> hipError_t by_launches(int64_t nsteps, int most, F &&f)
+// nsteps in `launches` launches of equal numbers of steps to within one.  f(n) enqueues n steps.
+template <typename F> hipError_t by_launches(int64_t nsteps, int64_t launches, F &&f)
 {
     hipError_t e = hipSuccess;
-    for (int64_t left = nsteps, l = nsteps > 0 ? (nsteps + most - 1) / most : 0; l > 0 && e == hipSuccess; --l) {
+    for (int64_t left = nsteps, l = launches; l > 0 && e == hipSuccess; --l) {
         const int n = (int)((left + l - 1) / l);
         e = f(n);
         left -= n;
@@ -253,13 +252,32 @@ template <typename F> hipError_t by_launches(int64_t nsteps, int most, F &&f)
     return e;
 }
 
-// How many of nsteps steps go by launches on tiles (the first ones): all where equal launches take
-// `least` steps or more each, otherwise those of full launches.
-static int64_t tile_share(int64_t nsteps, const lbm::TileSteps &t)
+// The steps of a call that go by launches on tiles (the first ones) and how many launches they take,
+// as few as possible: all steps where equal launches take `least` steps or more each, otherwise
+// those of full launches.
+struct TileShare { int64_t steps, launches; };
+
+static TileShare tile_share(int64_t nsteps, const lbm::TileSteps &t)
 {
-    if (t.most < 1 || nsteps < 1) return 0;
-    const int64_t launches = (nsteps + t.most - 1) / t.most;
-    return nsteps / launches >= t.least ? nsteps : nsteps / t.most * t.most;
+    if (t.most < 1 || nsteps < 1) return {0, 0};
+    const int64_t l = (nsteps + t.most - 1) / t.most;
+    if (nsteps / l >= t.least) return {nsteps, l};
+    return {nsteps / t.most * t.most, nsteps / t.most};
+}
+
+// The same for a call on `stream`, whose other steps go by passes of `fuse` steps.  Every launch and
+// pass writes the other population buffer.  A call that is being captured into a graph is replayed
+// from the buffer it started from, so it takes one launch more where it would end in the
+// other one (a single step ends there in any case).
+static TileShare tile_share(int64_t nsteps, const lbm::TileSteps &t, int fuse, hipStream_t stream)
+{
+    TileShare s = tile_share(nsteps, t);
+    if (s.steps <= s.launches) return s;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+    const int64_t rest = nsteps - s.steps;
+    if (status == hipStreamCaptureStatusActive && (s.launches + (fuse == 2 ? rest / 2 + rest % 2 : rest)) % 2) ++s.launches;
+    return s;
 }
 
 extern "C" {
@@ -441,10 +459,10 @@ hipError_t run_passes(lbm_ctx *c, int64_t npass, const StepEvents *tev, int ever
     return e;
 }
 
-// nsteps steps as launches of several steps on tiles.
-hipError_t tile_steps(lbm_ctx *c, int64_t nsteps)
+// Launches of several steps on tiles.
+hipError_t tile_steps(lbm_ctx *c, const TileShare &share)
 {
-    return by_launches(nsteps, c->tsteps.most, [&](int n) {
+    return by_launches(share.steps, share.launches, [&](int n) {
         const hipError_t e = lbm::launch_tile(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->tile, n, 0, c->stream);
         if (e == hipSuccess) {
             c->t += n;
@@ -458,9 +476,9 @@ hipError_t tile_steps(lbm_ctx *c, int64_t nsteps)
 // grid takes them).
 hipError_t single_steps(lbm_ctx *c, int64_t n)
 {
-    const int64_t tiles = tile_share(n, c->tsteps);
+    const TileShare tiles = tile_share(n, c->tsteps);
     hipError_t e = tile_steps(c, tiles);
-    for (n -= tiles; n > 0 && e == hipSuccess; --n) {
+    for (n -= tiles.steps; n > 0 && e == hipSuccess; --n) {
         e = lbm::launch_step(c->prm.storage, cur_buf(c), next_buf(c), c->kp, c->stream);
         if (e == hipSuccess) {
             c->t += 1;
@@ -474,15 +492,15 @@ hipError_t single_steps(lbm_ctx *c, int64_t n)
 hipError_t states_after(const lbm_ctx *c, const char *src, char *dst, size_t stride, int64_t n)
 {
     const int sto = c->prm.storage;
-    const int64_t tiles = c->tsteps.every ? tile_share(n, c->tsteps) : 0;
-    hipError_t e = by_launches(tiles, c->tsteps.most, [&](int k) {
+    const TileShare tiles = c->tsteps.every ? tile_share(n, c->tsteps) : TileShare{0, 0};
+    hipError_t e = by_launches(tiles.steps, tiles.launches, [&](int k) {
         const hipError_t r = lbm::launch_tile(sto, src, dst, c->kp, c->tile, k,
                                               (long long)(stride / elem_size(sto)), c->stream);
         src = dst + (size_t)(k - 1) * stride;
         dst += (size_t)k * stride;
         return r;
     });
-    for (n -= tiles; n > 0 && e == hipSuccess; --n) {
+    for (n -= tiles.steps; n > 0 && e == hipSuccess; --n) {
         e = lbm::launch_step(sto, src, dst, c->kp, c->stream);
         src = dst;
         dst += stride;
@@ -501,8 +519,9 @@ hipError_t run_steps(lbm_ctx *c, int64_t nsteps, const StepEvents *tev, int ever
     const int sto = c->prm.storage;
     int64_t s = 0, gi = 0;
     if (!tev) {
-        s = tile_share(nsteps, c->tsteps);
-        e = tile_steps(c, s);
+        const TileShare tiles = tile_share(nsteps, c->tsteps, c->fuse, c->stream);
+        e = tile_steps(c, tiles);
+        s = tiles.steps;
     }
     if (c->fuse == 2 && nsteps - s >= 2 && e == hipSuccess) {
         const int64_t npass = (nsteps - s) / 2;
@@ -950,7 +969,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint *a, double dJ, double *grad)
         e = states_after(c, ck, seg(1), a->pop, t1 - t0 - 1);
         int i = (int)(t1 - t0 - 1);
         if (e == hipSuccess)
-            e = by_launches(t1 - t0, steps, [&](int n) {
+            e = by_launches(t1 - t0, (t1 - t0 + steps - 1) / steps, [&](int n) {
                 A.mu_in = mu[cur];
                 A.mu_out = mu[cur ^ 1];
                 const hipError_t r = lbm::launch_adjoint_steps(c->prm.storage, ck, seg(0), stride, c->kp, A, grid,
@@ -1410,8 +1429,9 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
 {
     if (!b) return fail(LBM_ERR_INVALID, "batch is NULL");
     if (nsteps < 0) return fail(LBM_ERR_INVALID, "nsteps < 0");
-    int64_t left = nsteps - tile_share(nsteps, b->tsteps);
-    hipError_t e = by_launches(nsteps - left, b->tsteps.most, [&](int n) { return batch_tiles(b, n); });
+    const TileShare tiles = tile_share(nsteps, b->tsteps, b->fuse, b->stream);
+    int64_t left = nsteps - tiles.steps;
+    hipError_t e = by_launches(tiles.steps, tiles.launches, [&](int n) { return batch_tiles(b, n); });
     if (e != hipSuccess) return hip_fail(e, "batch tiles");
     if (b->fuse == 2 && left > 1) {
         e = batch_passes(b, left / 2, true, b->w2);

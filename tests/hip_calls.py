@@ -23,7 +23,7 @@ SOURCE = r"""
 struct dim3 { unsigned x, y, z; };
 static std::string text;
 static int left_copies = -1, left_allocs = -1;      // calls until one fails, -1: none does
-static int mode = 0;
+static int mode = 0, capturing = 0;
 static dim3 g_grid, g_block;
 static bool failing(int &n) { return n >= 0 && n-- == 0; }
 static int left_news = -1;
@@ -80,6 +80,8 @@ int hipHostMalloc(void **p, size_t n, unsigned)
 }
 int hipThreadExchangeStreamCaptureMode(int *m) { std::swap(*m, mode); return 0; }
 int calls_mode() { return mode; }
+void calls_capturing(int on) { capturing = on; }
+int hipStreamIsCapturing(void *, int *status) { *status = capturing; return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipGetSymbolAddress(void **p, const void *) { *p = calloc(1, 1 << 22); return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1.0f; return 0; }
