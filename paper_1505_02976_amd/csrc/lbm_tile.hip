@@ -416,7 +416,7 @@ constexpr long long TILE_STEPS1[3] = {180000, 270000, 450000}, TILE_STEPS2[3] = 
 constexpr long long TILE_STEPS3[2] = {2500000, 3000000};                        // FP32; with a field
 constexpr long long TILE_STEPS3_FLAT[3] = {900000, 1800000, 1500000};           // FP64 with a field, FP32, FP16 one or two tiles high
 constexpr int TILE_THIN = 32, TILE_NEAR = 150;
-constexpr double TILE_NEAR_BY[2][3] = {{2.0, 1.5, 1.6}, {1.2, 1.15, 1.5}};      // for one and for two steps
+constexpr double TILE_NEAR_BY[2][3] = {{2.0, 1.7, 1.6}, {1.2, 1.15, 1.5}};      // for one and for two steps
 constexpr long long TILE_STEPS1_BATCH[3] = {550000, 430000, 600000}, TILE_STEPS2_BATCH[3] = {1050000, 1200000, 2500000};
 constexpr long long TILE_STEPS3_BATCH = 2800000;                                // FP32, grids of TILE_LARGE on average
 constexpr long long TILE_SMALL = 100000;                                        // FP16: grids below on average, any two

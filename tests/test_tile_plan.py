@@ -62,7 +62,7 @@ def plan(tmp_path_factory):
     (F32, 1800, 1900, 0, 4), (F32, 1650, 1657, 1, 3), (F32, 2200, 2200, 1, 4),
     (F16, 640, 647, 0, 1), (F16, 850, 857, 0, 2), (F16, 1250, 1257, 0, 3),
     # walls few nodes apart; one wavefront of the passes across, one and a little
-    (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 30303, 33, 0, 3), (F32, 60606, 33, 0, 4),
+    (F64, 124, 1209, 0, 2), (F64, 2500, 60, 1, 2), (F32, 14705, 17, 1, 2), (F32, 64, 9375, 0, 2), (F32, 30303, 33, 0, 3), (F32, 60606, 33, 0, 4),
     (F64, 32, 100000, 0, 1), (F64, 64, 3906, 1, 1), (F64, 40, 60000, 0, 2), (F16, 80, 30000, 1, 2),
     # one block: any number, but for one step between walls
     (F64, 4, 64, 0, 1), (F32, 22, 22, 0, 2), (F16, 22, 22, 0, 1),
