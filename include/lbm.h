@@ -131,9 +131,10 @@ size_t lbm_workspace_bytes(const lbm_params *params);
  * lbm_workspace_bytes(params) bytes, 256-byte aligned, owned by the caller and kept alive
  * until lbm_destroy; the library owns its contents.  hip_stream: a hipStream_t (NULL =
  * default stream).  Enqueues the initialisation.  *out receives a context that the
- * caller releases with lbm_destroy.  The first context of a process (lbm3_init as well) allocates
- * 64 KiB of pinned host memory, held until the process ends, through which up to 1024 contexts
- * return the values of lbm_residual and lbm_nusselt; further ones copy them from the device. */
+ * caller releases with lbm_destroy.  The first context of a process (lbm3_init as well; the next one
+ * where that fails) allocates 64 KiB of pinned host memory, held until the process ends, through
+ * which up to 1024 contexts return the values of lbm_residual and lbm_nusselt; further ones copy
+ * them from the device. */
 lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_bytes,
                     void *hip_stream, lbm_ctx **out);
 
@@ -147,9 +148,11 @@ lbm_status lbm_init(const lbm_params *params, void *workspace, size_t workspace_
  * ordered with the caller's stream by events), the launches next to the walled rows.  A
  * single step is two launches: the interior columns, then the columns next to the walls
  * x = 0, x = nx - 1 together with the walled rows.  Grids up to about 5 (FP64), 3.5 (FP32)
- * and 2.3 (FP16) million nodes (with a porosity field 12.5, 12.5 and 6.5) run, until lbm_set_fusion is called, as launches of several
- * steps (up to 8, any number on a grid of at most 512 nodes) whose blocks keep a tile of the
- * grid in LDS; the results are again bitwise those of single steps.
+ * and 2.3 (FP16) million nodes (with a porosity field 12.5, 12.5 and 4.2; fewer between walls less than
+ * some 600 rows apart) run, until lbm_set_fusion is called, as launches of several steps (up to 8,
+ * any number on a grid of at most 512 nodes) whose blocks keep a tile of the grid in LDS; steps that
+ * are left over and calls too short to pay there run as passes and single steps.  The results
+ * are again bitwise those of single steps.
  * A call may be captured into a graph (after one call outside a capture, which creates the second
  * stream).  Replays go on where the last one ended if the call leaves the state in the buffer it started
  * from: calls of two steps and more on tiles do, calls of passes if they take an even number of
@@ -214,13 +217,15 @@ lbm_status lbm_residual(lbm_ctx *ctx, double *r_u_host, double *r_T_host);
 
 /* As lbm_residual, for callers that cannot allocate device memory (code under stream
  * capture set-up, tight serving loops, harnesses that forbid allocation): the reduction's
- * partial sums and totals go to a device-resident scratch array of the library
+ * partial sums (and its totals, in a context without a pinned slot, lbm_init) go to a
+ * device-resident scratch array of the library
  * (LBM_STATIC_SCRATCH_BYTES per device, allocated once when the library is loaded and held
  * until the process ends; its address is looked up by lbm_init on the current device) instead
  * of the context's workspace.  The snapshot stays in the workspace, so both functions share
- * one snapshot and either may follow the other.  The call allocates nothing.  Grids whose
- * partial sums do not fit (more than (LBM_STATIC_SCRATCH_BYTES - 256) / 40 reduction blocks of
- * 256 nodes, i.e. about 26.8 M nodes) return LBM_ERR_INVALID with a message.  Every call on a
+ * one snapshot and either may follow the other.  The call allocates nothing.  Grids of more than
+ * (LBM_STATIC_SCRATCH_BYTES - 256) / 40 runs of 256 nodes (about 26.8 M nodes, the wall nodes counted
+ * again) return LBM_ERR_INVALID with a message: a partial sum for each would not fit (the
+ * reduction uses 2048 at most; the bound is the interface's).  Every call on a
  * device uses that device's one array: calls that overlap on one device (other streams, other
  * threads) race and must be serialized by the caller; nothing in the array needs clearing
  * between calls.  Synchronizes. */
@@ -257,10 +262,11 @@ lbm_status lbm_batch_init(const lbm_params *params, int32_t n, void *workspace, 
  * stream of the batch beside its main launch, ordered by events; the call is ordered like
  * launches on the batch's stream), then one single step if nsteps is odd.  With one step
  * per pass: whole HIP graphs of 64 steps (built on the first call that needs one), then
- * single steps.  Batches of up to about 4 (FP64) and 6 (FP32) million nodes, and FP16 batches of
- * grids of up to about 2 million each on average, run, until lbm_batch_set_fusion,
+ * single steps.  Batches of up to about 4 (FP64) and 3.5 to 6 (FP32) million nodes, and FP16 batches
+ * of grids of up to about 1.7 million each on average, run, until lbm_batch_set_fusion,
  * lbm_batch_set_width or lbm_batch_autotune is called, as launches of several steps on tiles, as
- * lbm_step's small grids do.  Results are bitwise those of lbm_step on each problem alone.  Asynchronous. */
+ * lbm_step's small grids do.  May be captured as lbm_step may.  Results are bitwise those of
+ * lbm_step on each problem alone.  Asynchronous. */
 lbm_status lbm_batch_step(lbm_batch *batch, int64_t nsteps);
 
 /* Time steps per batched pass, 1 or 2 (as lbm_set_fusion, for all problems at once).  The

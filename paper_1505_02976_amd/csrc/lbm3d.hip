@@ -780,7 +780,7 @@ __device__ __forceinline__ void k3_wall_node(const S *__restrict__ src, S *__res
 // more, with the wall blocks' spills, takes longer also where the step is bound by memory:
 // 192 x 192 x 96 FP64 416 against 401 us, FP32 199 against 195, the FP64 box 162 against 146,
 // 120 x 4 x 120 FP64 11.8 against 10.7.  FP16 runs five with 10 spilled registers: 42 us against
-// 44 with four, 75 with six.
+// 44 with four, 75 with six (21 spilled registers where the wall path is there twice, for the leading blocks).
 template <typename S> struct StepWaves { static constexpr int v = sizeof(S) == 8 ? 2 : (sizeof(S) == 4 ? 4 : 5); };
 
 template <typename S, bool XW, bool NT>
@@ -788,6 +788,8 @@ __global__ void __launch_bounds__(B3, (StepWaves<S>::v))
 k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, Slabs L)
 {
     unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
+    // one call of k3_wall_node for both kinds of wall blocks spills less but takes longer: 192 x 192 x 96 FP16
+    // 108.0 us a step against 107.3
     if (NT && sizeof(S) == 2) {
         if (b < L.lead) {
             const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, i = b * B3 + threadIdx.x;
@@ -893,8 +895,8 @@ __device__ __forceinline__ double block_sum(double v, double *part)
 // The work is one latency: a cell loads the 19 temperature populations of three nodes.  One
 // cell per thread over as many blocks as that takes keeps every cell's loads in flight
 // together: a call on the 192 x 192 wall of an FP32 layer took 391 us with one block walking
-// the wall and takes 30 us, on the 95 x 83 adiabatic-edged wall of an FP16 box with porosity
-// per node 670 us and 54 us.
+// the wall and takes 21 us, on the 95 x 83 adiabatic-edged wall of an FP16 box with porosity
+// per node 670 us and 42 us.
 // Each block leaves its sum in part[], the block that finishes last adds those in
 // a fixed order: the FP64 result does not depend on which one that is.
 template <typename S>
@@ -1152,8 +1154,8 @@ Slabs slabs_of(const K3 &K, bool whole, bool half, bool inside)
     L.zw = K.pz || lead ? 0 : (unsigned)((2LL * pl + L.count - 1) / L.count);
     L.nbw = blocks_for((long long)L.walls * L.planes + L.zw);
     // large layers are bound by memory: wall blocks are filled (the last slabs have no z wall nodes
-    // left), 192 x 192 x 96 FP32 192 us a step instead of 193.5, 64 x 64 x 96 FP16 16.9 instead of 19.4;
-    // on rows with x walls the grids are often too small for that, 120 x 4 x 120 12.1 instead of 10.5
+    // left), 192 x 192 x 96 FP32 192 us a step instead of 193.5; on rows with x walls the grids are often
+    // too small for that, 120 x 4 x 120 12.1 instead of 10.5
     if (whole && !K.pz && !lead) L.zw = L.nbw * B3 - L.walls * L.planes;
     L.nbi = blocks_for((long long)L.inner * L.planes);
     return L;

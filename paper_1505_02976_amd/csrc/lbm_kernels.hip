@@ -357,7 +357,7 @@ __device__ __forceinline__ void node_any(const S *__restrict__ src, const KParam
 }
 
 // All nodes in one launch: a launch of their own for the wall nodes costs as much as the
-// interior's on small grids (moments and gradients of 4 x 64 FP64 43 -> 35 us a call, of
+// interior's on small grids (moments and gradients of 4 x 64 FP64 43 -> 31 us a call, of
 // 600 x 700 FP64 58 -> 51, of 4096 x 4096 FP32 598 -> 580, which is bound by memory).
 template <typename S, typename R>
 __global__ void __launch_bounds__(BULK_BX)
@@ -427,9 +427,9 @@ __device__ __forceinline__ bool grid_sum(double v[V], double (*sm)[RED_B], doubl
 // One launch over all nodes, at most RESID_BLOCKS blocks that each take every gridDim.x-th run
 // of RED_B nodes (dx, dy: that stride in columns and rows).  The pass is bound by memory; the
 // bounded number of blocks keeps the sum over them (a second launch) short.  Against one block
-// per RED_B nodes and another launch for the wall nodes a call takes 25 instead of 35 us
-// (4 x 64 FP64), 30 instead of 38 (250 x 250 FP32), 87 instead of 102 (1537 x 1025 FP64), 500
-// instead of 540 (4096 x 4096 FP32); 1024 to 4096 blocks differ by 2 %.  Adding up in the block
+// per RED_B nodes and another launch for the wall nodes a call takes 20 instead of 33 us
+// (4 x 64 FP64; 5 us of it by the pinned slot), 20 instead of 37 (250 x 250 FP32), 75 instead of 100
+// (1537 x 1025 FP64), 479 instead of 533 (4096 x 4096 FP32); 1024 to 4096 blocks differ by 2 %.  Adding up in the block
 // that finishes last (as k_nusselt does over its few blocks) is slower here: every block's
 // release flushes the snapshot it has just written out of the L2, 50 us over 1640 blocks.
 template <typename S, typename R>
@@ -519,7 +519,7 @@ __device__ __forceinline__ double node_Td(const S *__restrict__ src, const KPara
 // One thread per node of the three layers, NUS_J wall nodes per block: a call is one latency,
 // the loads of one node (of two on a prescribed-gradient wall).  With one block whose threads
 // took the three nodes one after the other and walked the wall a call took 31 us (128 x 128
-// FP64) and 108 us (4096 x 4096 FP32), now 26 and 28.
+// FP64) and 108 us (4096 x 4096 FP32), now 17 and 17 (through the pinned slot).
 constexpr int NUS_J = RED_B / 3;
 
 template <typename S, typename R>
@@ -899,6 +899,8 @@ long long interior_nodes(int storage, const KParams &P)
                         : (storage == 1 ? interior_nodes_t<float>(P) : interior_nodes_t<__half>(P));
 }
 
+// Partial sums that a workspace has room for and that bound lbm_residual_noalloc: one per RED_B nodes and
+// per RED_B wall nodes.  k_resid uses RESID_BLOCKS at most, k_nusselt one per NUS_J wall nodes.
 long long residual_partials(const KParams &P)
 {
     const long long N = (long long)P.nx * P.ny;
