@@ -582,9 +582,11 @@ __host__ __device__ __forceinline__ int inner_z(const K3 &K) { return K.pz ? K.n
 // are not: 14 x 180 x 60 14.2 and 14.1, 16 x 40 x 40 12.2 and 9.4.  Below XW_ROW a block would hold more than
 // 68 such nodes.
 constexpr int XW_ROW = 8, XW_ROW_F16 = 14;
-// FP16 layers of whole cache lines (the z walls alone) have the blocks of both walls ahead of the first
-// slab instead (`lead`): 192 x 192 x 96 107.5 us a step, spread over the slabs 108.7, 64 x 64 x 96 with porosity
-// per node 16.8 and 17.3, 192 x 100 x 50 33.3 and 34.1.
+// FP16 grids of whole cache lines have all wall blocks ahead of the first slab instead (`lead`): layers
+// 192 x 192 x 96 107.5 us a step, spread over the slabs 108.7, 64 x 64 x 96 with porosity per node 16.8 and 17.3,
+// with y walls 128 x 100 x 30 16.4 and 18.9, with y walls alone 128 x 128 x 64 36.9 and 41.9; FP32 grids where
+// the y walls are the only ones: 128 x 128 x 64 62.4 and 66.6, 128 x 12 x 200 20.4 and 21.6.  FP32 layers and FP64
+// grids are not (192 x 100 x 50 57.3 and 56.7; FP64 with y walls 110 and 108).
 struct Slabs {
     unsigned planes, count;
     unsigned inner, walls, zw;     // interior and wall nodes per plane, z wall nodes per slab
@@ -790,12 +792,26 @@ k3_step(const S *__restrict__ src, S *__restrict__ dst, K3 K, Slabs L)
     unsigned b = NT ? blockIdx.x : (unsigned)lbm::xcd_block((int)blockIdx.x, (int)gridDim.x);
     // one call of k3_wall_node for both kinds of wall blocks spills less but takes longer: 192 x 192 x 96 FP16
     // 108.0 us a step against 107.3
-    if (NT && sizeof(S) == 2) {
+    if (NT && sizeof(S) <= 4) {
         if (b < L.lead) {
-            const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, i = b * B3 + threadIdx.x;
-            if (i >= 2 * pl) return;
-            const unsigned k = i < pl ? i : i - pl, y = k / (unsigned)K.nx;
-            k3_wall_node<S, NT>(src, dst, K, (int)(k - y * (unsigned)K.nx), (int)y, i < pl ? 0 : K.nz - 1);
+            // the y walls of all interior planes (2 nx nodes each), then the two z walls
+            const unsigned nx = (unsigned)K.nx, ny = (unsigned)K.ny, pl = nx * ny, ys = (unsigned)inner_z(K) * L.walls;
+            unsigned i = b * B3 + threadIdx.x, x, y, z;
+            if (i < ys) {
+                z = i / L.walls;
+                i -= z * L.walls;
+                z += K.pz ? 0 : 1;
+                y = i < nx ? 0 : ny - 1;
+                x = i < nx ? i : i - nx;
+            } else {
+                i -= ys;
+                if (K.pz || i >= 2 * pl) return;
+                z = i < pl ? 0 : (unsigned)K.nz - 1;
+                i = i < pl ? i : i - pl;
+                y = i / nx;
+                x = i - y * nx;
+            }
+            k3_wall_node<S, NT>(src, dst, K, (int)x, (int)y, (int)z);
             return;
         }
         b -= L.lead;
@@ -1141,7 +1157,7 @@ template <typename S> bool lines_whole(const K3 &K)
 
 template <typename S> bool x_walls_inside(const K3 &K) { return !K.px && inner_x(K) >= (sizeof(S) == 2 ? XW_ROW_F16 : XW_ROW); }
 
-Slabs slabs_of(const K3 &K, bool whole, bool half, bool inside)
+Slabs slabs_of(const K3 &K, int storage, bool whole, bool inside)
 {
     Slabs L;
     const unsigned pl = (unsigned)K.nx * (unsigned)K.ny, nz = (unsigned)inner_z(K);
@@ -1149,10 +1165,10 @@ Slabs slabs_of(const K3 &K, bool whole, bool half, bool inside)
     L.walls = inside ? (K.py ? 0 : 2 * (unsigned)K.nx) : pl - L.inner;
     L.planes = std::min(nz, std::max(1u, (SLAB_NODES + L.inner - 1) / L.inner));
     L.count = (nz + L.planes - 1) / L.planes;
-    const bool lead = half && whole && K.py && !K.pz;
-    L.lead = lead ? blocks_for(2LL * pl) : 0;
+    const bool lead = whole && (storage == LBM_F16 || (storage == LBM_F32 && K.pz));
+    L.lead = lead ? blocks_for((long long)L.walls * nz + (K.pz ? 0 : 2LL * pl)) : 0;
     L.zw = K.pz || lead ? 0 : (unsigned)((2LL * pl + L.count - 1) / L.count);
-    L.nbw = blocks_for((long long)L.walls * L.planes + L.zw);
+    L.nbw = lead ? 0 : blocks_for((long long)L.walls * L.planes + L.zw);
     // large layers are bound by memory: wall blocks are filled (the last slabs have no z wall nodes
     // left), 192 x 192 x 96 FP32 192 us a step instead of 193.5; on rows with x walls the grids are often
     // too small for that, 120 x 4 x 120 12.1 instead of 10.5
@@ -1224,7 +1240,7 @@ lbm_status lbm3_step(lbm3_ctx *c, int64_t nsteps)
         whole = lines_whole<typename decltype(t)::type>(c->K);
         inside = x_walls_inside<typename decltype(t)::type>(c->K);
     });
-    const Slabs L = slabs_of(c->K, whole, c->storage == LBM_F16, inside);
+    const Slabs L = slabs_of(c->K, c->storage, whole, inside);
     const unsigned nb = L.lead + L.count * (L.nbw + L.nbi);
     for (int64_t s = 0; s < nsteps; ++s) {
         by_storage(c->storage, [&](auto t) {
